@@ -50,6 +50,14 @@ struct LaunchArgs {
 
 hipError_t launch(const LaunchArgs &a);
 
+// one per stencil family (step_*.hip)
+hipError_t launch_prod2d(const LaunchArgs &a);
+hipError_t launch_prod3d(const LaunchArgs &a);
+hipError_t launch_ur2d(const LaunchArgs &a);
+hipError_t launch_ur3d(const LaunchArgs &a);
+hipError_t launch_massive2d(const LaunchArgs &a);
+hipError_t launch_massive3d(const LaunchArgs &a);
+
 enum AdjOp : int { ADJ_STEP = 0, ADJ_MOMENTS = 1, ADJ_INIT = 2 };
 
 struct AdjointArgs {
