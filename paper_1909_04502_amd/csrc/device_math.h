@@ -167,9 +167,9 @@ __device__ __forceinline__ bool landau_frame(const double (&T)[D + 1][D + 1], do
 // d = 2: G_2 = (z^2 + 3z + 3)/(z + 1), so e = eps/n solves
 //   2 T^2 + (2m - e) T + m^2 - e m = 0;
 // the positive root is taken in the form that avoids cancellation.
-// d = 3: G_3 = z r + 4 with r = K1/K2 from a Chebyshev fit in log z, so that
-// e = eps/n = m r(m/T) + 3 T; its inverse T(e) is a second fit (built on the
-// host from the first by Newton's method).
+// d = 3: G_3 = z r + 4 with r = K1/K2, so that e = eps/n = m r(m/T) + 3 T; the
+// inverse T(e) and r(m/T(e)) are Chebyshev fits in log(e - m) (built on the host
+// by Newton's method), and r(z) one in log z for prescribed temperatures.
 // ---------------------------------------------------------------------------
 // Macroscopic state of a site (double).
 template <int D>
@@ -204,50 +204,85 @@ __device__ __forceinline__ Ratios ratios_2d(double z) {
   return r;
 }
 
-__device__ __forceinline__ double cheb_eval(const double *__restrict__ c, double s) {
-  double b1 = 0.0, b2 = 0.0;
-#pragma unroll 4
-  for (int k = kEosTerms - 1; k >= 1; --k) {
-    double b0 = 2.0 * s * b1 - b2 + c[k];
-    b2 = b1;
-    b1 = b0;
+// NS Chebyshev series of kEosTerms terms (c[0 .. kEosTerms) of the first, then of the next, ...) at the same
+// s in [-1, 1].  The even terms are a series in T_j(y), y = T_2(s), and the odd ones s times a series in
+// V_j(y) = T_(2j+1)(s)/s (V_0 = 1, V_1 = 2y - 1, the same recurrence): each runs as a Clenshaw sum of its
+// own, so that a single site's chain of dependent operations is half as long as over all terms.
+template <int NS>
+__device__ __forceinline__ void cheb_eval(const double *__restrict__ c, double s, double (&v)[NS]) {
+  constexpr int H = kEosTerms / 2;
+  static_assert(kEosTerms % 2 == 0, "even and odd terms");
+  const double w = 2.0 * s, y2 = w * w - 2.0;   // 2 y
+  double e1[NS], e2[NS], o1[NS], o2[NS];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) e1[q] = e2[q] = o1[q] = o2[q] = 0.0;
+#pragma unroll 2
+  for (int k = H - 1; k >= 1; --k) {
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      const double e0 = y2 * e1[q] + (c[q * kEosTerms + 2 * k] - e2[q]);
+      const double o0 = y2 * o1[q] + (c[q * kEosTerms + 2 * k + 1] - o2[q]);
+      e2[q] = e1[q];
+      e1[q] = e0;
+      o2[q] = o1[q];
+      o1[q] = o0;
+    }
   }
-  return s * b1 - b2 + c[0];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) {
+    // the constant term, by far the largest, is added last: one rounding at the size of the result
+    const double odd = (y2 * o1[q] - o2[q]) - o1[q] + c[q * kEosTerms + 1];
+    v[q] = c[q * kEosTerms] + (s * odd + (0.5 * y2 * e1[q] - e2[q]));
+  }
 }
 
-// A piecewise series at u in [-1, 1] (the whole fitted range; clamped): the piece of u and the
-// local variable s in [-1, 1] of that piece (the host's fit uses the same map).  When the wave's
-// sites share a piece (the usual case: temperature varies smoothly) the series is read through
-// uniform (scalar) loads of that piece; a wave that straddles a piece boundary evaluates every
-// piece, each with uniform loads, and keeps its own.
-__device__ __forceinline__ double cheb_eval_pieces(const double (*__restrict__ c)[48], double u) {
+// Piecewise series at u in [-1, 1] (the whole fitted range; clamped): the piece of u and the local
+// variable s in [-1, 1] of that piece (the host's fit uses the same map).
+__device__ __forceinline__ int cheb_piece(double u, double &s) {
   u = fmin(1.0, fmax(-1.0, u));
   const double t = (u + 1.0) * (0.5 * kEosPieces);
   int p = (int)t;
   p = p < 0 ? 0 : (p >= kEosPieces ? kEosPieces - 1 : p);
-  const double s = 2.0 * (t - p) - 1.0;
+  s = 2.0 * (t - p) - 1.0;
+  return p;
+}
+
+// When the wave's sites share a piece (the usual case: temperature varies smoothly) its series are read
+// through uniform (scalar) loads; a wave that straddles a piece boundary evaluates every piece, each with
+// uniform loads, and keeps its own.
+template <int NS>
+__device__ __forceinline__ void cheb_eval_pieces(const double (*__restrict__ c)[NS * kEosTerms], double u, double (&v)[NS]) {
+  double s;
+  const int p = cheb_piece(u, s);
   const int q = __builtin_amdgcn_readfirstlane(p);
-  if (__all(p == q)) return cheb_eval(c[q], s);
-  double r = 0.0;
+  if (__all(p == q)) {
+    cheb_eval<NS>(c[q], s, v);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < NS; ++k) v[k] = 0.0;
 #pragma unroll 1
   for (int k = 0; k < kEosPieces; ++k) {
-    const double v = cheb_eval(c[k], s);
-    r = p == k ? v : r;
+    double r[NS];
+    cheb_eval<NS>(c[k], s, r);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) v[i] = p == k ? r[i] : v[i];
   }
-  return r;
 }
 
 __device__ __forceinline__ double cheb_r(const Tables *__restrict__ tb, double z, bool &inrange) {
-  // Clenshaw on the piece's s in [-1, 1], affine in log z; the series fits h = r (z + 2) / z, which
-  // stays O(1) from z -> 0 (r ~ z/2) to z -> inf (r -> 1)
+  // the piece's s in [-1, 1] is affine in log z; the series fits h = r (z + 2) / z, which stays O(1)
+  // from z -> 0 (r ~ z/2) to z -> inf (r -> 1)
   const double u = (2.0 * log(z) - (tb->cheb_lo + tb->cheb_hi)) / (tb->cheb_hi - tb->cheb_lo);
   inrange = u >= -1.0 && u <= 1.0;
-  return cheb_eval_pieces(tb->cheb, u) * (z / (z + 2.0));
+  double h[1];
+  cheb_eval_pieces<1>(tb->cheb, u, h);
+  return h[0] * (z / (z + 2.0));
 }
 
-// d = 3: T from e = eps/n through the fitted inverse T = (e - m) u(log(e - m)), then r = K1/K2 at
-// z = m/T.  Both fits hold to ~1e-15 on T in [kEosTmin, kEosTmax] = [1/128, 128]; outside that range
-// the site is flagged.
+// d = 3: T from e = eps/n through the fitted inverse T = (e - m) u(x), x = log(e - m), and r = K1/K2 at
+// z = m/T from a series in the same x.  Both fits hold to ~1e-15 on T in [kEosTmin, kEosTmax] =
+// [1/128, 128]; outside that range the site is flagged.
 __device__ __forceinline__ bool temperature_3d(const Tables *__restrict__ tb, double e, double m, double &T,
                                                double &r_out) {
   if (m == 0.0) {
@@ -256,13 +291,16 @@ __device__ __forceinline__ bool temperature_3d(const Tables *__restrict__ tb, do
     return e > 0.0;
   }
   const double d = e - m;
-  bool ok = d > 0.0;
   const double u = (2.0 * log(d) - (tb->chebT_lo + tb->chebT_hi)) / (tb->chebT_hi - tb->chebT_lo);
-  ok = ok && u >= -1.0 && u <= 1.0;
-  T = d * cheb_eval_pieces(tb->chebT, u);
-  bool inr;
-  r_out = cheb_r(tb, m / T, inr);
-  return ok && inr && T > 0.0;
+  double v[2];
+  cheb_eval_pieces<2>((const double (*)[2 * kEosTerms])tb->chebT, u, v);
+  T = d * v[0];
+  // r = h z / (z + 2), for z >= 2 as h - 2 h / (z + 2), whose division's rounding shrinks with z
+  const double z = m / T;
+  const bool cold = z >= 2.0;
+  const double q = (cold ? 2.0 : z) * v[1] / (z + 2.0);
+  r_out = cold ? v[1] - q : q;
+  return d > 0.0 && u >= -1.0 && u <= 1.0 && T > 0.0;
 }
 
 __device__ __forceinline__ Ratios ratios_3d(double z, double r) {

@@ -393,15 +393,19 @@ static void pack_linv(Tables &t) {
 }
 
 // Chebyshev coefficients of f on [-1, 1] (n terms, long double nodes).
-template <class F>
-static void cheb_fit(int n, F f, double *coef) {
+// the k-th of kFitNodes Chebyshev nodes, and the first kEosTerms coefficients of the series through values at
+// all of them (more nodes than terms: the values' own rounding averages out)
+constexpr int kFitNodes = 44;
+static ld cheb_node(int k) {
   const ld pi = 3.141592653589793238462643383279502884L;
-  ld fk[64];
-  for (int k = 0; k < n; ++k) fk[k] = f(cosl(pi * (k + 0.5L) / n));
-  for (int j = 0; j < n; ++j) {
+  return cosl(pi * (k + 0.5L) / kFitNodes);
+}
+static void cheb_coefficients(const ld *fk, double *coef) {
+  const ld pi = 3.141592653589793238462643383279502884L;
+  for (int j = 0; j < kEosTerms; ++j) {
     ld c = 0.0L;
-    for (int k = 0; k < n; ++k) c += fk[k] * cosl(pi * j * (k + 0.5L) / n);
-    c *= 2.0L / n;
+    for (int k = 0; k < kFitNodes; ++k) c += fk[k] * cosl(pi * j * (k + 0.5L) / kFitNodes);
+    c *= 2.0L / kFitNodes;
     if (j == 0) c *= 0.5L;
     coef[j] = (double)c;
   }
@@ -430,10 +434,11 @@ static int cheb_piece(ld u, ld &s) {
 }
 static ld cheb_global(int p, ld s) { return ((s + 1.0L) * 0.5L + p) * (2.0L / kEosPieces) - 1.0L; }
 
-static ld cheb_eval_pieces(const double (*coef)[48], int n, ld u) {
+// `stride`: doubles from a piece's series to the next piece's
+static ld cheb_eval_pieces(const double *coef, int stride, int n, ld u) {
   ld s;
   const int p = cheb_piece(u, s);
-  return cheb_eval(coef[p], n, s);
+  return cheb_eval(coef + p * stride, n, s);
 }
 
 // e - m = m (r(m/T) - 1) + 3 T for d = 3 (e = eps/n = T (G_3 - 1), G_3 = z r + 4), with r from
@@ -447,7 +452,7 @@ static ld kinetic_exact(ld m, ld T, ld &dk) {
 // r(z) = K1/K2 from the fitted series (what the kernels evaluate), and the kinetic energy from it
 static ld r_fitted(const Tables &t, ld z) {
   const ld u = (2.0L * logl(z) - ((ld)t.cheb_lo + (ld)t.cheb_hi)) / ((ld)t.cheb_hi - (ld)t.cheb_lo);
-  return cheb_eval_pieces(t.cheb, t.cheb_n, u) * z / (z + 2.0L);
+  return cheb_eval_pieces(t.cheb[0], kEosTerms, t.cheb_n, u) * z / (z + 2.0L);
 }
 
 // the temperature of kinetic energy d per particle.  kinetic(T) increases in T from 1.5 T (cold)
@@ -493,13 +498,17 @@ int build_eos_fit(double m, Tables &t, std::string &err) {
     const ld z = expl(0.5L * (hi + lo) + 0.5L * (hi - lo) * u);
     return bessel_k(1.0L, z) / bessel_k(2.0L, z) * (z + 2.0L) / z;
   };
-  for (int p = 0; p < kEosPieces; ++p) cheb_fit(n, [&](ld s) { return hfun(cheb_global(p, s)); }, t.cheb[p]);
+  for (int p = 0; p < kEosPieces; ++p) {
+    ld h[kFitNodes];
+    for (int k = 0; k < kFitNodes; ++k) h[k] = hfun(cheb_global(p, cheb_node(k)));
+    cheb_coefficients(h, t.cheb[p]);
+  }
   t.cheb_n = n;
   t.cheb_lo = (double)lo;
   t.cheb_hi = (double)hi;
   for (int k = 0; k <= 64 * kEosPieces; ++k) {
     const ld u = -1.0L + 2.0L * k / (64.0L * kEosPieces), ref = hfun(u);
-    if (fabsl(cheb_eval_pieces(t.cheb, n, u) - ref) > 5e-16L * fabsl(ref)) {
+    if (fabsl(cheb_eval_pieces(t.cheb[0], kEosTerms, n, u) - ref) > 5e-16L * fabsl(ref)) {
       err = "equation-of-state fit failed";
       return RLBM_ERR_QUADRATURE;
     }
@@ -509,17 +518,28 @@ int build_eos_fit(double m, Tables &t, std::string &err) {
   // size m when cold, so it is taken from the long double Bessel functions, not the fitted r)
   ld dk;
   const ld xlo = logl(kinetic_exact(m, tmin, dk)), xhi = logl(kinetic_exact(m, tmax, dk));
-  auto ufun = [&](ld u) {
-    const ld d = expl(0.5L * (xhi + xlo) + 0.5L * (xhi - xlo) * u);
-    return temperature_exact(t, m, d) / d;
+  // T/(e - m) and h(m/T) at the variable u of the whole range
+  auto state = [&](ld u, ld &tq, ld &h) {
+    const ld d = expl(0.5L * (xhi + xlo) + 0.5L * (xhi - xlo) * u), T = temperature_exact(t, m, d), z = m / T;
+    tq = T / d;
+    h = bessel_k(1.0L, z) / bessel_k(2.0L, z) * (z + 2.0L) / z;
   };
-  for (int p = 0; p < kEosPieces; ++p) cheb_fit(n, [&](ld s) { return ufun(cheb_global(p, s)); }, t.chebT[p]);
+  for (int p = 0; p < kEosPieces; ++p) {
+    ld tq[kFitNodes], h[kFitNodes];
+    for (int k = 0; k < kFitNodes; ++k) state(cheb_global(p, cheb_node(k)), tq[k], h[k]);
+    cheb_coefficients(tq, t.chebT[p][0]);
+    cheb_coefficients(h, t.chebT[p][1]);
+  }
   t.chebT_n = n;
   t.chebT_lo = (double)xlo;
   t.chebT_hi = (double)xhi;
   for (int k = 0; k <= 64 * kEosPieces; ++k) {
-    const ld u = -1.0L + 2.0L * k / (64.0L * kEosPieces), ref = ufun(u);
-    if (fabsl(cheb_eval_pieces(t.chebT, n, u) - ref) > 1e-15L * fabsl(ref)) {
+    const ld u = -1.0L + 2.0L * k / (64.0L * kEosPieces);
+    ld tq, h;
+    state(u, tq, h);
+    const int st = 2 * kEosTerms;
+    if (fabsl(cheb_eval_pieces(t.chebT[0][0], st, n, u) - tq) > 1e-15L * fabsl(tq) ||
+        fabsl(cheb_eval_pieces(t.chebT[0][1], st, n, u) - h) > 5e-16L * fabsl(h)) {
       err = "inverse equation-of-state fit failed";
       return RLBM_ERR_QUADRATURE;
     }

@@ -344,7 +344,9 @@ constexpr int kMaxNE = 14, kMaxNO = 16, kMaxNM = 30;
 constexpr int kMaxShell = 4;
 constexpr int kNMom3 = 14;   // 4 (N^a) + 10 (T^ab) in 3D; 2D uses 3 + 6
 
-constexpr int kEosTerms = 44;
+// terms of each series of the 3D equation of state: on a piece the coefficients fall below 1e-17 of the
+// first by the 22nd for masses up to 10 (even: the evaluation takes the even and odd terms apart)
+constexpr int kEosTerms = 24;
 // the 3D equation-of-state fits cover T in [1/128, 128] in kEosPieces pieces of equal width in
 // log T (an odd count: T = 1 lies mid-piece, so lattices near the reference temperature evaluate
 // one piece per wave)
@@ -367,12 +369,13 @@ struct Tables {
   // EOS helper for d = 3: Chebyshev series in log z of h(z) = r(z) (z + 2) / z, r = K1(z)/K2(z),
   // on [cheb_lo, cheb_hi] = [log z_lo, log z_hi], one series per piece of equal width
   double cheb_lo, cheb_hi;
-  double cheb[kEosPieces][48];
+  double cheb[kEosPieces][kEosTerms];
   int32_t cheb_n, chebT_n;
   // and the inverse of the equation of state: T = (e - m) u(x), x = log(e - m), u a Chebyshev
   // series in x on [chebT_lo, chebT_hi] (e = eps/n; the same temperature range), also by pieces
+  // ([0]), next to h at that temperature as a series in the same variable ([1])
   double chebT_lo, chebT_hi;
-  double chebT[kEosPieces][48];
+  double chebT[kEosPieces][2][kEosTerms];
   // per pair of antipodal populations (even member 2pr):
   double c[kMaxPairs][3];       // velocity p^a / p^0
   double mom_e[kMaxPairs][8];   // even moment weights: p0, p0^2, p^a p^b (upper triangle)
