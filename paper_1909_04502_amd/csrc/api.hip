@@ -246,12 +246,7 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   h->cfg = *cfg;
   h->stencil = stencil_of(m);
   // default launch shapes (from sweeps of every variant on MI355X):
-  //  * 3D product rules: 64 x 4 tiles in (y, z) patches per XCD (half the re-reads from beyond
-  //    the L2 of the untiled order: 1.19x the algorithmic bytes instead of 2.35x) with the
-  //    unconstrained build, in float storage (4.39 ms at 256^3 in float arithmetic, 4.56 with
-  //    the occupancy-2 build; 6.67 ms in double arithmetic, whose occupancy-2 build spills); in
-  //    double storage the unconstrained build (468 registers, one wave per SIMD) in untiled
-  //    64 x 4 tiles (10.5 ms, 10.7 in patches);
+  //  * 3D product rules: every variant launches the same kernel in the same shape (split.hip);
   //  * the 3D massive rule: 64 x 2 XCD-ordered tiles (double, streaming kernel) or 64 x 1 patches
   //    (float);
   //  * 2D product rules in double: rows of 64 sites; float storage with double arithmetic: 64 x 4

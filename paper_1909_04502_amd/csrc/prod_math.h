@@ -73,36 +73,21 @@ struct Offs {
 // With TRANSPOSE the taps are mirrored (offset -o, same weight): this applies
 // the transpose of the streaming operator on a periodic grid (the adjoint
 // gather dL/dB(y) = sum_taps w dL/dF(y - o)).
-// 3D: the 26 directions of a shell fall into groups of at most 16 taps (the
-// axes, the edges by fours, the corners by twos); the loads of group g depend
-// (through an empty asm on the plane base) on every population of group g - 3,
-// so at most three groups of taps are in flight per wave instead of all of
-// them, and the registers their loads occupy stay bounded.
-__device__ __forceinline__ constexpr bool group_start_3d(int k) {
-  return k == 0 || k == 6 || k == 10 || k == 14 || k == 18 || k == 20 || k == 22 || k == 24;
-}
-__device__ __forceinline__ constexpr int group_first_3d(int k) { return k < 6 ? 0 : k < 18 ? 6 + 4 * ((k - 6) / 4) : k & ~1; }
-
 // A is the arithmetic type of the interpolation and of the result (the storage type S, or double
 // for float deviations updated in double).
 template <class ST, typename S, bool TRANSPOSE = false, typename A = S>
 __device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S *__restrict__ fin, int64_t sites,
                                           const Offs &o, A (&f)[ST::Q]) {
-  constexpr int D = ST::D, ND = ST::NDIR, KR = ST::NSHELL;
+  static_assert(ST::D == 2, "the 3D rules: split.hip");
+  constexpr int ND = ST::NDIR, KR = ST::NSHELL;
   typedef const __attribute__((address_space(1))) char gchar;   // keeps the loads global after laundering
   gchar *base = (gchar *)fin;
-  // population ranges [first, last] of the previous groups (index 0 most recent); the loads of a
-  // group depend on every population of the group kDepth back
-  constexpr int kDepth = 3;
-  int gfirst[kDepth], glast[kDepth];
-#pragma unroll
-  for (int e = 0; e < kDepth; ++e) gfirst[e] = glast[e] = -1;
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
     const A v = tab<A>(tb->sv[j], tb->svf[j]);
-    A pw[4][4];
+    A pw[3][3];
 #pragma unroll
-    for (int z = 1; z <= D; ++z) {
+    for (int z = 1; z <= 2; ++z) {
       const A mag = v * (A)kInvNorm[z];
       const A cm = (A)1 - mag;
       // pw[z][nf] = mag^nf (1-mag)^(z-nf)
@@ -119,20 +104,13 @@ __device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
       const int i = j * ND + k;
-      if constexpr (D == 3) {
-        if (group_start_3d(k) && glast[kDepth - 1] >= 0) {
-#pragma unroll
-          for (int q = gfirst[kDepth - 1]; q <= glast[kDepth - 1]; ++q) asm volatile("" : "+s"(base) : "v"(f[q]));
-        }
-      }
       gchar *plane = base + (int64_t)i * sites * (int64_t)sizeof(S);
-      const int dx = ST::dir(k, 0), dy = ST::dir(k, 1), dz = D == 3 ? ST::dir(k, D - 1) : 0;
-      const int z = (dx != 0) + (dy != 0) + (dz != 0);
+      const int dx = ST::dir(k, 0), dy = ST::dir(k, 1);
+      const int z = (dx != 0) + (dy != 0);
       A acc = 0;
-      {
 #pragma unroll
       for (int tap = 0; tap < (1 << z); ++tap) {
-        int bit = 0, ox = 0, oy = 0, oz = 0, nfar = 0;
+        int bit = 0, ox = 0, oy = 0, nfar = 0;
         if (dx != 0) {
           const int c = (tap >> bit++) & 1;
           ox = dx > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
@@ -143,32 +121,14 @@ __device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S
           oy = dy > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
           nfar += oy != 0;
         }
-        if (dz != 0) {
-          const int c = (tap >> bit++) & 1;
-          oz = dz > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
-          nfar += oz != 0;
-        }
         if (TRANSPOSE) {
           ox = -ox;
           oy = -oy;
-          oz = -oz;
         }
-        const uint32_t off = o.x[ox + 1] + o.y[oy + 1] + o.z[oz + 1];
+        const uint32_t off = o.x[ox + 1] + o.y[oy + 1];
         acc += pw[z][nfar] * (A) * (const __attribute__((address_space(1))) S *)(plane + off);
       }
       f[i] = acc;
-      }
-      if constexpr (D == 3) {
-        if (k == ND - 1 || group_start_3d(k + 1)) {
-#pragma unroll
-          for (int e = kDepth - 1; e > 0; --e) {
-            gfirst[e] = gfirst[e - 1];
-            glast[e] = glast[e - 1];
-          }
-          gfirst[0] = j * ND + group_first_3d(k);
-          glast[0] = i;
-        }
-      }
     }
   }
 }
@@ -209,6 +169,7 @@ template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT = false>
 __device__ __forceinline__ Macro<ST::D> collide_prod(const Tables *__restrict__ tb, S (&f)[ST::Q], double tau,
                                                      double wallT = -1.0) {
   const bool wall = EXT && wallT >= 0.0;
+  static_assert(ST::D == 2, "the 3D rules: split.hip");
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2, KR = ST::NSHELL;
   using B = BasisDef<D, N>;
   constexpr AngTable<D, N> AT{};
@@ -300,14 +261,8 @@ __device__ __forceinline__ Macro<ST::D> collide_prod(const Tables *__restrict__ 
   mac.n = lorentz_dot<D>(mac.U, Nv);
   const double m = tb->m;
   Ratios rr;
-  if constexpr (D == 2) {
-    mac.ok = temperature_2d(mac.eps / mac.n, m, mac.T) && mac.ok;
-    rr = ratios_2d(m / mac.T);
-  } else {
-    double r;
-    mac.ok = temperature_3d(tb, mac.eps / mac.n, m, mac.T, r) && mac.ok;
-    rr = ratios_3d(m / mac.T, r);
-  }
+  mac.ok = temperature_2d(mac.eps / mac.n, m, mac.T) && mac.ok;
+  rr = ratios_2d(m / mac.T);
   mac.ok = mac.ok && mac.n > 0.0 && mac.eps > 0.0;
   if constexpr (!RELAX) return mac;
   // a no-slip wall site relaxes fully (Omega = 1) to the equilibrium at rest of its own n and
@@ -320,81 +275,35 @@ __device__ __forceinline__ Macro<ST::D> collide_prod(const Tables *__restrict__ 
   if (wall) equilibrium_state<D>(tb, mac, rr, wallT, Te, re);
   // ---- step 5: a' = G^{-1} M over parity blocks ----
   A ap[B::NM];
-  if constexpr (D == 3) {
-    // class by class (moments, shift, L^{-1}, L^{-T}), so that only one block's
-    // temporaries are live next to the populations
-    constexpr ClassTable<D, N> CL{};
-    // the packed blocks are read class by class: laundering the table pointer on the previous
-    // block's result keeps the compiler from hoisting (and spilling) all 91 scalar loads
-    typedef const __attribute__((address_space(4))) double cdouble;
-    cdouble *lp = (cdouble *)tb->LinvP;
-    A prev = 0;
+  double Md[B::NM];
+  basis_moments<D, N>(mac.n, Te, Ue, re, Md);
+  if constexpr (DEV) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      constexpr int kMax = 8;
-      double mc[kMax], ak[kMax];
-      if (c > 0) asm volatile("" : "+s"(lp) : "v"(prev));
+    for (int k = 0; k < B::NM; ++k) Md[k] -= tb->Mref[k];
+  }
+  // moments of the shifted monomials (p^0 - m) p^e = p^0 p^e - m p^e
 #pragma unroll
-      for (int t = 0; t < CL.cnt[c]; ++t) {
-        const int k = CL.idx[c][t];
-        mc[t] = basis_moment<D, N>(k, mac.n, Te, Ue, re);
-        if constexpr (DEV) mc[t] -= tb->Mref[k];
-      }
-      // moments of the shifted monomials (p^0 - m) p^e = p^0 p^e - m p^e
+  for (int q = 0; q < AT.n; ++q)
+    if (AT.m1[q] >= 0) Md[AT.m1[q]] -= m * Md[AT.m0[q]];
+  // projection coefficients on the orthonormal polynomials J = Linv psi
+  // (Eq. mj-projection-coefficients), then a' = Linv^T a so that
+  // f^eq_i = w_i psi(p_i)^T a' = w_i sum_k a_k J_k(p_i)
+  double ak[B::NM];
 #pragma unroll
-      for (int t = 0; t < CL.cnt[c]; ++t) {
-        const int pk = CL.partner[CL.idx[c][t]];
-        if (pk >= 0) mc[t] -= m * mc[CL.pos[pk]];
-      }
+  for (int r = 0; r < B::NM; ++r) {
+    double acc = 0.0;
 #pragma unroll
-      for (int t = 0; t < CL.cnt[c]; ++t) {
-        double acc = 0.0;
+    for (int c = 0; c <= r; ++c)
+      if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * Md[c];
+    ak[r] = acc;
+  }
 #pragma unroll
-        for (int u = 0; u <= t; ++u) acc += lp[CL.off[c] + t * (t + 1) / 2 + u] * mc[u];
-        ak[t] = acc;
-      }
-      // reload the block for the transposed pass rather than keep it in (spilled) scalar registers
-      asm volatile("" : "+s"(lp) : "v"(ak[CL.cnt[c] - 1]));
+  for (int c = 0; c < B::NM; ++c) {
+    double acc = 0.0;
 #pragma unroll
-      for (int u = 0; u < CL.cnt[c]; ++u) {
-        double acc = 0.0;
-#pragma unroll
-        for (int t = u; t < CL.cnt[c]; ++t) acc += lp[CL.off[c] + t * (t + 1) / 2 + u] * ak[t];
-        ap[CL.idx[c][u]] = (A)acc;
-      }
-      prev = ap[CL.idx[c][0]];
-    }
-  } else {
-    double Md[B::NM];
-    basis_moments<D, N>(mac.n, Te, Ue, re, Md);
-    if constexpr (DEV) {
-#pragma unroll
-      for (int k = 0; k < B::NM; ++k) Md[k] -= tb->Mref[k];
-    }
-    // moments of the shifted monomials (p^0 - m) p^e = p^0 p^e - m p^e
-#pragma unroll
-    for (int q = 0; q < AT.n; ++q)
-      if (AT.m1[q] >= 0) Md[AT.m1[q]] -= m * Md[AT.m0[q]];
-    // projection coefficients on the orthonormal polynomials J = Linv psi
-    // (Eq. mj-projection-coefficients), then a' = Linv^T a so that
-    // f^eq_i = w_i psi(p_i)^T a' = w_i sum_k a_k J_k(p_i)
-    double ak[B::NM];
-#pragma unroll
-    for (int r = 0; r < B::NM; ++r) {
-      double acc = 0.0;
-#pragma unroll
-      for (int c = 0; c <= r; ++c)
-        if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * Md[c];
-      ak[r] = acc;
-    }
-#pragma unroll
-    for (int c = 0; c < B::NM; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int r = c; r < B::NM; ++r)
-        if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * ak[r];
-      ap[c] = (A)acc;
-    }
+    for (int r = c; r < B::NM; ++r)
+      if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * ak[r];
+    ap[c] = (A)acc;
   }
   // ---- step 8 ingredients: Omega_jk = a0 - v_j (n_k . U)/tau ----
   const double itau = wall ? 0.0 : 1.0 / tau;
@@ -431,50 +340,6 @@ __device__ __forceinline__ Macro<ST::D> collide_prod(const Tables *__restrict__ 
     }
     return acc;
   };
-  if constexpr (D == 3) {
-    // Direction-major: f^eq_jk = sum_l (s0_jl P0_kl + s1_jl P1_kl) with the
-    // shell-independent angular sums P_kl = sum_{|e| = l} a'_{m(e)} w_k n_k^e,
-    // so only the 8 sums of one direction pair are live next to a'.
-#pragma unroll
-    for (int qp = 0; qp < NPD; ++qp) {
-      const int k = 2 * qp;
-      A P0[4] = {0, 0, 0, 0}, P1[4] = {0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < AT.n; ++q) {
-        const double c = nhat_pow<ST>(k, AT.e[q][0], AT.e[q][1], AT.e[q][2]) * dir_weight<ST>(k);
-        if (c == 0.0) continue;
-        const int l = AT.e[q][0] + AT.e[q][1] + AT.e[q][2];
-        if (AT.m0[q] >= 0) P0[l] += (A)c * ap[AT.m0[q]];
-        if (AT.m1[q] >= 0) P1[l] += (A)c * ap[AT.m1[q]];
-      }
-#pragma unroll
-      for (int j = 0; j < KR; ++j) {
-        A E = 0, O = 0;
-#pragma unroll
-        for (int l = 0; l <= N; ++l) {
-          const A t = tab<A>(tb->sfeq[j][0][l], tb->sfeqf[j][0][l]) * P0[l] +
-                      tab<A>(tb->sfeq[j][1][l], tb->sfeqf[j][1][l]) * P1[l];
-          if (l & 1) O += t;
-          else E += t;
-        }
-        const A vj = tab<A>(tb->sv[j], tb->svf[j]);
-        const A b = vj * nU[qp];
-        const A om0 = a0 - b, om1 = a0 + b;
-        const int i = j * ND + k;
-        const A f0 = f[i], f1 = f[i + 1];
-        f[i] = f0 + om0 * ((E + O) - f0);
-        f[i + 1] = f1 + om1 * ((E - O) - f1);
-        if (force) {
-          const A gv = vj * gdotn(qp) * cU0;
-          const A fe0 = (E + O) + (DEV ? tab<A>(tb->fref[i], tb->freff[i]) : (A)0);
-          const A fe1 = (E - O) + (DEV ? tab<A>(tb->fref[i + 1], tb->freff[i + 1]) : (A)0);
-          f[i] += cF * (gv - gU) * fe0;
-          f[i + 1] += cF * (-gv - gU) * fe1;
-        }
-      }
-    }
-    return mac;
-  }
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
     A ce[20];
