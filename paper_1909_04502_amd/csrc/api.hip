@@ -246,9 +246,8 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   h->cfg = *cfg;
   h->stencil = stencil_of(m);
   // default launch shapes (from sweeps of every variant on MI355X):
-  //  * 3D product rules: every variant launches the same kernel in the same shape (split.hip);
-  //  * the 3D massive rule: 64 x 2 XCD-ordered tiles (double, streaming kernel) or 64 x 1 patches
-  //    (float);
+  //  * 3D rules: every variant launches the same kernel in the same shape (split.hip,
+  //    split_onlat.hip, split_ur3d.hip);
   //  * 2D product rules in double: rows of 64 sites; float storage with double arithmetic: 64 x 4
   //    band tiles of the occupancy-2 build (4 % faster than rows of 64); float storage and
   //    arithmetic: 64 x 4 band tiles of the occupancy-4 build (0.057 against 0.060 ms at 1024^2 for
@@ -260,7 +259,7 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   //    of the massless rules (at most 65,536 sites, such as 64 x 64), which take rows of 64 sites
   //    so that four times as many blocks spread over the CUs (about 9 % faster at 64 x 64)
   if (m.d == 3 && m.kind == RLBM_QUAD_MASSIVE_ONLATTICE) h->variant = cfg->storage == RLBM_F64 ? 4 : 8;
-  else if (m.d == 3 && m.kind == RLBM_QUAD_UR_ONLATTICE) h->variant = 4;   // streaming kernel, as the 3D massive rule
+  else if (m.d == 3 && m.kind == RLBM_QUAD_UR_ONLATTICE) h->variant = 4;
   else if (m.d == 3) h->variant = cfg->storage == RLBM_F64 ? 0 : 11;
   else if (m.kind == RLBM_QUAD_PRODUCT && cfg->storage == RLBM_F64) h->variant = 5;
   else if (m.kind == RLBM_QUAD_PRODUCT && cfg->storage == RLBM_F32_DEV) h->variant = 10;

@@ -20,7 +20,7 @@ struct FieldPtrs {
 // tiles per XCD, 2 = (y, z) patches per XCD in 3D, a band in 2D).  lds: the 2D
 // product rules stage their upstream windows in LDS (64 x 4 band tiles); lattices
 // the staged kernel does not cover take the register kernel of the same shape.
-// The 3D product rules have one kernel and launch shape under every variant.
+// The 3D rules have one kernel and launch shape under every variant.
 struct Variant {
   int bx, by, bz, occ, xcd, lds;
 };
@@ -51,7 +51,7 @@ struct LaunchArgs {
 
 hipError_t launch(const LaunchArgs &a);
 
-// one per stencil family (step_*.hip, split.hip)
+// one per stencil family (step_*.hip; split*.hip: the 3D rules)
 hipError_t launch_prod2d(const LaunchArgs &a);
 hipError_t launch_prod3d(const LaunchArgs &a);
 hipError_t launch_ur2d(const LaunchArgs &a);

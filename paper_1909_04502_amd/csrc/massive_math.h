@@ -45,94 +45,44 @@ __device__ __forceinline__ void massive_coefficients(const Tables *__restrict__ 
                                                      const Ratios &rr, A (&ap)[BasisDef<D, N>::NM]) {
   using B = BasisDef<D, N>;
   const double m = tb->m;
-  if constexpr (D == 3) {
-    constexpr ClassTable<D, N> CL{};
-    // the packed blocks are read class by class; laundering the table pointer on the previous
-    // block's result keeps the compiler from hoisting (and spilling) all their scalar loads
-    typedef const __attribute__((address_space(4))) double cdouble;
-    cdouble *lp = (cdouble *)tb->LinvP;
-    A prev = 0;
+  static_assert(D == 2, "the 3D rules: split_math.h");
+  constexpr AngTable<D, N> AT{};
+  double Md[B::NM];
+  basis_moments<D, N>(mac.n, mac.T, mac.U, rr, Md);
+  if constexpr (DEV) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      constexpr int kMax = 8;
-      double mc[kMax], ak[kMax];
-      if (c > 0) asm volatile("" : "+s"(lp) : "v"(prev));
+    for (int k = 0; k < B::NM; ++k) Md[k] -= tb->Mref[k];
+  }
 #pragma unroll
-      for (int t = 0; t < CL.cnt[c]; ++t) {
-        const int k = CL.idx[c][t];
-        mc[t] = basis_moment<D, N>(k, mac.n, mac.T, mac.U, rr);
-        if constexpr (DEV) mc[t] -= tb->Mref[k];
-      }
+  for (int q = 0; q < AT.n; ++q)
+    if (AT.m1[q] >= 0) Md[AT.m1[q]] -= m * Md[AT.m0[q]];
+  double ak[B::NM];
 #pragma unroll
-      for (int t = 0; t < CL.cnt[c]; ++t) {
-        const int pk = CL.partner[CL.idx[c][t]];
-        if (pk >= 0) mc[t] -= m * mc[CL.pos[pk]];
-      }
+  for (int r = 0; r < B::NM; ++r) {
+    double acc = 0.0;
 #pragma unroll
-      for (int t = 0; t < CL.cnt[c]; ++t) {
-        double acc = 0.0;
+    for (int c = 0; c <= r; ++c)
+      if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * Md[c];
+    ak[r] = acc;
+  }
 #pragma unroll
-        for (int u = 0; u <= t; ++u) acc += lp[CL.off[c] + t * (t + 1) / 2 + u] * mc[u];
-        ak[t] = acc;
-      }
-      asm volatile("" : "+s"(lp) : "v"(ak[CL.cnt[c] - 1]));
+  for (int c = 0; c < B::NM; ++c) {
+    double acc = 0.0;
 #pragma unroll
-      for (int u = 0; u < CL.cnt[c]; ++u) {
-        double acc = 0.0;
-#pragma unroll
-        for (int t = u; t < CL.cnt[c]; ++t) acc += lp[CL.off[c] + t * (t + 1) / 2 + u] * ak[t];
-        ap[CL.idx[c][u]] = (A)acc;
-      }
-      prev = ap[CL.idx[c][0]];
-    }
-  } else {
-    constexpr AngTable<D, N> AT{};
-    double Md[B::NM];
-    basis_moments<D, N>(mac.n, mac.T, mac.U, rr, Md);
-    if constexpr (DEV) {
-#pragma unroll
-      for (int k = 0; k < B::NM; ++k) Md[k] -= tb->Mref[k];
-    }
-#pragma unroll
-    for (int q = 0; q < AT.n; ++q)
-      if (AT.m1[q] >= 0) Md[AT.m1[q]] -= m * Md[AT.m0[q]];
-    double ak[B::NM];
-#pragma unroll
-    for (int r = 0; r < B::NM; ++r) {
-      double acc = 0.0;
-#pragma unroll
-      for (int c = 0; c <= r; ++c)
-        if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * Md[c];
-      ak[r] = acc;
-    }
-#pragma unroll
-    for (int c = 0; c < B::NM; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int r = c; r < B::NM; ++r)
-        if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * ak[r];
-      ap[c] = (A)acc;
-    }
+    for (int r = c; r < B::NM; ++r)
+      if (AT.cls[r] == AT.cls[c]) acc += tb->Linv[r][c] * ak[r];
+    ap[c] = (A)acc;
   }
 }
 
-// The update of one site with the populations reached through callbacks:
-// fetch(i) returns the pre-collision f_i for the moments, refetch(i) returns it
-// again for the relaxation, and put(i, v) takes the post-collision value.  The
-// register-resident collide passes its array; the streaming kernel loads from
-// memory twice and stores directly, so that no population stays live across
-// the eigen-solve and the projection.
+// The collision of one site: f (pre-collision) is replaced by the post-collision populations in place (RELAX =
+// false: only the macroscopic state is formed).
 // EXT: no-slip wall planes (site_wall), in a separate instantiation: a wall
 // site takes the equilibrium at rest of its own n and its own or the plane's
 // prescribed temperature (Omega = 1).
-// REVERSE relaxes the groups in the reverse of their loading order (the rest
-// population first); every population's update is independent of the others,
-// so only the instruction order changes (4 % faster for the register-resident
-// 3D rule in float deviations, slower for the streaming kernel).
-template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT, bool REVERSE, class Fetch, class Refetch,
-          class Put>
-__device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict__ tb, double tau, double wallT,
-                                                       Fetch &&fetch, Refetch &&refetch, Put &&put) {
+template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT = false>
+__device__ __forceinline__ Macro<ST::D> collide_massive(const Tables *__restrict__ tb, S (&f)[ST::Q], double tau,
+                                                        double wallT = -1.0) {
   constexpr int D = ST::D, Q = ST::Q, NG = ST::NG, NT = D * (D + 1) / 2;
   constexpr bool REST = (Q & 1) != 0;   // an odd count carries a rest population, the last one
   using B = BasisDef<D, N>;
@@ -153,7 +103,7 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
     for (int a = 0; a < NT; ++a) Sab[a] = 0;
 #pragma unroll
     for (int i = ST::gfirst(g); i < ST::gfirst(g) + ST::gcount(g); i += 2) {
-      const A fi = fetch(i), fj = fetch(i + 1);
+      const A fi = f[i], fj = f[i + 1];
       const A s = fi + fj;
       const A d = fi - fj;
       S0 += s;
@@ -193,7 +143,7 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
   }
   if constexpr (REST) {
     const double m = tb->m;
-    const A fr = fetch(Q - 1);
+    const A fr = f[Q - 1];
     N0 += (A)m * fr;
     T00 += (A)(m * m) * fr;
   }
@@ -232,14 +182,8 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
   mac.n = lorentz_dot<D>(mac.U, Nv);
   const double m = tb->m;
   Ratios rr;
-  if constexpr (D == 2) {
-    mac.ok = temperature_2d(mac.eps / mac.n, m, mac.T) && mac.ok;
-    rr = ratios_2d(m / mac.T);
-  } else {
-    double r;
-    mac.ok = temperature_3d(tb, mac.eps / mac.n, m, mac.T, r) && mac.ok;
-    rr = ratios_3d(m / mac.T, r);
-  }
+  mac.ok = temperature_2d(mac.eps / mac.n, m, mac.T) && mac.ok;
+  rr = ratios_2d(m / mac.T);
   mac.ok = mac.ok && mac.n > 0.0 && mac.eps > 0.0;
   if constexpr (!RELAX) return mac;
   // ---- step 5: a' over the shifted monomials ----
@@ -281,30 +225,8 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
   }
   // full equilibrium of population i from its deviation part (float-deviation storage)
   auto feq_full = [&](int i, A e) { return DEV ? e + tab<A>(tb->fref[i], tb->freff[i]) : e; };
-  auto relax_rest = [&]() {
-    if constexpr (REST) {
-      const A E = ap[0] * tab<A>(tb->wrest, tb->wrestf);   // the constant monomial is basis entry 0
-      const A fr = refetch(Q - 1);
-      A out = fr + a0 * (E - fr);
-      if (force) out -= cF * gU * feq_full(Q - 1, E);
-      put(Q - 1, out);
-    }
-  };
-  if constexpr (REST && REVERSE) relax_rest();
-  // each group's populations are fetched before any of it is relaxed: in the streaming kernel its
-  // re-loads are then in flight together instead of one pair per memory round trip (a store between
-  // two re-loads makes the wave wait for every access it has in flight)
-  constexpr int GMAX = [] {
-    int mx = 0;
-    for (int g = 0; g < NG; ++g) mx = ST::gcount(g) > mx ? ST::gcount(g) : mx;
-    return mx;
-  }();
 #pragma unroll
-  for (int gg = 0; gg < NG; ++gg) {
-    const int g = REVERSE ? NG - 1 - gg : gg;
-    A fg[GMAX];
-#pragma unroll
-    for (int j = 0; j < ST::gcount(g); ++j) fg[j] = refetch(ST::gfirst(g) + j);
+  for (int g = 0; g < NG; ++g) {
     A ce[20];
 #pragma unroll
     for (int q = 0; q < AT.n; ++q) {
@@ -315,8 +237,7 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
       ce[q] = acc;
     }
 #pragma unroll
-    for (int ii = 0; ii < ST::gcount(g); ii += 2) {
-      const int i = REVERSE ? ST::gfirst(g) + ST::gcount(g) - 2 - ii : ST::gfirst(g) + ii;
+    for (int i = ST::gfirst(g); i < ST::gfirst(g) + ST::gcount(g); i += 2) {
       A E = 0, O = 0;
 #pragma unroll
       for (int q = 0; q < AT.n; ++q) {
@@ -336,7 +257,7 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
         else if (c != 0) b += (A)c * ub[a];
       }
       const A om0 = a0 - b, om1 = a0 + b;
-      const A f0 = fg[i - ST::gfirst(g)], f1 = fg[i + 1 - ST::gfirst(g)];
+      const A f0 = f[i], f1 = f[i + 1];
       A out0 = f0 + om0 * ((E + O) - f0);
       A out1 = f1 + om1 * ((E - O) - f1);
       if (force) {
@@ -351,20 +272,18 @@ __device__ __forceinline__ Macro<ST::D> massive_update(const Tables *__restrict_
         out0 += cF * (gn - gU) * feq_full(i, E + O);
         out1 += cF * (-gn - gU) * feq_full(i + 1, E - O);
       }
-      put(i, out0);
-      put(i + 1, out1);
+      f[i] = out0;
+      f[i + 1] = out1;
     }
   }
-  if constexpr (REST && !REVERSE) relax_rest();
+  if constexpr (REST) {
+    const A E = ap[0] * tab<A>(tb->wrest, tb->wrestf);   // the constant monomial is basis entry 0
+    const A fr = f[Q - 1];
+    A out = fr + a0 * (E - fr);
+    if (force) out -= cF * gU * feq_full(Q - 1, E);
+    f[Q - 1] = out;
+  }
   return mac;
-}
-
-template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT = false>
-__device__ __forceinline__ Macro<ST::D> collide_massive(const Tables *__restrict__ tb, S (&f)[ST::Q], double tau,
-                                                        double wallT = -1.0) {
-  auto get = [&](int i) { return f[i]; };
-  return massive_update<ST, N, S, DEV, RELAX, EXT, ST::D == 3>(tb, tau, wallT, get, get,
-                                                                [&](int i, S v) { f[i] = v; });
 }
 
 }  // namespace rlbm

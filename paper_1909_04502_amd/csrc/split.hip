@@ -24,8 +24,8 @@
 //
 // Sites are dealt to blocks in runs of 64 consecutive sites of a slab of kSlab rows (all rows of the
 // slab joined end to end, so that rows of any length fill their waves), slab by slab and plane by plane
-// inside patches of kSlab rows by kSlab planes; XCD k takes patches k, k + 8, ..., so that the y and z
-// halo rows of the blocks in flight on an XCD stay in its L2.
+// inside patches of kSlab rows by kSlab planes, so that the y and z halo rows of the blocks in flight on an
+// XCD stay in its L2 (split_tiling: which patches an XCD takes).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -36,58 +36,6 @@
 #include "split_math.h"
 
 namespace rlbm {
-
-constexpr int kSlab = 8;   // rows of a run's slab, planes of a patch
-
-struct SplitTiling {
-  int npy;      // slabs along y
-  int runs;     // runs of 64 sites per slab plane
-  int rows;     // rows per slab
-  int planes;   // planes per patch
-};
-
-// The block's run, and the site of this lane (a lane past the run's live sites takes the last of them: its
-// loads stay inside the lattice, and it stores nothing).  False where the whole run lies past the lattice.
-template <bool XCH>
-__device__ __forceinline__ bool split_site(const Tables *__restrict__ tb, const SplitTiling &tl, int lane, SplitRun &run,
-                                           int &x, int &y) {
-  const uint32_t t = blockIdx.x, k = t % 8, l = t / 8, per = (uint32_t)(tl.runs * tl.planes);
-  const uint32_t p = (l / per) * 8 + k, w = l % per;
-  const int nx = tb->nx, ny = tb->ny;
-  run.z = (int)(p / tl.npy) * tl.planes + (int)(w / tl.runs);
-  const int y0 = (int)(p % tl.npy) * tl.rows, off0 = (int)(w % tl.runs) * 64;
-  if (run.z >= tb->nz) return false;
-  const int rows = ny - y0 < tl.rows ? ny - y0 : tl.rows;   // of this slab
-  if (off0 >= rows * nx) return false;
-  run.live = rows * nx - off0 < 64 ? rows * nx - off0 : 64;
-  const int q = off0 / nx;
-  run.x0 = off0 - q * nx;
-  run.y0 = y0 + q;
-  run.brk = nx - run.x0 < 64 ? nx - run.x0 : 64;
-  const int at = run.x0 + (lane < run.live ? lane : run.live - 1);
-  if constexpr (XCH) {   // one row boundary at most
-    x = at >= nx ? at - nx : at;
-    y = run.y0 + (at >= nx);
-  } else {
-    // at / nx of at < 128 by a float quotient, corrected
-    int r = (int)((float)at * __builtin_amdgcn_rcpf((float)nx));
-    r -= r * nx > at;
-    r += at - r * nx >= nx;
-    x = at - r * nx;
-    y = run.y0 + r;
-  }
-  return true;
-}
-
-__device__ __forceinline__ void split_fields(const FieldPtrs &fp, int64_t site, int64_t sites, const Macro<3> &mac) {
-  if (fp.n) fp.n[site] = mac.n;
-  if (fp.eps) fp.eps[site] = mac.eps;
-  if (fp.T) fp.T[site] = mac.T;
-  if (fp.U) {
-#pragma unroll
-    for (int a = 0; a <= 3; ++a) fp.U[a * sites + site] = mac.U[a];
-  }
-}
 
 // The update from the pre-collision populations f of this wave's shell w on: state, relaxation, store (RELAX =
 // false: the fields alone).
@@ -180,22 +128,8 @@ __global__ void __launch_bounds__(64 * ST::NSHELL) k_init_split(const Tables *__
   const bool live = lane < run.live;
   const int64_t sites = tb->sites;
   const uint32_t site = ((uint32_t)run.z * tb->ny + y) * tb->nx + x;
-  double U[4], uu = 0.0;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    U[a + 1] = u0[a * sites + site];
-    uu += U[a + 1] * U[a + 1];
-  }
-  const double g = 1.0 / sqrt(1.0 - uu);
-  U[0] = g;
-#pragma unroll
-  for (int a = 1; a <= 3; ++a) U[a] *= g;
-  const double n = n0[site], T = T0[site];
-  bool inr = true;
-  const double r = tb->m == 0.0 ? 0.0 : cheb_r(tb, tb->m / T, inr);
-  if (live && (!inr || !(uu < 1.0) || !(n > 0.0) || !(T > 0.0))) *err = 1;
   double M[B::NM];
-  basis_moments<3, N>(n, T, U, ratios_3d(tb->m / T, r), M);
+  if (!first_moments3<N>(tb, n0, T0, u0, site, M) && live) *err = 1;
   A f[ND];
 #pragma unroll
   for (int q = 0; q < ND / 2; ++q) {
@@ -218,12 +152,10 @@ __global__ void __launch_bounds__(64 * ST::NSHELL) k_init_split(const Tables *__
 
 template <class ST, int N, typename S, bool DEV, typename A>
 static hipError_t launch_split_t(const LaunchArgs &a) {
-  const int rows = a.ny < kSlab ? a.ny : kSlab, planes = a.nz < kSlab ? a.nz : kSlab;
-  const SplitTiling tl{(a.ny + rows - 1) / rows, (int)(((int64_t)rows * a.nx + 63) / 64), rows, planes};
-  const int64_t npatch = (int64_t)tl.npy * ((a.nz + planes - 1) / planes);
-  const int64_t nb = 8 * ((npatch + 7) / 8) * (int64_t)tl.runs * planes;
-  if (nb > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)nb), block(64 * ST::NSHELL);
+  unsigned nb;
+  const SplitTiling tl = split_tiling(a.nx, a.ny, a.nz, nb);
+  if (nb == 0) return hipErrorInvalidValue;
+  const dim3 grid(nb), block(64 * ST::NSHELL);
   using T = std::true_type;
   using F = std::false_type;
   auto step = [&](auto relax, auto ext, auto nt) {

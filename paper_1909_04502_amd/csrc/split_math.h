@@ -1,9 +1,11 @@
-// split_math.h -- the pieces of the update that split.hip's waves share (HIP device code): one shell's
-// pull, direction sums and relaxation of the 3D product rule, the macroscopic state from the sums, and
-// the equilibrium's coefficients by parity class.
+// split_math.h -- the pieces of the 3D update that the waves of a block share (HIP device code): the sites of
+// a block; one shell's pull, direction sums and relaxation of the product rule; the macroscopic state from
+// the sums; and the equilibrium's coefficients by parity class.
 #pragma once
 #include <type_traits>
+#include <utility>
 
+#include "kernels.h"
 #include "prod_math.h"
 
 namespace rlbm {
@@ -72,6 +74,38 @@ struct Moments3 {
     for (int a = 0; a < 6; ++a) Tab[a] = fmadd(pmm, S[4 + a], Tab[a]);
   }
 };
+
+// N^a and T^ab in double (the reference's added back for deviations).
+template <bool DEV, typename A>
+__device__ __forceinline__ void moments_to_state(const Tables *__restrict__ tb, const Moments3<A> &mom, double (&Nv)[4],
+                                                 double (&T)[4][4]) {
+  Nv[0] = mom.N0;
+  T[0][0] = mom.T00;
+  int ab = 0;
+#pragma unroll
+  for (int a = 1; a <= 3; ++a) {
+    Nv[a] = mom.Na[a - 1];
+    T[0][a] = T[a][0] = mom.T0a[a - 1];
+#pragma unroll
+    for (int b = a; b <= 3; ++b) {
+      T[a][b] = T[b][a] = mom.Tab[ab];
+      ++ab;
+    }
+  }
+  if constexpr (DEV) {
+    int s = 0;
+#pragma unroll
+    for (int a = 0; a <= 3; ++a) {
+      Nv[a] += tb->Nref[a];
+#pragma unroll
+      for (int b = a; b <= 3; ++b) {
+        T[a][b] += tb->Tref[s];
+        if (a != b) T[b][a] = T[a][b];
+        ++s;
+      }
+    }
+  }
+}
 
 // index of the angular monomial n^(ex, ey, ez) in AngTable order (-1: above the order)
 template <int N>
@@ -215,6 +249,74 @@ __device__ __forceinline__ int near_site(int v, int n, int open) {
   if (open) return v < 0 ? 0 : (v >= n ? n - 1 : v);
   v = v < 0 ? v + n : v;
   return v >= n ? v - n : v;
+}
+
+constexpr int kSlab = 8;   // rows of a run's slab, planes of a patch
+
+struct SplitTiling {
+  int chunk;    // runs per XCD (0: the XCDs take whole patches in turn)
+  int npy;      // slabs along y
+  int runs;     // runs of 64 sites per slab plane
+  int rows;     // rows per slab
+  int planes;   // planes per patch
+};
+
+// The tiling of a lattice, and its blocks (0: more than a grid holds).
+inline SplitTiling split_tiling(int nx, int ny, int nz, unsigned &blocks) {
+  const int rows = ny < kSlab ? ny : kSlab, planes = nz < kSlab ? nz : kSlab;
+  SplitTiling tl{0, (ny + rows - 1) / rows, (int)(((int64_t)rows * nx + 63) / 64), rows, planes};
+  const int64_t npatch = (int64_t)tl.npy * ((nz + planes - 1) / planes), per = (int64_t)tl.runs * planes;
+  // whole patches in turn while an XCD has several of them (97 x 130 x 83 in double 0.60 ms, 0.64 in eighths of
+  // the sequence); a lattice of few patches is cut into eighths, which spreads it over all XCDs (the tube of
+  // 6400 x 1 x 1 is one patch: 0.052 ms on one XCD, 0.014 on eight)
+  const int64_t nb = npatch >= 32 ? 8 * ((npatch + 7) / 8) * per : 8 * ((npatch * per + 7) / 8);
+  blocks = nb > 0x7fffffff ? 0u : (unsigned)nb;
+  tl.chunk = npatch >= 32 ? 0 : (int)(nb / 8);
+  return tl;
+}
+
+// The block's run, and the site of this lane (a lane past the run's live sites takes the last of them: its
+// loads stay inside the lattice, and it stores nothing).  False where the whole run lies past the lattice.
+template <bool XCH>
+__device__ __forceinline__ bool split_site(const Tables *__restrict__ tb, const SplitTiling &tl, int lane, SplitRun &run,
+                                           int &x, int &y) {
+  const uint32_t k = blockIdx.x % 8, l = blockIdx.x / 8, per = (uint32_t)(tl.runs * tl.planes);
+  const uint32_t t = k * (uint32_t)tl.chunk + l;
+  const uint32_t p = tl.chunk ? t / per : (l / per) * 8 + k, w = tl.chunk ? t % per : l % per;
+  const int nx = tb->nx, ny = tb->ny;
+  run.z = (int)(p / tl.npy) * tl.planes + (int)(w / tl.runs);
+  const int y0 = (int)(p % tl.npy) * tl.rows, off0 = (int)(w % tl.runs) * 64;
+  if (run.z >= tb->nz) return false;
+  const int rows = ny - y0 < tl.rows ? ny - y0 : tl.rows;   // of this slab
+  if (off0 >= rows * nx) return false;
+  run.live = rows * nx - off0 < 64 ? rows * nx - off0 : 64;
+  const int q = off0 / nx;
+  run.x0 = off0 - q * nx;
+  run.y0 = y0 + q;
+  run.brk = nx - run.x0 < 64 ? nx - run.x0 : 64;
+  const int at = run.x0 + (lane < run.live ? lane : run.live - 1);
+  if constexpr (XCH) {   // one row boundary at most
+    x = at >= nx ? at - nx : at;
+    y = run.y0 + (at >= nx);
+  } else {
+    // at / nx of at < 128 by a float quotient, corrected
+    int r = (int)((float)at * __builtin_amdgcn_rcpf((float)nx));
+    r -= r * nx > at;
+    r += at - r * nx >= nx;
+    x = at - r * nx;
+    y = run.y0 + r;
+  }
+  return true;
+}
+
+__device__ __forceinline__ void split_fields(const FieldPtrs &fp, int64_t site, int64_t sites, const Macro<3> &mac) {
+  if (fp.n) fp.n[site] = mac.n;
+  if (fp.eps) fp.eps[site] = mac.eps;
+  if (fp.T) fp.T[site] = mac.T;
+  if (fp.U) {
+#pragma unroll
+    for (int a = 0; a <= 3; ++a) fp.U[a * sites + site] = mac.U[a];
+  }
 }
 
 // The directions in groups of at most MAX of the shell's y and z taps.
@@ -404,34 +506,8 @@ __device__ __forceinline__ void split_moments(const Tables *__restrict__ tb, con
     for (int q = 0; q < 10; ++q) S[q] = sums[j][q * 64 + lane];
     mom.add(tb, j, S);
   }
-  Nv[0] = mom.N0;
-  T[0][0] = mom.T00;
-  int ab = 0;
-#pragma unroll
-  for (int a = 1; a <= 3; ++a) {
-    Nv[a] = mom.Na[a - 1];
-    T[0][a] = T[a][0] = mom.T0a[a - 1];
-#pragma unroll
-    for (int b = a; b <= 3; ++b) {
-      T[a][b] = T[b][a] = mom.Tab[ab];
-      ++ab;
-    }
-  }
-  if constexpr (DEV) {
-    int s = 0;
-#pragma unroll
-    for (int a = 0; a <= 3; ++a) {
-      Nv[a] += tb->Nref[a];
-#pragma unroll
-      for (int b = a; b <= 3; ++b) {
-        T[a][b] += tb->Tref[s];
-        if (a != b) T[b][a] = T[a][b];
-        ++s;
-      }
-    }
-  }
+  moments_to_state<DEV>(tb, mom, Nv, T);
 }
-
 // Steps 2-4, without the state in LDS.
 __device__ __forceinline__ Macro<3> split_state(const Tables *__restrict__ tb, const double (&Nv)[4], const double (&T)[4][4],
                                                 Ratios &rr) {
@@ -444,6 +520,28 @@ __device__ __forceinline__ Macro<3> split_state(const Tables *__restrict__ tb, c
   rr = ratios_3d(m / mac.T, r);
   mac.ok = mac.ok && mac.n > 0.0 && mac.eps > 0.0;
   return mac;
+}
+
+// The Maxwell-Juettner moments of the initial fields at a site; false where they are not physical.
+template <int N>
+__device__ __forceinline__ bool first_moments3(const Tables *__restrict__ tb, const double *__restrict__ n0,
+                                               const double *__restrict__ T0, const double *__restrict__ u0, uint32_t site,
+                                               double (&M)[BasisDef<3, N>::NM]) {
+  double U[4], uu = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    U[a + 1] = u0[a * tb->sites + site];
+    uu += U[a + 1] * U[a + 1];
+  }
+  const double g = 1.0 / sqrt(1.0 - uu);
+  U[0] = g;
+#pragma unroll
+  for (int a = 1; a <= 3; ++a) U[a] *= g;
+  const double n = n0[site], T = T0[site];
+  bool inr = true;
+  const double r = tb->m == 0.0 ? 0.0 : cheb_r(tb, tb->m / T, inr);
+  basis_moments<3, N>(n, T, U, ratios_3d(tb->m / T, r), M);
+  return inr && uu < 1.0 && n > 0.0 && T > 0.0;
 }
 
 // What the equilibrium is built from, to LDS.
@@ -533,8 +631,22 @@ __device__ __forceinline__ void split_class(const Tables *__restrict__ tb, int l
   }
 }
 
-// The parity classes over the waves: with four waves the even class (8 monomials at N = 3) and one axis
-// class each (5) with a plane class (2); with three the even class, the axis classes, the plane classes.
+// The wave that takes parity class c (0: even, 1, 2, 4: one odd axis, 3, 5, 6: two, 7: three; at N = 3 they
+// hold 8, 5, 2 and 1 monomials), of W = 3, 4 or 8 waves.
+RLBM_HD constexpr int class_owner(int W, int c) {
+  const int bits = (c & 1) + ((c >> 1) & 1) + (c >> 2);
+  if (W == 3) return bits == 0 ? 0 : (bits == 1 ? 1 : 2);
+  if (W == 4) return c == 0 ? 0 : (c == 1 || c == 3 ? 1 : (c == 2 || c == 5 ? 2 : 3));
+  return c;
+}
+
+template <int N, int W, bool DEV, typename A, class X, int... C>
+__device__ __forceinline__ void split_classes(const Tables *__restrict__ tb, int w, int lane, double n, double T,
+                                              const double (&U)[4], const Ratios &rr, X &sh,
+                                              std::integer_sequence<int, C...>) {
+  ((w == class_owner(W, C) ? split_class<N, DEV, A, C>(tb, lane, n, T, U, rr, sh) : (void)0), ...);
+}
+
 template <int N, int W, bool DEV, typename A, class X>
 __device__ __forceinline__ void split_coefficients(const Tables *__restrict__ tb, int w, int lane, X &sh) {
   const double n = sh.mac[0][lane], T = sh.mac[1][lane];
@@ -545,27 +657,90 @@ __device__ __forceinline__ void split_coefficients(const Tables *__restrict__ tb
   rr.r0 = sh.mac[6][lane];
   rr.r2 = sh.mac[7][lane];
   rr.r3 = sh.mac[8][lane];
-  if (w == 0) {
-    split_class<N, DEV, A, 0>(tb, lane, n, T, U, rr, sh);
-  } else if (W == 3 && w == 1) {
-    split_class<N, DEV, A, 1>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 2>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 4>(tb, lane, n, T, U, rr, sh);
-  } else if (W == 3) {
-    split_class<N, DEV, A, 3>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 5>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 6>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 7>(tb, lane, n, T, U, rr, sh);
-  } else if (w == 1) {
-    split_class<N, DEV, A, 1>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 3>(tb, lane, n, T, U, rr, sh);
-  } else if (w == 2) {
-    split_class<N, DEV, A, 2>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 5>(tb, lane, n, T, U, rr, sh);
-  } else {
-    split_class<N, DEV, A, 4>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 6>(tb, lane, n, T, U, rr, sh);
-    split_class<N, DEV, A, 7>(tb, lane, n, T, U, rr, sh);
+  split_classes<N, W, DEV, A>(tb, w, lane, n, T, U, rr, sh, std::make_integer_sequence<int, 8>{});
+}
+
+// ---- on-lattice rules: the waves exchange their part of the moments ----
+
+// What the waves exchange, per lane; the state takes the place of the moments once they are read.
+template <int N, int W, typename A>
+struct OnlatLds {
+  union {
+    A mom[W][14][64];                // N^0, T^00, N^a, T^0a, T^ab of each wave's groups
+    struct {
+      double mac[9][64];             // n, T, U^0..U^3, r0, r2, r3 of the site
+      A om[9][64];                   // U^0 / tau, v0 U^a / tau; EXT: m/T, (v0 g^a) U^0, g . U
+      A ap[BasisDef<3, N>::NM][64];  // a' of the equilibrium
+    };
+  };
+};
+
+template <typename A>
+__device__ __forceinline__ void put_moments(const Moments3<A> &mom, int lane, A (&to)[14][64]) {
+  to[0][lane] = mom.N0;
+  to[1][lane] = mom.T00;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    to[2 + a][lane] = mom.Na[a];
+    to[5 + a][lane] = mom.T0a[a];
+  }
+#pragma unroll
+  for (int a = 0; a < 6; ++a) to[8 + a][lane] = mom.Tab[a];
+}
+
+// The state of the lane's site from all waves' moments; fields and flag; and, for the relaxation, what the
+// equilibrium and Omega (and the force) are built from, to LDS over the moments.  A wall site: as split_put.
+template <int N, int W, typename S, bool DEV, bool RELAX, bool EXT>
+__device__ __forceinline__ void onlat_state(const Tables *__restrict__ tb, OnlatLds<N, W, S> &sh, int lane, bool live, int x,
+                                            int y, int z, uint32_t site, const void *__restrict__ tau_field,
+                                            const FieldPtrs &fields, int *err) {
+  const int64_t sites = tb->sites;
+  double tau = RELAX ? (tau_field == nullptr ? tb->tau : (double)((const S *)tau_field)[site]) : 1.0;
+  Moments3<S> mom;
+#pragma unroll
+  for (int p = 0; p < W; ++p) {
+    mom.N0 += sh.mom[p][0][lane];
+    mom.T00 += sh.mom[p][1][lane];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      mom.Na[a] += sh.mom[p][2 + a][lane];
+      mom.T0a[a] += sh.mom[p][5 + a][lane];
+    }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) mom.Tab[a] += sh.mom[p][8 + a][lane];
+  }
+  double Nv[4], T[4][4];
+  moments_to_state<DEV>(tb, mom, Nv, T);
+  Ratios rr;
+  const Macro<3> mac = split_state(tb, Nv, T, rr);
+  if (!mac.ok && live) *err = 1;
+  if (fields.any && live) split_fields(fields, site, sites, mac);
+  if constexpr (RELAX) {
+    const double wallT = EXT ? site_wall(tb, x, y, z) : -1.0;
+    const bool wall = EXT && wallT >= 0.0;
+    double Ue[4], Te = mac.T;
+    Ratios re = rr;
+#pragma unroll
+    for (int a = 0; a <= 3; ++a) Ue[a] = wall ? (a == 0 ? 1.0 : 0.0) : mac.U[a];
+    if (wall) equilibrium_state<3>(tb, mac, rr, wallT, Te, re);
+    if (tb->tau_T != 0.0) tau += tb->tau_T / mac.T;   // step 7: the temperature-dependent part of tau
+    const double itau = wall ? 0.0 : 1.0 / tau;
+    asm volatile("" ::: "memory");   // the moments are in registers; their place is reused from here on
+    put_state(sh, lane, mac.n, Te, Ue, re);
+    sh.om[0][lane] = wall ? (S)1 : (S)(mac.U[0] * itau);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) sh.om[1 + a][lane] = (S)(tb->v0 * mac.U[a + 1] * itau);
+    if constexpr (EXT) {   // zero where no force acts
+      const bool force = tb->has_force && !wall;
+      double gU = 0.0;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        gU += tb->g[a] * mac.U[a + 1];
+        sh.om[5 + a][lane] = (S)(tb->v0 * tb->g[a] * mac.U[0]);
+      }
+      sh.om[4][lane] = force ? (S)(tb->m / mac.T) : (S)0;
+      sh.om[8][lane] = (S)gU;
+    }
   }
 }
 

@@ -93,43 +93,26 @@ __device__ __forceinline__ Offs make_offs(const Tables *__restrict__ tb, int x, 
 // Integer streaming: population I at the site comes from x - n_I.  The byte
 // offsets of the upstream rows are computed once per axis and distance (up to
 // ST::RMAX sites), so each population costs one add and one load.
-template <class ST>
-RLBM_HD constexpr int dir_z(int i) {
-  if constexpr (ST::D == 3) return ST::dir(i, 2);
-  else return 0;
-}
-
 template <class ST, typename S, int R, int... I>
 __device__ __forceinline__ void gather_onlat_impl(const S *__restrict__ fin, int64_t sites, const uint32_t (&ox)[2 * R + 1],
-                                                  const uint32_t (&oy)[2 * R + 1], const uint32_t (&oz)[2 * R + 1],
-                                                  S (&f)[ST::Q], std::integer_sequence<int, I...>) {
-  ((f[I] = *(const S *)((const char *)(fin + (int64_t)I * sites) + ox[R - ST::dir(I, 0)] + oy[R - ST::dir(I, 1)] +
-                        oz[R - dir_z<ST>(I)])),
-   ...);
-}
-
-// byte offsets of the rows x + k - R, y + k - R, z + k - R (k = 0 .. 2R)
-template <class ST, typename S>
-__device__ __forceinline__ void onlat_offsets(const Tables *__restrict__ tb, int x, int y, int z,
-                                              uint32_t (&ox)[2 * ST::RMAX + 1], uint32_t (&oy)[2 * ST::RMAX + 1],
-                                              uint32_t (&oz)[2 * ST::RMAX + 1]) {
-  constexpr int R = ST::RMAX;
-  const uint32_t nx = tb->nx, nxy = (uint32_t)tb->nx * tb->ny;
-#pragma unroll
-  for (int k = 0; k <= 2 * R; ++k) {
-    ox[k] = (uint32_t)wrap_or_clamp(x + k - R, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
-    oy[k] = (uint32_t)wrap_or_clamp(y + k - R, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
-    oz[k] = ST::D == 3 ? (uint32_t)wrap_or_clamp(z + k - R, tb->nz, tb->open[2]) * nxy * (uint32_t)sizeof(S) : 0u;
-  }
+                                                  const uint32_t (&oy)[2 * R + 1], S (&f)[ST::Q],
+                                                  std::integer_sequence<int, I...>) {
+  ((f[I] = *(const S *)((const char *)(fin + (int64_t)I * sites) + ox[R - ST::dir(I, 0)] + oy[R - ST::dir(I, 1)])), ...);
 }
 
 template <class ST, typename S>
 __device__ __forceinline__ void gather_onlat(const Tables *__restrict__ tb, const S *__restrict__ fin, int64_t sites,
-                                             int x, int y, int z, S (&f)[ST::Q]) {
+                                             int x, int y, S (&f)[ST::Q]) {
   constexpr int R = ST::RMAX;
-  uint32_t ox[2 * R + 1], oy[2 * R + 1], oz[2 * R + 1];
-  onlat_offsets<ST, S>(tb, x, y, z, ox, oy, oz);
-  gather_onlat_impl<ST, S, R>(fin, sites, ox, oy, oz, f, std::make_integer_sequence<int, ST::Q>{});
+  // byte offsets of the columns x + k - R and the rows y + k - R (k = 0 .. 2R)
+  uint32_t ox[2 * R + 1], oy[2 * R + 1];
+  const uint32_t nx = tb->nx;
+#pragma unroll
+  for (int k = 0; k <= 2 * R; ++k) {
+    ox[k] = (uint32_t)wrap_or_clamp(x + k - R, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
+    oy[k] = (uint32_t)wrap_or_clamp(y + k - R, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
+  }
+  gather_onlat_impl<ST, S, R>(fin, sites, ox, oy, f, std::make_integer_sequence<int, ST::Q>{});
 }
 
 // pre-collision populations at the site, in the arithmetic type A (the storage type S, or double
@@ -139,7 +122,7 @@ __device__ __forceinline__ void gather(const Tables *__restrict__ tb, const S *_
                                        int y, int z, A (&f)[ST::Q]) {
   if constexpr (ST::ONLAT) {
     static_assert(sizeof(A) == sizeof(S), "on-lattice rules compute in their storage type");
-    gather_onlat<ST, S>(tb, fin, sites, x, y, z, f);
+    gather_onlat<ST, S>(tb, fin, sites, x, y, f);
   } else {
     const Offs o = make_offs<ST, S>(tb, x, y, z);
     pull_prod<ST, S, false, A>(tb, fin, sites, o, f);
@@ -233,11 +216,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 
   const double tau = site_tau<S>(tb, tau_field, site);
   const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, z) : -1.0);
   if (!mac.ok) flag_error(err);
-  // a fresh copy of the plane size for the store addresses: otherwise the compiler keeps the
-  // load phase's plane offsets alive (in spilled scalar registers) for reuse here
-  int64_t sites_st = sites;
-  if constexpr (ST::D == 3) asm volatile("" : "+s"(sites_st));
-  store_site<ST, S, NT, A>(fout, sites_st, (uint32_t)site * (uint32_t)sizeof(S), f);
+  store_site<ST, S, NT, A>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (last.any) write_fields<ST::D>(last, site, sites, mac);
 }
 
@@ -484,123 +463,6 @@ __global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tb,
   if (last.any) write_fields<ST::D>(last, site, sites, mac);
 }
 
-// Massive rules whose populations do not fit in registers (the 143-vector 3D
-// stencil in double storage): every population is loaded once for the
-// moments; the first kStreamKeep of them stay in registers, the others are
-// loaded again (from the caches or memory) for the relaxation; every result is
-// stored at once.  Keeping about a third of them balances the re-read traffic
-// against the registers the eigen-solve and the projection need.
-template <class ST, int N, typename S, bool DEV, int OCC, bool NT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 1, 8)))
-k_step_stream(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__restrict__ fout,
-              const void *__restrict__ tau_field, FieldPtrs last, int *err, Tiling tl) {
-  int x, y, z;
-  if (!site_coords(tb, tl, x, y, z)) return;
-  const int64_t sites = tb->sites;
-  const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
-  constexpr int R = ST::RMAX;
-  uint32_t ox[2 * R + 1], oy[2 * R + 1], oz[2 * R + 1];
-  onlat_offsets<ST, S>(tb, x, y, z, ox, oy, oz);
-  // a second, opaque copy of the input pointer: the relaxation's loads are not merged with the
-  // moment loads (which would keep every population live)
-  const S *fin2 = fin;
-  asm volatile("" : "+s"(fin2));
-  const uint32_t site_off = (uint32_t)site * (uint32_t)sizeof(S);
-  auto load = [&](const S *base, int i) {
-    return *(const S *)((const char *)(base + (int64_t)i * sites) + ox[R - ST::dir(i, 0)] + oy[R - ST::dir(i, 1)] +
-                        oz[R - dir_z<ST>(i)]);
-  };
-  const double tau = site_tau<S>(tb, tau_field, site);
-  constexpr int kStreamKeep = 48;
-  S keep[kStreamKeep];
-  const Macro<ST::D> mac = massive_update<ST, N, S, DEV, true, false, false>(
-      tb, tau, -1.0,
-      [&](int i) {
-        const S v = load(fin, i);
-        if (i < kStreamKeep) keep[i < kStreamKeep ? i : 0] = v;
-        return v;
-      },
-      [&](int i) { return i < kStreamKeep ? keep[i < kStreamKeep ? i : 0] : load(fin2, i); },
-      [&](int i, S v) { put_pop<NT>(fout, sites, site_off, i, v); });
-  if (!mac.ok) flag_error(err);
-  if (last.any) write_fields<ST::D>(last, site, sites, mac);
-}
-
-// The moments and the initial state for stencils too large to hold in registers (the 288-vector
-// (3+1)-d massless rule): the same arithmetic as k_moments and k_init, with every population loaded
-// (or, at the initial state, evaluated from its projection row) when the update asks for it.
-template <class ST, int N, typename S, bool DEV>
-__global__ void __launch_bounds__(256) k_moments_stream(const Tables *__restrict__ tb, const S *__restrict__ fin,
-                                                        FieldPtrs out, int *err, Tiling tl) {
-  int x, y, z;
-  if (!site_coords(tb, tl, x, y, z)) return;
-  const int64_t sites = tb->sites;
-  const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
-  constexpr int R = ST::RMAX;
-  uint32_t ox[2 * R + 1], oy[2 * R + 1], oz[2 * R + 1];
-  onlat_offsets<ST, S>(tb, x, y, z, ox, oy, oz);
-  auto load = [&](int i) {
-    return *(const S *)((const char *)(fin + (int64_t)i * sites) + ox[R - ST::dir(i, 0)] + oy[R - ST::dir(i, 1)] +
-                        oz[R - dir_z<ST>(i)]);
-  };
-  const Macro<ST::D> mac = massive_update<ST, N, S, DEV, false, false, false>(
-      tb, 1.0, -1.0, load, load, [&](int, S) {});
-  if (!mac.ok) flag_error(err);
-  write_fields<ST::D>(out, site, sites, mac);
-}
-
-template <class ST, int N, typename S, bool DEV>
-__global__ void __launch_bounds__(256) k_init_stream(const Tables *__restrict__ tb, const double *__restrict__ n0,
-                                                     const double *__restrict__ T0, const double *__restrict__ u0,
-                                                     const double *__restrict__ noise, double amp,
-                                                     S *__restrict__ fout, const void *__restrict__ tau_field,
-                                                     FieldPtrs fields0, int *err, Tiling tl) {
-  constexpr int D = ST::D, Q = ST::Q;
-  static_assert(D == 3, "streaming init: the (3+1)-d rule");
-  using B = BasisDef<D, N>;
-  int x, y, z;
-  if (!site_coords(tb, tl, x, y, z)) return;
-  const int64_t sites = tb->sites;
-  const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
-  double U[D + 1], uu = 0.0;
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    U[a + 1] = u0[a * sites + site];
-    uu += U[a + 1] * U[a + 1];
-  }
-  const double g = 1.0 / sqrt(1.0 - uu);
-  U[0] = g;
-#pragma unroll
-  for (int a = 1; a <= D; ++a) U[a] *= g;
-  const double n = n0[site], T = T0[site];
-  bool inr = true;
-  const double r = tb->m == 0.0 ? 0.0 : cheb_r(tb, tb->m / T, inr);
-  if (!inr || !(uu < 1.0) || !(n > 0.0) || !(T > 0.0)) flag_error(err);
-  const Ratios rr = ratios_3d(tb->m / T, r);
-  double M[B::NM];
-  basis_moments<D, N>(n, T, U, rr, M);
-  if constexpr (ST::SHIFT) shift_basis_moments<D, N>(tb->m, M);
-  // f_i(x, 0) = f^eq_i (1 + amp xi_i) from the projection rows, in storage form
-  auto feq = [&](int i) {
-    const int pr = i >> 1;
-    double E = 0.0, O = 0.0;
-#pragma unroll
-    for (int k = 0; k < B::NE; ++k) E += tb->Re[pr][k] * M[k];
-#pragma unroll
-    for (int k = 0; k < B::NO; ++k) O += tb->Ro[pr][k] * M[B::NE + k];
-    double v = (i & 1) ? E - O : E + O;
-    if (noise != nullptr) v *= 1.0 + amp * noise[(int64_t)i * sites + site];
-    return DEV ? (S)(v - tb->fref[i]) : (S)v;
-  };
-  static_assert((Q & 1) == 0, "streaming init: stencils without a rest population");
-  const double tau = site_tau<S>(tb, tau_field, site);
-  const uint32_t site_off = (uint32_t)site * (uint32_t)sizeof(S);
-  const Macro<D> mac = massive_update<ST, N, S, DEV, true, false, false>(
-      tb, tau, -1.0, feq, feq, [&](int i, S v) { put_pop<false>(fout, sites, site_off, i, v); });
-  if (!mac.ok) flag_error(err);
-  if (fields0.any) write_fields<D>(fields0, site, sites, mac);
-}
-
 template <class ST, int N, typename S, bool DEV, typename A = S>
 __global__ void __launch_bounds__(256) k_moments(const Tables *__restrict__ tb, const S *__restrict__ fin,
                                                  FieldPtrs out, int *err, Tiling tl) {
@@ -639,15 +501,7 @@ __global__ void __launch_bounds__(256) k_init(const Tables *__restrict__ tb, con
 #pragma unroll
   for (int a = 1; a <= D; ++a) U[a] *= g;
   const double n = n0[site], T = T0[site];
-  Ratios rr;
-  if constexpr (D == 2) {
-    rr = ratios_2d(tb->m / T);
-  } else {
-    bool inr = true;
-    const double r = tb->m == 0.0 ? 0.0 : cheb_r(tb, tb->m / T, inr);
-    if (!inr) flag_error(err);
-    rr = ratios_3d(tb->m / T, r);
-  }
+  const Ratios rr = ratios_2d(tb->m / T);
   if (!(uu < 1.0) || !(n > 0.0) || !(T > 0.0)) flag_error(err);
   double M[B::NM];
   basis_moments<D, N>(n, T, U, rr, M);
@@ -703,33 +557,23 @@ static hipError_t launch_t(const LaunchArgs &a) {
   }
   dim3 grid((unsigned)nb, 1, 1);
   const Tiling tl{vr.bx, by, bz, (int)nb, order};
-  // the 143 doubles of the 3D massive rule overflow the registers (scratch spills): stream them;
-  // 143 floats fit, and there the single load is faster
-  constexpr bool kStream = (ST::ONLAT && ST::SHIFT && ST::D == 3 && sizeof(S) == 8) || ST::Q > 144;
-  // the 288 populations of the (3+1)-d massless rule do not fit in registers in either storage: its
-  // moments and initial state take the streaming forms too
-  constexpr bool kStreamAll = ST::Q > 144;
+  static_assert(ST::D == 2, "the 3D rules: split.hip, split_onlat.hip, split_ur3d.hip");
   switch (a.op) {
     case OP_STEP: {
       // one instantiation per (occupancy target 0, 2 or 4, force/walls, store kind)
       auto go = [&](auto occ, auto ext, auto nt) {
         constexpr int O = decltype(occ)::value;
         constexpr bool E = decltype(ext)::value, T = decltype(nt)::value;
-        if constexpr (kStream) {
-          hipLaunchKernelGGL((k_step_stream<ST, N, S, DEV, O, T>), grid, block, 0, a.stream, a.tb,
-                             (const S *)a.fin, (S *)a.fout, a.tau_field, a.fields, a.err, tl);
-        } else {
-          hipLaunchKernelGGL((k_step<ST, N, S, DEV, O, E, T, A>), grid, block, 0, a.stream, a.tb, (const S *)a.fin,
-                             (S *)a.fout, a.tau_field, a.fields, a.err, tl);
-        }
+        hipLaunchKernelGGL((k_step<ST, N, S, DEV, O, E, T, A>), grid, block, 0, a.stream, a.tb, (const S *)a.fin,
+                           (S *)a.fout, a.tau_field, a.fields, a.err, tl);
       };
       using O0 = std::integral_constant<int, 0>;
       using O2 = std::integral_constant<int, 2>;
       using O4 = std::integral_constant<int, 4>;
       using F = std::false_type;
       using T = std::true_type;
-      const bool ext = a.ext && !kStream;
-      if constexpr (ST::D == 2 && !ST::ONLAT) {
+      const bool ext = a.ext;
+      if constexpr (!ST::ONLAT) {
         if (vr.lds && a.lds_ok && !ext) {
           const long ntile = ((a.nx + 63) / 64) * (long)((a.ny + 3) / 4);
           const Tiling ltl{64, 4, 1, (int)ntile, 1};
@@ -743,12 +587,7 @@ static hipError_t launch_t(const LaunchArgs &a) {
           break;
         }
       }
-      if constexpr (kStreamAll) {
-        // one build (no occupancy target) for the 288-vector rule: every other build multiplies its
-        // compile time and none is faster for a kernel that streams its populations
-        if (a.nt) go(O0{}, F{}, T{});
-        else go(O0{}, F{}, F{});
-      } else if (ext) {
+      if (ext) {
         if (a.nt) go(O0{}, T{}, T{});
         else go(O0{}, T{}, F{});
       } else if (vr.occ == 2) {
@@ -764,20 +603,12 @@ static hipError_t launch_t(const LaunchArgs &a) {
       break;
     }
     case OP_MOMENTS:
-      if constexpr (kStreamAll)
-        hipLaunchKernelGGL((k_moments_stream<ST, N, S, DEV>), grid, block, 0, a.stream, a.tb, (const S *)a.fin,
-                           a.fields, a.err, tl);
-      else
-        hipLaunchKernelGGL((k_moments<ST, N, S, DEV, A>), grid, block, 0, a.stream, a.tb, (const S *)a.fin, a.fields,
-                           a.err, tl);
+      hipLaunchKernelGGL((k_moments<ST, N, S, DEV, A>), grid, block, 0, a.stream, a.tb, (const S *)a.fin, a.fields,
+                         a.err, tl);
       break;
     case OP_INIT:
-      if constexpr (kStreamAll)
-        hipLaunchKernelGGL((k_init_stream<ST, N, S, DEV>), grid, block, 0, a.stream, a.tb, a.n0, a.T0, a.u0,
-                           a.noise, a.amp, (S *)a.fout, a.tau_field, a.fields, a.err, tl);
-      else
-        hipLaunchKernelGGL((k_init<ST, N, S, DEV, A>), grid, block, 0, a.stream, a.tb, a.n0, a.T0, a.u0, a.noise,
-                           a.amp, (S *)a.fout, a.tau_field, a.fields, a.err, tl);
+      hipLaunchKernelGGL((k_init<ST, N, S, DEV, A>), grid, block, 0, a.stream, a.tb, a.n0, a.T0, a.u0, a.noise,
+                         a.amp, (S *)a.fout, a.tau_field, a.fields, a.err, tl);
       break;
     default:
       return hipErrorInvalidValue;

@@ -1,5 +1,4 @@
-"""The 3D product-rule kernels (a site's populations spread over the waves of a block) against the FP64
-oracle, to the bounds that the other step kernels keep: double 1e-12 on the populations and fields; float
+"""The 3D kernels (a site's populations spread over the waves of a block) against the FP64 oracle, to the bounds that the other step kernels keep: double 1e-12 on the populations and fields; float
 storage (16 + 4 k) 2^-24 on the fields after k steps, and (32 + sqrt k) 2^-24 where the update is in double.
 
 The extents cover runs of 64 sites that end inside a row, hold a row boundary, end a slab of eight rows
@@ -21,13 +20,14 @@ EXTENTS = [(64, 8, 8), (65, 9, 3), (97, 13, 9), (127, 1, 2), (128, 3, 1), (200, 
            (9, 3, 10), (2, 2, 2), (1, 1, 1), (1, 70, 1)]
 
 
-def check(extent, storage, order=3, bc=None, zeta=1.0, tau=0.8, force=None):
+def check(extent, storage, order=3, bc=None, zeta=1.0, tau=0.8, force=None, quad=None, **kw):
     from paper_1909_04502_amd import rlbm as R
+    quad = qd.product_3d(zeta, order) if quad is None else quad
     n, T, u = (torch.tensor(a) for a in W.taylor_green_3d(*extent, 0.1, density_sigma=1e-2, seed=5))
     field = isinstance(tau, torch.Tensor)
-    gl = R.Lattice(d=3, zeta=zeta, order=order, kind="product", extent=extent, storage=storage,
-                   tau=0.8 if field else tau, tau_field=tau if field else None, bc=bc, force=force)
-    ol = OL.Lattice(qd.product_3d(zeta, order), tau, extent, bc=bc, force=force)
+    gl = R.Lattice(d=3, zeta=zeta, order=order, extent=extent, storage=storage, tau=0.8 if field else tau,
+                   tau_field=tau if field else None, bc=bc, force=force, **kw)
+    ol = OL.Lattice(quad, tau, extent, bc=bc, force=force, tau_T=kw.get("tau_T", 0.0))
     f0, first = gl.init(n, T, u, want_fields=True)
     res, last = gl.step(f0, gl.new_state(), STEPS, want_last=True)
     now = gl.moments(res)
@@ -73,3 +73,22 @@ def test_split_step_force_and_walls(extent, storage):
     print(f"[case] split walls {extent} {storage}", flush=True)
     check(extent, storage, bc=("wall", "periodic", "open"), force=(1e-3, -2e-3, 3e-3))
     check(extent, storage, order=2, bc=("periodic", "wall", "wall"), force=(0.0, 0.0, 1e-3))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("extent", [(64, 8, 8), (65, 9, 3), (131, 3, 3), (20, 11, 5), (3, 3, 3)])
+def test_split_massive_rule(extent, storage):
+    print(f"[case] split massive {extent} {storage}", flush=True)
+    v0 = 0.2719557997821228
+    check(extent, storage, zeta=5.0, quad=qd.massive_onlattice(3, 5.0, 3, v0), kind="massive_onlattice", v0=v0)
+    if storage == "f32dev":
+        check(extent, storage, zeta=5.0, quad=qd.massive_onlattice(3, 5.0, 3, v0), kind="massive_onlattice", v0=v0,
+              bc=("wall", "periodic", "open"), force=(0.0, 1e-3, 0.0))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("extent,bc", [((640, 1, 1), ("periodic", "open", "open")), ((65, 7, 6), None),
+                                       ((13, 9, 8), ("open", "periodic", "open")), ((6, 6, 6), None)])
+def test_split_massless_rule(extent, bc, storage):
+    print(f"[case] split massless {extent} {storage}", flush=True)
+    check(extent, storage, zeta=0.0, quad=qd.ur_onlattice_3d(3), kind="ur_onlattice", bc=bc, tau=0.6, tau_T=0.3)
