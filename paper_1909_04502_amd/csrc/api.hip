@@ -19,6 +19,7 @@ struct rlbm_lattice {
   int *d_err = nullptr;
   int stencil = 0;
   int variant = 1;
+  int staged_variant = -1;   // the variant that stands for the staged step kernel besides its own
   int store_mode = RLBM_STORES_AUTO;
   int64_t sites = 0;
   std::string last_error;
@@ -102,6 +103,7 @@ int lattice_ext(const rlbm_lattice *h) {
 // on with aligned rows, 3-14 % slower with ragged ones.
 constexpr int64_t kNontemporalFootprint = 384ll << 20;
 constexpr int64_t kNontemporalRowAlign = 64;
+constexpr int64_t kStagedFootprint = 256ll << 20;   // the Infinity Cache
 
 int uses_nontemporal(const rlbm_lattice *h) {
   if (h->store_mode != RLBM_STORES_AUTO) return h->store_mode == RLBM_STORES_NONTEMPORAL;
@@ -122,11 +124,9 @@ rlbm::LaunchArgs base_args(const rlbm_lattice *h, hipStream_t stream) {
   a.err = h->d_err;
   a.stream = stream;
   a.variant = h->variant;
+  a.staged = h->variant == h->staged_variant;
   a.ext = lattice_ext(h);
   a.nt = uses_nontemporal(h);
-  // the staged windows are read in 16-byte chunks that wrap around x as a whole
-  a.lds_ok = h->cfg.model.d == 2 && h->cfg.model.kind == RLBM_QUAD_PRODUCT && h->cfg.bc[0] == RLBM_PERIODIC &&
-             h->cfg.extent[0] % 4 == 0;
   return a;
 }
 
@@ -252,7 +252,7 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   //    band tiles of the occupancy-2 build (4 % faster than rows of 64); float storage and
   //    arithmetic: 64 x 4 band tiles of the occupancy-4 build (0.057 against 0.060 ms at 1024^2 for
   //    the unconstrained one); in every storage the LDS-staged kernel on lattices larger than the
-  //    caches (below);
+  //    Infinity Cache (below);
   //  * 2D on-lattice rules: 64 x 4 tiles of the occupancy-2 build, except the massive rules whose
   //    update fits in 128 registers (order 2, and order 3 in float deviations), which take the
   //    occupancy-4 build: four waves per SIMD instead of three, 7-27 % faster; and small lattices
@@ -277,15 +277,19 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
     for (int a = 0; a < m.d; ++a)
       if (cfg->bc[a] == RLBM_PERIODIC && std::fabs(h->quad.disp[i * m.d + a]) > (double)cfg->extent[a])
         return fail(RLBM_ERR_INVALID_ARG, "a periodic extent is shorter than the stencil's longest displacement");
-  // 2D product rules whose state outgrows the caches (the non-temporal store threshold) take the
-  // LDS-staged kernel where it applies, in every storage (double at 1024^2: 0.106 against 0.122 ms
-  // per step for rows of 64 sites; at 2048^2 float storage 0.221 against 0.256 ms, float storage
-  // with double arithmetic 0.255 against 0.266 ms); below that, where the halo re-reads hit the
-  // Infinity Cache, the register kernels stay ahead (float storage at 1024^2: 0.057 against 0.059)
-  const int64_t elem = cfg->storage == RLBM_F64 ? 8 : 4;
-  if (m.d == 2 && m.kind == RLBM_QUAD_PRODUCT && cfg->bc[0] == RLBM_PERIODIC && cfg->extent[0] % 4 == 0 &&
-      2 * elem * (int64_t)h->quad.Q * sites > kNontemporalFootprint)
-    h->variant = 12;
+  // 2D product rules whose two states outgrow the Infinity Cache take the LDS-staged kernel, at any x extent and
+  // boundary and in every storage (per step, register kernel -> staged; double 705 x 777 71 -> 61 us, 1023 x 1025
+  // 130 -> 119, walls and force 700 x 801 76 -> 69, order 2 901 x 803 66 -> 52; float storage 1100 x 1100 83 -> 76,
+  // 1501 x 1999 195 -> 171; with double arithmetic 1201 x 1101 99 -> 97, 1501 x 1999 202 -> 200).  Below that, where
+  // the halo re-reads hit that cache, the register kernels stay ahead (double 512 x 512 29 against 31 us, 700 x 700
+  // 47 against 53; float storage at 1024 x 1024 57 against 60).  Past the non-temporal store threshold the staged
+  // kernel's own variant number is the default where the x axis is periodic and its extent a multiple of 4; elsewhere
+  // the register kernel's number stands for it.
+  const int64_t both = 2 * (cfg->storage == RLBM_F64 ? 8 : 4) * (int64_t)h->quad.Q * sites;
+  if (m.d == 2 && m.kind == RLBM_QUAD_PRODUCT && both > kStagedFootprint) {
+    if (cfg->bc[0] == RLBM_PERIODIC && cfg->extent[0] % 4 == 0 && both > kNontemporalFootprint) h->variant = 12;
+    h->staged_variant = h->variant;
+  }
   int bc[3] = {cfg->bc[0], cfg->bc[1], cfg->bc[2]};
   rc = rlbm::build_tables(h->quad, cfg->tau, cfg->storage != RLBM_F64 ? cfg->n_ref : 1.0, cfg->storage,
                           cfg->extent, bc, *t, err);
@@ -615,10 +619,6 @@ rlbm_status rlbm_batch_create(const rlbm_config *cfgs, int32_t nlat, rlbm_batch 
   b->order = cfgs[0].model.order;
   b->storage = cfgs[0].storage;
   b->elem = b->storage == RLBM_F64 ? 8 : 4;
-  // default launch: runs of 256 consecutive sites (no lane idles past a row's end: 5-6 % faster
-  // than 64 x 4 tiles on 256 lattices of sides 64..512), the 2048-block grid in double and the
-  // 512-block grid in float
-  b->variant = b->storage == RLBM_F64 ? 2 * 4 + rlbm::kBatchLinearTile : rlbm::kBatchLinearTile;
   for (int l = 0; l < nlat; ++l) {
     rlbm_lattice *h = nullptr;
     rlbm_status st = rlbm_create(&cfgs[l], &h);
@@ -632,6 +632,13 @@ rlbm_status rlbm_batch_create(const rlbm_config *cfgs, int32_t nlat, rlbm_batch 
     b->total_elems += (int64_t)h->quad.Q * h->sites;
     b->total_sites += h->sites;
   }
+  // default launch: staged 64 x 4 tiles where the two states outgrow the Infinity Cache (96 lattices of sides
+  // 64..512, per step, runs of 256 sites -> staged: double 1440 -> 1184 us, float 799 -> 662, float with double
+  // arithmetic 878 -> 808; 404 MiB in double 119 -> 109, 296 MiB in float 117 -> 101).  Below that, runs of 256
+  // consecutive sites, no lane of which idles past a row's end (56 MiB in double 22 against 24 us), on the
+  // 2048-block grid in double and the 512-block grid in float
+  if (2 * b->total_elems * b->elem > kStagedFootprint) b->variant = 0;
+  else b->variant = b->storage == RLBM_F64 ? 2 * 4 + rlbm::kBatchLinearTile : rlbm::kBatchLinearTile;
   hipError_t he = hipMalloc(&b->d_tabs, sizeof(rlbm::Tables) * nlat);
   for (int l = 0; he == hipSuccess && l < nlat; ++l)
     he = hipMemcpy(b->d_tabs + l, b->lats[l]->d_tables, sizeof(rlbm::Tables), hipMemcpyDeviceToDevice);

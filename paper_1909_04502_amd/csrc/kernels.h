@@ -18,8 +18,7 @@ struct FieldPtrs {
 // fold bz into by), occupancy target (minimum waves per SIMD the compiler must
 // allow, 0 = its choice) and tile order (0 = as dealt, 1 = a contiguous band of
 // tiles per XCD, 2 = (y, z) patches per XCD in 3D, a band in 2D).  lds: the 2D
-// product rules stage their upstream windows in LDS (64 x 4 band tiles); lattices
-// the staged kernel does not cover take the register kernel of the same shape.
+// product rules stage their upstream windows in LDS (64 x 4 band tiles).
 // The 3D rules have one kernel and launch shape under every variant.
 struct Variant {
   int bx, by, bz, occ, xcd, lds;
@@ -44,8 +43,8 @@ struct LaunchArgs {
   double amp = 0.0;
   int *err = nullptr;               // device error flag
   int ext = 0;                      // the lattice has an external force or no-slip walls
+  int staged = 0;                   // 2D product rules: the LDS-staged step kernel, whatever the variant
   int nt = 0;                       // step kernels store the populations non-temporally
-  int lds_ok = 0;                   // the LDS-staged 2D product kernel covers this lattice
   hipStream_t stream = 0;
 };
 
@@ -82,8 +81,9 @@ struct AdjointArgs {
 // reverse-mode kernels (2D product rules, periodic boundaries)
 hipError_t launch_adjoint(const AdjointArgs &a);
 
-// Batched step: tile shapes (0: 64 x 4, 1: 64 x 2, 2: 128 x 2 sites; 3: 256 consecutive sites of
-// a lattice, its rows joined end to end, so that no lane idles past a row's end) and grid sizes
+// Batched step: tile shapes (0: 64 x 4, staged in LDS, one block per tile whatever the grid size;
+// 1: 64 x 2, 2: 128 x 2 sites; 3: 256 consecutive sites of a lattice, its rows joined end to end, so
+// that no lane idles past a row's end) and grid sizes
 constexpr int kBatchTiles[4][2] = {{64, 4}, {64, 2}, {128, 2}, {256, 1}};
 constexpr int kBatchLinearTile = 3;
 struct BatchArgs {
