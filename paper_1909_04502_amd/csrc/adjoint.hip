@@ -81,11 +81,14 @@ __global__ void __launch_bounds__(256) k_adjoint(const Tables *__restrict__ tb, 
   if (dtau != nullptr) dtau[site] += taub;
 }
 
-// The same reverse step for float storage and arithmetic, in three passes over the shells that each
-// pull what they need again (cache hits: the taps were read just before), so that one shell's
-// populations are live at a time instead of all Q twice over: the moments of F_t; the reverse of the
-// relaxation and of the equilibrium (F_t and S^T lam_{t+1}); and lam_t = mu (1 - Omega) + the terms
-// through n, T and U, stored shell by shell.  That fits two waves per SIMD.
+// The same reverse step for float storage and arithmetic, in passes over the shells: the taps of F_t and of
+// S^T lam_{t+1}, each pulled once and kept in LDS (its own places: no barrier), with the moments of F_t; the
+// reverse of the relaxation and of the equilibrium; and lam_t = mu (1 - Omega) + the terms through n, T and U,
+// stored shell by shell.  That fits two waves per SIMD.  All taps of F_t are asked for before the first is
+// summed, and those of a shell of lam before the sums of a shell of F_t: left to itself the scheduler waits
+// for every load in turn (62 us at 512 x 512).  Order 3 at 512 x 512: 40 us, of which the vector arithmetic
+// of four waves per SIMD takes 19; 51 us when each pass pulled its shells again (3590 instead of 2815 vector
+// instructions a wave, 455 instead of 221 lines read).  Blocks of one or two rows: 44 and 49 us.
 template <class ST, int N, typename S, bool DEV>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
 k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, const S *__restrict__ lam_next,
@@ -98,14 +101,39 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
   const int64_t sites = tb->sites;
   const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
   const Offs o = offs_periodic<ST, S>(tb, x, y, z);
+  // this thread's F_t and S^T lam_{t+1}, kept in LDS
+  __shared__ A fl[ST::Q][kAdjBX * kAdjBY], ml[ST::Q][kAdjBX * kAdjBY];
+  const int tid = threadIdx.y * kAdjBX + threadIdx.x;
   // ---- forward recomputation: moments, Landau frame, n, T, equilibrium coefficients ----
   MomAcc<D> acc;
+  StageTaps<ST, S> tf[KR], tm[KR];
+  const S *fb = Bprev, *lb = lam_next;
+#pragma unroll
+  for (int j = 0; j < KR; ++j) load_taps<ST, S, false>(fb, sites, o, tf[j]);
+  // tau and dtau are asked for with the taps: where there is none, a place in the state instead, unused (a load
+  // under a condition would be waited for at once)
+  const S tau1 = (tau_field != nullptr ? (const S *)tau_field : Bprev)[site];
+  const double dtau0 = (dtau != nullptr ? (const double *)dtau : (const double *)Bprev)[site];
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
+    load_taps<ST, S, true>(lb, sites, o, tm[j]);
+    __builtin_amdgcn_sched_barrier(0);
     A fs[ND];
-    pull_shell<ST, S, false, A>(tb, Bprev, sites, o, j, fs);
+    stage_interpolate<ST, S, A>(tb, j, tf[j], fs);
     moments_shell<ST, A, ND>(tb, j, fs, 0, acc);
+#pragma unroll
+    for (int k = 0; k < ND; ++k) fl[j * ND + k][tid] = fs[k];
+    __builtin_amdgcn_sched_barrier(0);
   }
+#pragma unroll
+  for (int j = 0; j < KR; ++j) {
+    A ms[ND];
+    stage_interpolate<ST, S, A>(tb, j, tm[j], ms);
+#pragma unroll
+    for (int k = 0; k < ND; ++k) ml[j * ND + k][tid] = ms[k];
+  }
+  asm volatile("" ::: "memory");   // they are read back, not kept in registers
   double Nv[D + 1], T[D + 1][D + 1];
   moments_finish<ST, DEV>(tb, acc, Nv, T);
   Macro<D> mac;
@@ -126,7 +154,7 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
     basis_moments<D, N>(mac.n, mac.T, mac.U, rr, Md);
     feq_coefficients<D, N, DEV>(tb, Md, ap);
   }
-  const double itau = 1.0 / tau_at<S>(tb, tau_field, site);
+  const double itau = 1.0 / (tau_field != nullptr ? (double)tau1 : tb->tau);
   const double a0 = mac.U[0] * itau;
   double nU[NPD];
 #pragma unroll
@@ -140,10 +168,6 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
     nU[q] = c0 * itau;
   }
   // ---- reverse of the relaxation and of the equilibrium evaluation ----
-  // (the base pointers pass through an empty asm on a forward result: the pulls are issued again
-  // here rather than their values kept live from the pass above)
-  const S *fb = Bprev, *lb = lam_next;
-  asm volatile("" : "+s"(fb), "+s"(lb) : "v"(ap[0]));
   double a0b = 0.0, nUb[NPD], apb[B::NM];
 #pragma unroll
   for (int q = 0; q < NPD; ++q) nUb[q] = 0.0;
@@ -152,8 +176,11 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
     A fs[ND], ms[ND];
-    pull_shell<ST, S, false, A>(tb, fb, sites, o, j, fs);
-    pull_shell<ST, S, true, A>(tb, lb, sites, o, j, ms);
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+      fs[k] = fl[j * ND + k][tid];
+      ms[k] = ml[j * ND + k][tid];
+    }
     relax_vjp_shell<ST, N, A>(tb, j, fs, ms, ap, a0, nU, a0b, nUb, apb);
   }
   // Omega depends on tau through a0 = U^0 / tau and nU = (n . U) / tau
@@ -184,13 +211,14 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
 #pragma unroll
     for (int b = 0; b <= D; ++b) Ts[a][b] = 0.5 * (Tbar[a][b] + Tbar[b][a]);
   // ---- lam_t = mu (1 - Omega) + dL/dN^a p^a + dL/dT^ab p^a p^b, shell by shell ----
-  const S *lb2 = lam_next;
-  asm volatile("" : "+s"(lb2) : "v"(Nb[0]));
+  asm volatile("" ::: "memory");
   const uint32_t so = (uint32_t)site * (uint32_t)sizeof(S);
+  __attribute__((address_space(1))) S *lo = (__attribute__((address_space(1))) S *)lam;
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
     A ms[ND], out[ND];
-    pull_shell<ST, S, true, A>(tb, lb2, sites, o, j, ms);
+#pragma unroll
+    for (int k = 0; k < ND; ++k) ms[k] = ml[j * ND + k][tid];
     const double v = tb->sv[j];
 #pragma unroll
     for (int qp = 0; qp < NPD; ++qp) {
@@ -200,9 +228,13 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
     }
     moments_vjp_shell<ST, A, ND>(tb, j, Nb, Ts, out, 0);
 #pragma unroll
-    for (int k = 0; k < ND; ++k) *(S *)((char *)(lam + (int64_t)(j * ND + k) * sites) + so) = (S)out[k];
+    for (int k = 0; k < ND; ++k) {
+      *(__attribute__((address_space(1))) S *)((__attribute__((address_space(1))) char *)(lo + k * sites) + so) = (S)out[k];
+    }
+    lo += ND * sites;
+    asm volatile("" : "+s"(lo));
   }
-  if (dtau != nullptr) dtau[site] += taub;
+  if (dtau != nullptr) dtau[site] = dtau0 + taub;
 }
 
 // lam_{T+1}(x) = J_macro(F(x))^T g(x), F = S(B); g = (dL/dn, dL/deps, dL/dT, dL/dU)
@@ -315,8 +347,8 @@ static hipError_t launch_adj_t(const AdjointArgs &a) {
   switch (a.op) {
     case ADJ_STEP:
       // float storage and arithmetic: the streamed kernel (two waves per SIMD); double storage or
-      // arithmetic: the register-resident one (re-pulled doubles miss the L1 and the streamed form
-      // is slower there)
+      // arithmetic: the register-resident one (at order 3 a block's F_t and lam in double would take
+      // 128 KB of LDS, one block per CU, which is what the registers allow too)
       if constexpr (sizeof(S) == 4 && sizeof(A) == 4)
         hipLaunchKernelGGL((k_adjoint_streamed<ST, N, S, DEV>), grid, block, 0, a.stream, a.tb, (const S *)a.state,
                            (const S *)a.lam_in, (S *)a.lam_out, a.tau_field, a.dtau, a.err);

@@ -18,6 +18,7 @@
 // exact eigenpair.
 #pragma once
 #include "prod_math.h"
+#include "stage2d.h"
 
 namespace rlbm {
 
@@ -567,64 +568,43 @@ __device__ __forceinline__ bool collide_vjp(const Tables *__restrict__ tb, S (&f
 // ---------------------------------------------------------------------------
 // The reverse step streamed shell by shell (2D product rules, float storage).
 // collide_vjp keeps the populations, the adjoint and the equilibrium of all Q
-// directions in registers at once; the streamed kernel pulls what each pass
-// over the shells needs again (from the cache: the same taps were read moments
-// before), so that one shell's populations are live at a time.
+// directions in registers at once; the streamed kernel keeps them in LDS, so
+// that one shell's populations are live at a time.
 // ---------------------------------------------------------------------------
 
-// Pre-collision values of shell j's populations: the interpolated pull of pull_prod (2D) for the
-// directions of that shell; TRANSPOSE mirrors the taps as there.
-template <class ST, typename S, bool TRANSPOSE, typename A>
-__device__ __forceinline__ void pull_shell(const Tables *__restrict__ tb, const S *fin, int64_t sites, const Offs &o,
-                                           int j, A (&fs)[ST::NDIR]) {
-  static_assert(ST::D == 2, "the streamed reverse step is built for the 2D product rules");
-  constexpr int ND = ST::NDIR;
+// The taps of shell j's populations at a site, from global memory; TRANSPOSE mirrors them as pull_prod does.
+// stage_interpolate sums them.  plane: the shell's first plane; moved on to the next shell's (through
+// an empty asm: all shells' plane addresses at once would not fit the scalar registers).
+template <class ST, typename S, bool TRANSPOSE>
+__device__ __forceinline__ void load_taps(const S *&fin, int64_t sites, const Offs &o, StageTaps<ST, S> &t) {
   typedef const __attribute__((address_space(1))) char gchar;
-  gchar *base = (gchar *)fin;
-  const A v = tab<A>(tb->sv[j], tb->svf[j]);
-  A pw[3][3];
+  int m = 0;
 #pragma unroll
-  for (int z = 1; z <= 2; ++z) {
-    const A mag = v * (A)kInvNorm[z];
-    const A cm = (A)1 - mag;
-#pragma unroll
-    for (int nf = 0; nf <= z; ++nf) {
-      A r = 1;
-#pragma unroll
-      for (int t = 0; t < nf; ++t) r *= mag;
-#pragma unroll
-      for (int t = nf; t < z; ++t) r *= cm;
-      pw[z][nf] = r;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < ND; ++k) {
-    gchar *plane = base + (int64_t)(j * ND + k) * sites * (int64_t)sizeof(S);
+  for (int k = 0; k < ST::NDIR; ++k) {
+    gchar *plane = (gchar *)fin + k * sites * (int64_t)sizeof(S);
     const int dx = ST::dir(k, 0), dy = ST::dir(k, 1);
     const int z = (dx != 0) + (dy != 0);
-    A acc = 0;
 #pragma unroll
     for (int tap = 0; tap < (1 << z); ++tap) {
-      int bit = 0, ox = 0, oy = 0, nfar = 0;
+      int bit = 0, ox = 0, oy = 0;
       if (dx != 0) {
         const int c = (tap >> bit++) & 1;
         ox = dx > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
-        nfar += ox != 0;
       }
       if (dy != 0) {
         const int c = (tap >> bit++) & 1;
         oy = dy > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
-        nfar += oy != 0;
       }
       if (TRANSPOSE) {
         ox = -ox;
         oy = -oy;
       }
       const uint32_t off = o.x[ox + 1] + o.y[oy + 1];
-      acc += pw[z][nfar] * (A) * (const __attribute__((address_space(1))) S *)(plane + off);
+      t.v[m++] = *(const __attribute__((address_space(1))) S *)(plane + off);
     }
-    fs[k] = acc;
   }
+  fin += ST::NDIR * sites;
+  asm volatile("" : "+s"(fin));
 }
 
 // Shell j's part of the reverse of the relaxation and of the equilibrium evaluation.  With

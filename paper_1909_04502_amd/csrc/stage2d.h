@@ -192,7 +192,7 @@ __device__ __forceinline__ void stage_read(const __attribute__((address_space(3)
 
 template <class ST, typename S, typename A>
 __device__ __forceinline__ void stage_interpolate(const Tables *__restrict__ tb, int j, const StageTaps<ST, S> &t,
-                                                A (&f)[ST::Q]) {
+                                                  A (&fs)[ST::NDIR]) {
   const A v = tab<A>(tb->sv[j], tb->svf[j]);
   A pw[3][3];
 #pragma unroll
@@ -222,7 +222,7 @@ __device__ __forceinline__ void stage_interpolate(const Tables *__restrict__ tb,
       if (dy != 0) nfar += dy > 0 ? !((tap >> bit++) & 1) : ((tap >> bit++) & 1);
       acc += pw[z][nfar] * (A)t.v[m++];
     }
-    f[j * ST::NDIR + k] = acc;
+    fs[k] = acc;
   }
 }
 
@@ -263,11 +263,15 @@ __device__ __forceinline__ void stage_pull(const Tables *__restrict__ tb, const 
       asm volatile("" ::: "memory");
       plan.load(fin, sites, j + 2, lds + (j & 1) * L::E * (int)sizeof(S));
     }
-    stage_interpolate<ST, S, A>(tb, j, taps, f);
+    A fs[ST::NDIR];
+    stage_interpolate<ST, S, A>(tb, j, taps, fs);
     // the shell's sums are formed here, before the next barrier, so that its taps do not stay live
     // in registers across the later shells (the compiler would otherwise sink every sum to the end)
 #pragma unroll
-    for (int k = 0; k < ST::NDIR; ++k) asm volatile("" : "+v"(f[j * ST::NDIR + k]));
+    for (int k = 0; k < ST::NDIR; ++k) {
+      asm volatile("" : "+v"(fs[k]));
+      f[j * ST::NDIR + k] = fs[k];
+    }
   }
 }
 
