@@ -20,7 +20,7 @@ namespace rlbm {
 // vector loads from the dispatch packet that each wave waits for).
 constexpr int kAdjBX = 64, kAdjBY = 4;
 
-__device__ __forceinline__ bool site_xyz(const Tables *__restrict__ tb, int &x, int &y, int &z) {
+__device__ __forceinline__ bool site_xyz(CTables *tb, int &x, int &y, int &z) {
   const uint32_t gx = (tb->nx + kAdjBX - 1) / kAdjBX, gy = (tb->ny + kAdjBY - 1) / kAdjBY;
   uint32_t t = blockIdx.x;
   {
@@ -39,7 +39,7 @@ __device__ __forceinline__ int wrap_p(int v, int n) {
 }
 
 template <class ST, typename S>
-__device__ __forceinline__ Offs offs_periodic(const Tables *__restrict__ tb, int x, int y, int z) {
+__device__ __forceinline__ Offs offs_periodic(CTables *tb, int x, int y, int z) {
   Offs o;
   const uint32_t nx = tb->nx, nxy = (uint32_t)tb->nx * tb->ny;
 #pragma unroll
@@ -52,7 +52,7 @@ __device__ __forceinline__ Offs offs_periodic(const Tables *__restrict__ tb, int
 }
 
 template <typename S>
-__device__ __forceinline__ double tau_at(const Tables *__restrict__ tb, const void *tau_field, int64_t site) {
+__device__ __forceinline__ double tau_at(CTables *tb, const void *tau_field, int64_t site) {
   return tau_field == nullptr ? tb->tau : (double)((const S *)tau_field)[site];
 }
 
@@ -61,10 +61,11 @@ __device__ __forceinline__ void set_err(int *err) { *err = 1; }
 
 // lam_t(x) = J_C(F_t(x))^T (S^T lam_{t+1})(x), F_t = S(B_{t-1}); dtau(x) += dL/dtau(x)
 template <class ST, int N, typename S, bool DEV, typename A = S>
-__global__ void __launch_bounds__(256) k_adjoint(const Tables *__restrict__ tb, const S *__restrict__ Bprev,
+__global__ void __launch_bounds__(256) k_adjoint(const Tables *__restrict__ tabs, const S *__restrict__ Bprev,
                                                  const S *__restrict__ lam_next, S *__restrict__ lam,
                                                  const void *__restrict__ tau_field, double *__restrict__ dtau,
                                                  int *err) {
+  CTables *tb = (CTables *)tabs;
   int x, y, z;
   if (!site_xyz(tb, x, y, z)) return;
   const int64_t sites = tb->sites;
@@ -91,8 +92,9 @@ __global__ void __launch_bounds__(256) k_adjoint(const Tables *__restrict__ tb, 
 // instructions a wave, 455 instead of 221 lines read).  Blocks of one or two rows: 44 and 49 us.
 template <class ST, int N, typename S, bool DEV>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
-k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, const S *__restrict__ lam_next,
+k_adjoint_streamed(const Tables *__restrict__ tabs, const S *__restrict__ Bprev, const S *__restrict__ lam_next,
                    S *__restrict__ lam, const void *__restrict__ tau_field, double *__restrict__ dtau, int *err) {
+  CTables *tb = (CTables *)tabs;
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2, KR = ST::NSHELL;
   using B = BasisDef<D, N>;
   using A = S;
@@ -232,15 +234,16 @@ k_adjoint_streamed(const Tables *__restrict__ tb, const S *__restrict__ Bprev, c
       *(__attribute__((address_space(1))) S *)((__attribute__((address_space(1))) char *)(lo + k * sites) + so) = (S)out[k];
     }
     lo += ND * sites;
-    asm volatile("" : "+s"(lo));
+    one_after_another(lo);
   }
   if (dtau != nullptr) dtau[site] = dtau0 + taub;
 }
 
 // lam_{T+1}(x) = J_macro(F(x))^T g(x), F = S(B); g = (dL/dn, dL/deps, dL/dT, dL/dU)
 template <class ST, int N, typename S, bool DEV, typename A = S>
-__global__ void __launch_bounds__(256) k_moments_vjp(const Tables *__restrict__ tb, const S *__restrict__ B,
+__global__ void __launch_bounds__(256) k_moments_vjp(const Tables *__restrict__ tabs, const S *__restrict__ B,
                                                      FieldPtrs g, S *__restrict__ lam, int *err) {
+  CTables *tb = (CTables *)tabs;
   constexpr int D = ST::D;
   int x, y, z;
   if (!site_xyz(tb, x, y, z)) return;
@@ -272,12 +275,13 @@ __global__ void __launch_bounds__(256) k_moments_vjp(const Tables *__restrict__ 
 // Reverse of the initial condition B_0 = C(f_0), f_0 = f^eq(n0, T0, U(u0)) (1 + amp xi):
 // du0 (and dn0, dT0 when requested) from lam_1 = dL/dF_1; dtau(x) += dL/dtau(x).
 template <class ST, int N, typename S, bool DEV, typename A = S>
-__global__ void __launch_bounds__(256) k_init_vjp(const Tables *__restrict__ tb, const double *__restrict__ n0,
+__global__ void __launch_bounds__(256) k_init_vjp(const Tables *__restrict__ tabs, const double *__restrict__ n0,
                                                   const double *__restrict__ T0, const double *__restrict__ u0,
                                                   const double *__restrict__ noise, double amp,
                                                   const S *__restrict__ lam1, const void *__restrict__ tau_field,
                                                   double *__restrict__ du0, double *__restrict__ dn0,
                                                   double *__restrict__ dT0, double *__restrict__ dtau, int *err) {
+  CTables *tb = (CTables *)tabs;
   constexpr int D = ST::D, Q = ST::Q;
   using B = BasisDef<D, N>;
   int x, y, z;

@@ -149,7 +149,7 @@ __device__ __forceinline__ double eos_slope_2d(double T, double m, const RatiosD
 // Reverse of feq_coefficients (the deviation shift by M^ref has no derivative): given
 // apb = dL/da', sets Mb = dL/dM (unshifted basis moments).
 template <int D, int N>
-__device__ __forceinline__ void coefficients_vjp(const Tables *__restrict__ tb, const double (&apb)[BasisDef<D, N>::NM],
+__device__ __forceinline__ void coefficients_vjp(CTables *tb, const double (&apb)[BasisDef<D, N>::NM],
                                                  double (&Mb)[BasisDef<D, N>::NM]) {
   using B = BasisDef<D, N>;
   constexpr AngTable<D, N> AT{};
@@ -181,7 +181,7 @@ __device__ __forceinline__ void coefficients_vjp(const Tables *__restrict__ tb, 
 // Transposed product-rule equilibrium evaluation: given g_i = dL/df^eq_i,
 // accumulate dL/dM (unshifted basis moments).
 template <class ST, int N, typename A>
-__device__ __forceinline__ void feq_vjp(const Tables *__restrict__ tb, const A (&g)[ST::Q],
+__device__ __forceinline__ void feq_vjp(CTables *tb, const A (&g)[ST::Q],
                                         double (&Mb)[BasisDef<ST::D, N>::NM]) {
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2, KR = ST::NSHELL;
   using B = BasisDef<D, N>;
@@ -220,7 +220,7 @@ __device__ __forceinline__ void feq_vjp(const Tables *__restrict__ tb, const A (
 // Coefficients a' = Linv^T Linv M' of the projected equilibrium over the shifted monomials
 // (Sec. 5.2), from the basis moments Md (deviation form for DEV: Md becomes M - M^ref).
 template <int D, int N, bool DEV>
-__device__ __forceinline__ void feq_coefficients(const Tables *__restrict__ tb, double (&Md)[BasisDef<D, N>::NM],
+__device__ __forceinline__ void feq_coefficients(CTables *tb, double (&Md)[BasisDef<D, N>::NM],
                                                  double (&ap)[BasisDef<D, N>::NM]) {
   using B = BasisDef<D, N>;
   constexpr AngTable<D, N> AT{};
@@ -254,7 +254,7 @@ __device__ __forceinline__ void feq_coefficients(const Tables *__restrict__ tb, 
 // Angular coefficients of shell j: ce[q] multiplies the direction monomial n^e(q) in the
 // equilibrium of that shell's populations.
 template <int D, int N>
-__device__ __forceinline__ void shell_coefficients(const Tables *__restrict__ tb, int j,
+__device__ __forceinline__ void shell_coefficients(CTables *tb, int j,
                                                    const double (&ap)[BasisDef<D, N>::NM], double (&ce)[20]) {
   constexpr AngTable<D, N> AT{};
 #pragma unroll
@@ -270,7 +270,7 @@ __device__ __forceinline__ void shell_coefficients(const Tables *__restrict__ tb
 // Forward equilibrium of the product rule from basis moments (deviation form
 // for DEV): used by the initial condition.
 template <class ST, int N, typename A, bool DEV>
-__device__ __forceinline__ void feq_prod(const Tables *__restrict__ tb, double (&Md)[BasisDef<ST::D, N>::NM],
+__device__ __forceinline__ void feq_prod(CTables *tb, double (&Md)[BasisDef<ST::D, N>::NM],
                                          A (&feq)[ST::Q]) {
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2, KR = ST::NSHELL;
   using B = BasisDef<D, N>;
@@ -307,7 +307,7 @@ struct MomAcc {
 
 // Adds shell j's populations f[base .. base + NDIR) to the moment sums.
 template <class ST, typename S, int M>
-__device__ __forceinline__ void moments_shell(const Tables *__restrict__ tb, int j, const S (&f)[M], int base,
+__device__ __forceinline__ void moments_shell(CTables *tb, int j, const S (&f)[M], int base,
                                               MomAcc<ST::D> &acc) {
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2;
   double S0 = 0, Sa[D], Sab[D * (D + 1) / 2];
@@ -349,7 +349,7 @@ __device__ __forceinline__ void moments_shell(const Tables *__restrict__ tb, int
 
 // N^a and T^ab from the accumulated sums (plus the reference moments for DEV).
 template <class ST, bool DEV>
-__device__ __forceinline__ void moments_finish(const Tables *__restrict__ tb, const MomAcc<ST::D> &acc,
+__device__ __forceinline__ void moments_finish(CTables *tb, const MomAcc<ST::D> &acc,
                                                double (&Nv)[ST::D + 1], double (&T)[ST::D + 1][ST::D + 1]) {
   constexpr int D = ST::D;
   Nv[0] = acc.N0;
@@ -382,7 +382,7 @@ __device__ __forceinline__ void moments_finish(const Tables *__restrict__ tb, co
 
 // Moments of the populations (product structure), double.
 template <class ST, typename S, bool DEV>
-__device__ __forceinline__ void moments_prod(const Tables *__restrict__ tb, const S (&f)[ST::Q],
+__device__ __forceinline__ void moments_prod(CTables *tb, const S (&f)[ST::Q],
                                              double (&Nv)[ST::D + 1], double (&T)[ST::D + 1][ST::D + 1]) {
   MomAcc<ST::D> acc;
 #pragma unroll
@@ -393,7 +393,7 @@ __device__ __forceinline__ void moments_prod(const Tables *__restrict__ tb, cons
 // dL/dF_i of shell j's populations from dL/dN^a and the symmetric part Ts of dL/dT^ab:
 // sum_a Nb_a p^a + sum_ab Ts_ab p^a p^b, added to out[base .. base + NDIR).
 template <class ST, typename A, int M>
-__device__ __forceinline__ void moments_vjp_shell(const Tables *__restrict__ tb, int j, const double (&Nb)[ST::D + 1],
+__device__ __forceinline__ void moments_vjp_shell(CTables *tb, int j, const double (&Nb)[ST::D + 1],
                                                   const double (&Ts)[ST::D + 1][ST::D + 1], A (&out)[M], int base) {
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2;
   const double p0 = tb->smom[j][0], pm = tb->smom[j][1];
@@ -423,7 +423,7 @@ __device__ __forceinline__ void moments_vjp_shell(const Tables *__restrict__ tb,
 
 // dL/dF_i from dL/dN^a and dL/dT^ab (full matrix): sum_a Nb_a p^a + sum_ab Tb_ab p^a p^b.
 template <class ST, typename A>
-__device__ __forceinline__ void moments_vjp_add(const Tables *__restrict__ tb, const double (&Nb)[ST::D + 1],
+__device__ __forceinline__ void moments_vjp_add(CTables *tb, const double (&Nb)[ST::D + 1],
                                                 const double (&Tb)[ST::D + 1][ST::D + 1], A (&out)[ST::Q]) {
   constexpr int D = ST::D;
   // symmetric parts of Tb
@@ -440,7 +440,7 @@ __device__ __forceinline__ void moments_vjp_add(const Tables *__restrict__ tb, c
 // moments: dL/dN^a (Nb) and dL/dT^ab (Tbar, full matrix) from the incoming adjoints nb, epsb,
 // Tb, Ub (Ub is updated in place).
 template <int D>
-__device__ __forceinline__ void macro_vjp_moments(const Tables *__restrict__ tb, const double (&Nv)[D + 1],
+__device__ __forceinline__ void macro_vjp_moments(CTables *tb, const double (&Nv)[D + 1],
                                                   const double (&T)[D + 1][D + 1], const Macro<D> &mac, double nb,
                                                   double epsb, double Tb, double (&Ub)[D + 1], double (&Nb)[D + 1],
                                                   double (&Tbar)[D + 1][D + 1]) {
@@ -466,7 +466,7 @@ __device__ __forceinline__ void macro_vjp_moments(const Tables *__restrict__ tb,
 // Reverse of the macroscopic map F -> (n, eps, T, U) given the forward values:
 // adds dL/dF to out.  nb, epsb, Tb, Ub are the incoming adjoints.
 template <class ST, typename A>
-__device__ __forceinline__ void macro_vjp(const Tables *__restrict__ tb, const double (&Nv)[ST::D + 1],
+__device__ __forceinline__ void macro_vjp(CTables *tb, const double (&Nv)[ST::D + 1],
                                           const double (&T)[ST::D + 1][ST::D + 1], const Macro<ST::D> &mac,
                                           double nb, double epsb, double Tb, double (&Ub)[ST::D + 1],
                                           A (&out)[ST::Q]) {
@@ -479,7 +479,7 @@ __device__ __forceinline__ void macro_vjp(const Tables *__restrict__ tb, const d
 // Reverse of the collision.  In: f = pre-collision populations F (storage
 // precision; deviations for DEV), mu = dL/dB.  Out: f <- dL/dF, taub = dL/dtau.
 template <class ST, int N, typename S, bool DEV>
-__device__ __forceinline__ bool collide_vjp(const Tables *__restrict__ tb, S (&f)[ST::Q], const S (&mu)[ST::Q],
+__device__ __forceinline__ bool collide_vjp(CTables *tb, S (&f)[ST::Q], const S (&mu)[ST::Q],
                                             double tau, double &taub) {
   constexpr int D = ST::D, ND = ST::NDIR, NPD = ND / 2, KR = ST::NSHELL;
   using B = BasisDef<D, N>;
@@ -572,48 +572,13 @@ __device__ __forceinline__ bool collide_vjp(const Tables *__restrict__ tb, S (&f
 // that one shell's populations are live at a time.
 // ---------------------------------------------------------------------------
 
-// The taps of shell j's populations at a site, from global memory; TRANSPOSE mirrors them as pull_prod does.
-// stage_interpolate sums them.  plane: the shell's first plane; moved on to the next shell's (through
-// an empty asm: all shells' plane addresses at once would not fit the scalar registers).
-template <class ST, typename S, bool TRANSPOSE>
-__device__ __forceinline__ void load_taps(const S *&fin, int64_t sites, const Offs &o, StageTaps<ST, S> &t) {
-  typedef const __attribute__((address_space(1))) char gchar;
-  int m = 0;
-#pragma unroll
-  for (int k = 0; k < ST::NDIR; ++k) {
-    gchar *plane = (gchar *)fin + k * sites * (int64_t)sizeof(S);
-    const int dx = ST::dir(k, 0), dy = ST::dir(k, 1);
-    const int z = (dx != 0) + (dy != 0);
-#pragma unroll
-    for (int tap = 0; tap < (1 << z); ++tap) {
-      int bit = 0, ox = 0, oy = 0;
-      if (dx != 0) {
-        const int c = (tap >> bit++) & 1;
-        ox = dx > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
-      }
-      if (dy != 0) {
-        const int c = (tap >> bit++) & 1;
-        oy = dy > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
-      }
-      if (TRANSPOSE) {
-        ox = -ox;
-        oy = -oy;
-      }
-      const uint32_t off = o.x[ox + 1] + o.y[oy + 1];
-      t.v[m++] = *(const __attribute__((address_space(1))) S *)(plane + off);
-    }
-  }
-  fin += ST::NDIR * sites;
-  asm volatile("" : "+s"(fin));
-}
-
 // Shell j's part of the reverse of the relaxation and of the equilibrium evaluation.  With
 // B_i = F_i + Omega_i (f^eq_i - F_i), Omega_i = (U^0 - v_j n_i . U)/tau = a0 -+ v_j nU:
 // dL/dOmega_i = mu_i (f^eq_i - F_i) accumulates into a0b and nUb, and dL/df^eq_i = mu_i Omega_i,
 // pushed through the shell's equilibrium evaluation, into apb = dL/da'.  f and mu are the shell's
 // pre-collision populations and adjoint (deviations for DEV, as is the equilibrium from ap).
 template <class ST, int N, typename A>
-__device__ __forceinline__ void relax_vjp_shell(const Tables *__restrict__ tb, int j, const A (&f)[ST::NDIR],
+__device__ __forceinline__ void relax_vjp_shell(CTables *tb, int j, const A (&f)[ST::NDIR],
                                                 const A (&mu)[ST::NDIR],
                                                 const double (&ap)[BasisDef<ST::D, N>::NM], double a0,
                                                 const double (&nU)[ST::NDIR / 2], double &a0b,

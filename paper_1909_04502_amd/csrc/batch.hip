@@ -30,7 +30,7 @@ __global__ void __launch_bounds__(BX * BY) k_step_batch(const Tables *__restrict
   const int lo = k * chunk, hi = min(ntiles, lo + chunk);
   for (int t = lo + b; t < hi; t += per_xcd) {
     const int2 d = tiles[t];
-    const Tables *__restrict__ tb = tabs + d.x;
+    CTables *tb = (CTables *)(tabs + d.x);
     const int nx = tb->nx, ny = tb->ny;
     const int64_t sites = tb->sites;
     int x, y;
@@ -58,17 +58,18 @@ __global__ void __launch_bounds__(BX * BY) k_step_batch(const Tables *__restrict
       o.z[dd + 1] = 0u;
     }
     A f[ST::Q];
-    pull_prod<ST, S, false, A>(tb, fi, sites, o, f);
+    // (left to itself the scheduler waits for every load in turn in this loop: 80 us a step instead of 50 for 26
+    // lattices of sides 64..169)
+    pull_ahead<ST, S, A>(tb, fi, sites, o, f);
     const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
     if (!mac.ok) *(volatile int *)err = 1;
     const uint32_t so = (uint32_t)site * (uint32_t)sizeof(S);
-#pragma unroll
-    for (int i = 0; i < ST::Q; ++i) put_pop<NT>(fo, sites, so, i, (S)f[i]);
+    put_pops<NT>(fo, sites, so, f);
   }
 }
 
 // The 64 x 4 tiles of the batch, one per block, their populations pulled through LDS (stage2d.h).  96 lattices of
-// sides 64..512, 5.1 GiB in double: 1184 us a step, 4.7 TB/s of what it has to move, against 1440 for runs of 256
+// sides 64..512, 5.1 GiB in double: 1180 us a step, 4.7 TB/s of what it has to move, against 1440 for runs of 256
 // sites pulled to registers, whose L1 is busy all the time with taps of 8 bytes per lane (97 loads per site for 32
 // populations).  Blocks of a finished tile make room for the next tile's loads, so none walks a list.
 template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, typename A = S>
@@ -81,7 +82,7 @@ __global__ void __launch_bounds__(256) k_step_batch_lds(const Tables *__restrict
   const int t = (int)(blockIdx.x % 8) * ((ntiles + 7) / 8) + (int)(blockIdx.x / 8);
   if (t >= ntiles) return;   // the whole block
   const int2 d = tiles[t];
-  const Tables *__restrict__ tb = tabs + d.x;
+  CTables *tb = (CTables *)(tabs + d.x);
   const int nx = tb->nx, ny = tb->ny;
   const int64_t sites = tb->sites;
   const int gx = (nx + 63) / 64;
@@ -94,8 +95,7 @@ __global__ void __launch_bounds__(256) k_step_batch_lds(const Tables *__restrict
   if (!mac.ok) *err = 1;
   S *fo = fout + elem_off[d.x];
   const uint32_t so = (uint32_t)(y * nx + x) * (uint32_t)sizeof(S);
-#pragma unroll
-  for (int i = 0; i < ST::Q; ++i) put_pop<NT>(fo, sites, so, i, (S)f[i]);
+  put_pops<NT>(fo, sites, so, f);
 }
 
 template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, typename A = S>

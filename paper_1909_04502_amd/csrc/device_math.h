@@ -11,6 +11,18 @@
 
 namespace rlbm {
 
+// The tables as kernels read them: in the constant address space, where uniform reads are scalar loads whatever
+// else the kernel does to memory (the 3D product rule in double: 97 x 130 x 83 0.54 ms a step instead of 0.60).
+// The 3D on-lattice rules read them as plain memory: with scalar loads moved freely past their stores the massive
+// rule takes 3.42 ms at 192^3 instead of 3.27.
+#ifdef RLBM_TABLES_PLAIN
+typedef const Tables CTables;
+typedef const double CDouble;
+#else
+typedef const __attribute__((address_space(4))) Tables CTables;
+typedef const __attribute__((address_space(4))) double CDouble;
+#endif
+
 __device__ __forceinline__ constexpr double eta_c(int a, int b) { return a != b ? 0.0 : (a == 0 ? 1.0 : -1.0); }
 
 // ---------------------------------------------------------------------------
@@ -209,7 +221,7 @@ __device__ __forceinline__ Ratios ratios_2d(double z) {
 // V_j(y) = T_(2j+1)(s)/s (V_0 = 1, V_1 = 2y - 1, the same recurrence): each runs as a Clenshaw sum of its
 // own, so that a single site's chain of dependent operations is half as long as over all terms.
 template <int NS>
-__device__ __forceinline__ void cheb_eval(const double *__restrict__ c, double s, double (&v)[NS]) {
+__device__ __forceinline__ void cheb_eval(CDouble *c, double s, double (&v)[NS]) {
   constexpr int H = kEosTerms / 2;
   static_assert(kEosTerms % 2 == 0, "even and odd terms");
   const double w = 2.0 * s, y2 = w * w - 2.0;   // 2 y
@@ -251,7 +263,7 @@ __device__ __forceinline__ int cheb_piece(double u, double &s) {
 // through uniform (scalar) loads; a wave that straddles a piece boundary evaluates every piece, each with
 // uniform loads, and keeps its own.
 template <int NS>
-__device__ __forceinline__ void cheb_eval_pieces(const double (*__restrict__ c)[NS * kEosTerms], double u, double (&v)[NS]) {
+__device__ __forceinline__ void cheb_eval_pieces(CDouble (*c)[NS * kEosTerms], double u, double (&v)[NS]) {
   double s;
   const int p = cheb_piece(u, s);
   const int q = __builtin_amdgcn_readfirstlane(p);
@@ -270,7 +282,7 @@ __device__ __forceinline__ void cheb_eval_pieces(const double (*__restrict__ c)[
   }
 }
 
-__device__ __forceinline__ double cheb_r(const Tables *__restrict__ tb, double z, bool &inrange) {
+__device__ __forceinline__ double cheb_r(CTables *tb, double z, bool &inrange) {
   // the piece's s in [-1, 1] is affine in log z; the series fits h = r (z + 2) / z, which stays O(1)
   // from z -> 0 (r ~ z/2) to z -> inf (r -> 1)
   const double u = (2.0 * log(z) - (tb->cheb_lo + tb->cheb_hi)) / (tb->cheb_hi - tb->cheb_lo);
@@ -283,7 +295,7 @@ __device__ __forceinline__ double cheb_r(const Tables *__restrict__ tb, double z
 // d = 3: T from e = eps/n through the fitted inverse T = (e - m) u(x), x = log(e - m), and r = K1/K2 at
 // z = m/T from a series in the same x.  Both fits hold to ~1e-15 on T in [kEosTmin, kEosTmax] =
 // [1/128, 128]; outside that range the site is flagged.
-__device__ __forceinline__ bool temperature_3d(const Tables *__restrict__ tb, double e, double m, double &T,
+__device__ __forceinline__ bool temperature_3d(CTables *tb, double e, double m, double &T,
                                                double &r_out) {
   if (m == 0.0) {
     T = e / 3.0;
@@ -293,7 +305,7 @@ __device__ __forceinline__ bool temperature_3d(const Tables *__restrict__ tb, do
   const double d = e - m;
   const double u = (2.0 * log(d) - (tb->chebT_lo + tb->chebT_hi)) / (tb->chebT_hi - tb->chebT_lo);
   double v[2];
-  cheb_eval_pieces<2>((const double (*)[2 * kEosTerms])tb->chebT, u, v);
+  cheb_eval_pieces<2>((CDouble (*)[2 * kEosTerms])tb->chebT, u, v);
   T = d * v[0];
   // r = h z / (z + 2), for z >= 2 as h - 2 h / (z + 2), whose division's rounding shrinks with z
   const double z = m / T;
@@ -356,6 +368,54 @@ __device__ __forceinline__ void basis_moments(double n, double T, const double (
   }
 }
 
+// Uniform pointers pass through this between groups of planes: left to itself the compiler forms the addresses of
+// all planes at once, does not find the scalar registers for them and moves them through vector registers instead
+// (260 of the 1525 vector instructions of the float 2D order-3 step).
+template <typename P>
+__device__ __forceinline__ void one_after_another(P &p) {
+  asm volatile("" : "+s"(p));
+}
+
+// Likewise for the tables: what is read through t from here on is asked for when v is there, not with everything else
+// at the start of the kernel.
+template <typename V>
+__device__ __forceinline__ void from_here_on(CTables *&t, const V &v) {
+  asm volatile("" : "+s"(t) : "v"(v));
+}
+
+// Tiles of bx x by sites in rows of gx, as kernel arguments (scalar registers): blockDim and gridDim would be read
+// from the dispatch packet by vector loads that every wave waits for before its first tap load, and a quotient by gx
+// formed without its reciprocal is a chain of vector instructions.
+struct Tiling {
+  int bx, by;     // block shape
+  int nb;         // tiles
+  int band;       // each XCD takes a contiguous band of the tiles (the hardware deals consecutive blocks round-robin to
+                  // the 8 XCDs, each with its own L2, where neighbouring rows' halos then stay); else as dealt
+  uint32_t gx, inv;   // tiles per row, floor((2^32 - 1) / gx)
+};
+
+inline Tiling tiling(int nx, int ny, int bx, int by, int band) {
+  const uint32_t gx = (uint32_t)((nx + bx - 1) / bx), gy = (uint32_t)((ny + by - 1) / by);
+  return Tiling{bx, by, (int)(gx * gy), band, gx, 0xffffffffu / gx};
+}
+
+// First site of this block's tile.
+__device__ __forceinline__ void tile_origin(const Tiling &tl, int &x0, int &y0) {
+  uint32_t t = blockIdx.x;
+  if (tl.band) {
+    const uint32_t q = (uint32_t)tl.nb / 8, r = (uint32_t)tl.nb % 8, k = t % 8, l = t / 8;
+    t = k * q + (k < r ? k : r) + l;
+  }
+  // t / gx is this or one more (t < 2^31)
+  uint32_t ty = __umulhi(t, tl.inv), tx = t - ty * tl.gx;
+  if (tx >= tl.gx) {
+    ++ty;
+    tx -= tl.gx;
+  }
+  x0 = (int)tx * tl.bx;
+  y0 = (int)ty * tl.by;
+}
+
 // One post-collision population: plane base (uniform) + 32-bit byte offset of the site.  NT marks
 // the store non-temporal: the line is written towards memory without being kept in the L2 or the
 // last-level cache, which pays when the two state buffers are larger than that cache (the next
@@ -365,6 +425,23 @@ __device__ __forceinline__ void put_pop(S *__restrict__ fout, int64_t sites, uin
   S *p = (S *)((char *)(fout + (int64_t)i * sites) + site_off);
   if constexpr (NT) __builtin_nontemporal_store(v, p);
   else *p = v;
+}
+
+// The Q post-collision populations of a site, rounded to the storage type.
+template <bool NT, int Q, typename S, typename A>
+__device__ __forceinline__ void put_pops(S *__restrict__ fout, int64_t sites, uint32_t site_off, const A (&f)[Q]) {
+  typedef __attribute__((address_space(1))) S gS;   // keeps the stores global after the pointer's detour
+  gS *plane = (gS *)fout;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    if (i != 0 && i % 8 == 0) {
+      plane += 8 * sites;
+      one_after_another(plane);
+    }
+    gS *p = (gS *)((__attribute__((address_space(1))) char *)(plane + (i % 8) * sites) + site_off);
+    if constexpr (NT) __builtin_nontemporal_store((S)f[i], p);
+    else *p = (S)f[i];
+  }
 }
 
 }  // namespace rlbm

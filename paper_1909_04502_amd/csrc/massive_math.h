@@ -41,7 +41,7 @@ RLBM_HD constexpr int ipow_dir(int i, int ex, int ey, int ez) {
 // a' = Linv^T Linv M' (coefficients of f^eq / w over the shifted monomials)
 // from the Maxwell-Juettner moments of (n, T, U), class by class.
 template <int D, int N, bool DEV, typename A>
-__device__ __forceinline__ void massive_coefficients(const Tables *__restrict__ tb, const Macro<D> &mac,
+__device__ __forceinline__ void massive_coefficients(CTables *tb, const Macro<D> &mac,
                                                      const Ratios &rr, A (&ap)[BasisDef<D, N>::NM]) {
   using B = BasisDef<D, N>;
   const double m = tb->m;
@@ -81,7 +81,7 @@ __device__ __forceinline__ void massive_coefficients(const Tables *__restrict__ 
 // site takes the equilibrium at rest of its own n and its own or the plane's
 // prescribed temperature (Omega = 1).
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT = false>
-__device__ __forceinline__ Macro<ST::D> collide_massive(const Tables *__restrict__ tb, S (&f)[ST::Q], double tau,
+__device__ __forceinline__ Macro<ST::D> collide_massive(CTables *tb, S (&f)[ST::Q], double tau,
                                                         double wallT = -1.0) {
   constexpr int D = ST::D, Q = ST::Q, NG = ST::NG, NT = D * (D + 1) / 2;
   constexpr bool REST = (Q & 1) != 0;   // an odd count carries a rest population, the last one
@@ -227,6 +227,8 @@ __device__ __forceinline__ Macro<ST::D> collide_massive(const Tables *__restrict
   auto feq_full = [&](int i, A e) { return DEV ? e + tab<A>(tb->fref[i], tb->freff[i]) : e; };
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
+    if (N > 2 && g % 2 == 0)   // (order 2: all fit the scalar registers)
+      from_here_on(tb, g == 0 ? ap[0] : f[ST::gfirst(g - 2)]);
     A ce[20];
 #pragma unroll
     for (int q = 0; q < AT.n; ++q) {

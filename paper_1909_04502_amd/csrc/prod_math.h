@@ -57,7 +57,7 @@ RLBM_HD constexpr double dir_weight(int k) {
 }
 
 template <typename A>
-__device__ __forceinline__ A tab(const double &d, const float &f) {
+__device__ __forceinline__ A tab(double d, float f) {
   if constexpr (sizeof(A) == 8) return d;
   else return f;
 }
@@ -76,7 +76,7 @@ struct Offs {
 // A is the arithmetic type of the interpolation and of the result (the storage type S, or double
 // for float deviations updated in double).
 template <class ST, typename S, bool TRANSPOSE = false, typename A = S>
-__device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S *__restrict__ fin, int64_t sites,
+__device__ __forceinline__ void pull_prod(CTables *tb, const S *__restrict__ fin, int64_t sites,
                                           const Offs &o, A (&f)[ST::Q]) {
   static_assert(ST::D == 2, "the 3D rules: split.hip");
   constexpr int ND = ST::NDIR, KR = ST::NSHELL;
@@ -84,6 +84,10 @@ __device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S
   gchar *base = (gchar *)fin;
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
+    if (j != 0) {
+      base += ND * sites * (int64_t)sizeof(S);
+      one_after_another(base);
+    }
     const A v = tab<A>(tb->sv[j], tb->svf[j]);
     A pw[3][3];
 #pragma unroll
@@ -104,7 +108,7 @@ __device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
       const int i = j * ND + k;
-      gchar *plane = base + (int64_t)i * sites * (int64_t)sizeof(S);
+      gchar *plane = base + k * sites * (int64_t)sizeof(S);
       const int dx = ST::dir(k, 0), dy = ST::dir(k, 1);
       const int z = (dx != 0) + (dy != 0);
       A acc = 0;
@@ -136,7 +140,7 @@ __device__ __forceinline__ void pull_prod(const Tables *__restrict__ tb, const S
 // Wall temperature of a site: negative off the walls; on the first or last
 // plane of a wall axis the prescribed temperature of that plane, or 0 for the
 // site's own temperature.
-__device__ __forceinline__ double site_wall(const Tables *__restrict__ tb, int x, int y, int z) {
+__device__ __forceinline__ double site_wall(CTables *tb, int x, int y, int z) {
   if (tb->wall[0] && (x == 0 || x == tb->nx - 1)) return tb->wallT[0][x == 0 ? 0 : 1];
   if (tb->wall[1] && (y == 0 || y == tb->ny - 1)) return tb->wallT[1][y == 0 ? 0 : 1];
   if (tb->wall[2] && (z == 0 || z == tb->nz - 1)) return tb->wallT[2][z == 0 ? 0 : 1];
@@ -146,7 +150,7 @@ __device__ __forceinline__ double site_wall(const Tables *__restrict__ tb, int x
 // The temperature and moment ratios the equilibrium is built from: the
 // site's own, or a wall plane's prescribed temperature.
 template <int D>
-__device__ __forceinline__ void equilibrium_state(const Tables *__restrict__ tb, const Macro<D> &mac,
+__device__ __forceinline__ void equilibrium_state(CTables *tb, const Macro<D> &mac,
                                                   const Ratios &rr, double wallT, double &Te, Ratios &re) {
   Te = mac.T;
   re = rr;
@@ -166,7 +170,7 @@ __device__ __forceinline__ void equilibrium_state(const Tables *__restrict__ tb,
 // instantiation, so that lattices without them keep the leaner kernel).
 // wallT: see site_wall.
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT = false>
-__device__ __forceinline__ Macro<ST::D> collide_prod(const Tables *__restrict__ tb, S (&f)[ST::Q], double tau,
+__device__ __forceinline__ Macro<ST::D> collide_prod(CTables *tb, S (&f)[ST::Q], double tau,
                                                      double wallT = -1.0) {
   const bool wall = EXT && wallT >= 0.0;
   static_assert(ST::D == 2, "the 3D rules: split.hip");
@@ -342,6 +346,9 @@ __device__ __forceinline__ Macro<ST::D> collide_prod(const Tables *__restrict__ 
   };
 #pragma unroll
   for (int j = 0; j < KR; ++j) {
+    // (order 2: all fit the scalar registers; float arithmetic: between the shells it would also change which
+    // products are fused with which sums, and so the last bits)
+    if (N > 2 && (j == 0 || (j == 2 && (sizeof(A) == 8 || EXT)))) from_here_on(tb, j == 0 ? ap[0] : f[0]);
     A ce[20];
 #pragma unroll
     for (int q = 0; q < AT.n; ++q) {

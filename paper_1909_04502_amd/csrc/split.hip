@@ -15,7 +15,7 @@
 // storage and 3.05 of 3.60 ms in double; a copy of the same planes takes 1.17 and 2.35 ms.
 // Per step, against the register kernel that this one replaced (64 x 4 sites per block, one site per thread,
 // the equation of state in the same form):
-//   double 97 x 130 x 83     0.60 ms (2.9 TB/s of population traffic)   0.91
+//   double 97 x 130 x 83     0.54 ms (3.2 TB/s of population traffic)   0.91
 //   double 192^3             3.6 ms (3.3 TB/s)                          4.1
 //   double 128^3, order 2    0.77 ms                                    2.8
 //   float 256^3              4.1 ms (3.4 TB/s)                          4.2
@@ -40,7 +40,7 @@ namespace rlbm {
 // The update from the pre-collision populations f of this wave's shell w on: state, relaxation, store (RELAX =
 // false: the fields alone).
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT, bool NT, typename A>
-__device__ __forceinline__ void split_update(const Tables *__restrict__ tb, SplitLds<N, ST::NSHELL, A> &sh, int w, int lane,
+__device__ __forceinline__ void split_update(CTables *tb, SplitLds<N, ST::NSHELL, A> &sh, int w, int lane,
                                              bool live, int x, int y, int z, A (&f)[ST::NDIR], S *__restrict__ fout,
                                              const void *__restrict__ tau_field, const FieldPtrs &fields, int *err) {
   constexpr int ND = ST::NDIR, W = ST::NSHELL;
@@ -94,8 +94,9 @@ __device__ __forceinline__ void split_update(const Tables *__restrict__ tb, Spli
 // The step, and (RELAX = false) the fields of the streamed state.
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT, bool NT, typename A, bool XCH>
 __global__ void __launch_bounds__(64 * ST::NSHELL) __attribute__((amdgpu_waves_per_eu(sizeof(A) == 8 ? 3 : 4, 8)))
-k_step_split(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__restrict__ fout,
+k_step_split(const Tables *__restrict__ tabs, const S *__restrict__ fin, S *__restrict__ fout,
              const void *__restrict__ tau_field, FieldPtrs fields, int *err, SplitTiling tl) {
+  CTables *tb = (CTables *)tabs;
   static_assert(ST::D == 3 && !ST::ONLAT, "3D product rules");
   constexpr int ND = ST::NDIR, W = ST::NSHELL;
   __shared__ SplitLds<N, W, A> sh;
@@ -112,11 +113,12 @@ k_step_split(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__rest
 
 // f(x, 0) = f^eq(n0, T0, U(u0)) (1 + amp xi) from the projection rows, then collide; store f*(x, 0).
 template <class ST, int N, typename S, bool DEV, typename A>
-__global__ void __launch_bounds__(64 * ST::NSHELL) k_init_split(const Tables *__restrict__ tb, const double *__restrict__ n0,
+__global__ void __launch_bounds__(64 * ST::NSHELL) k_init_split(const Tables *__restrict__ tabs, const double *__restrict__ n0,
                                                                 const double *__restrict__ T0, const double *__restrict__ u0,
                                                                 const double *__restrict__ noise, double amp,
                                                                 S *__restrict__ fout, const void *__restrict__ tau_field,
                                                                 FieldPtrs fields, int *err, SplitTiling tl) {
+  CTables *tb = (CTables *)tabs;
   constexpr int ND = ST::NDIR, W = ST::NSHELL;
   using B = BasisDef<3, N>;
   __shared__ SplitLds<N, W, A> sh;

@@ -57,7 +57,7 @@ __device__ __forceinline__ void shell_sums3(const A *f, A (&S)[10]) {
 template <typename A>
 struct Moments3 {
   A N0 = 0, T00 = 0, Na[3] = {0, 0, 0}, T0a[3] = {0, 0, 0}, Tab[6] = {0, 0, 0, 0, 0, 0};
-  __device__ __forceinline__ void add(const Tables *__restrict__ tb, int j, const A (&S)[10]) {
+  __device__ __forceinline__ void add(CTables *tb, int j, const A (&S)[10]) {
     const A p0 = tab<A>(tb->smom[j][0], tb->smomf[j][0]);
     const A pm = tab<A>(tb->smom[j][1], tb->smomf[j][1]);
     const A p00 = tab<A>(tb->smom[j][2], tb->smomf[j][2]);
@@ -77,7 +77,7 @@ struct Moments3 {
 
 // N^a and T^ab in double (the reference's added back for deviations).
 template <bool DEV, typename A>
-__device__ __forceinline__ void moments_to_state(const Tables *__restrict__ tb, const Moments3<A> &mom, double (&Nv)[4],
+__device__ __forceinline__ void moments_to_state(CTables *tb, const Moments3<A> &mom, double (&Nv)[4],
                                                  double (&T)[4][4]) {
   Nv[0] = mom.N0;
   T[0][0] = mom.T00;
@@ -121,7 +121,7 @@ RLBM_HD constexpr int ang_index3(int ex, int ey, int ez) {
 // and odd parts of f^eq on the direction pairs are formed from the sums that the pairs of an axis, a plane
 // and the corners share.  ap(k): a' of basis monomial k; a0 = U^0 / tau; nU(q) = (n_q . U) / tau of pair q.
 template <int N, bool EXT, typename A, class Ap, class NU, class Extra>
-__device__ __forceinline__ void relax_shell3(const Tables *__restrict__ tb, int j, Ap &&ap, A a0, NU &&nU, Extra &&extra,
+__device__ __forceinline__ void relax_shell3(CTables *tb, int j, Ap &&ap, A a0, NU &&nU, Extra &&extra,
                                              A *f) {
   constexpr AngTable<3, N> AT{};
   A ce[20];
@@ -278,7 +278,7 @@ inline SplitTiling split_tiling(int nx, int ny, int nz, unsigned &blocks) {
 // The block's run, and the site of this lane (a lane past the run's live sites takes the last of them: its
 // loads stay inside the lattice, and it stores nothing).  False where the whole run lies past the lattice.
 template <bool XCH>
-__device__ __forceinline__ bool split_site(const Tables *__restrict__ tb, const SplitTiling &tl, int lane, SplitRun &run,
+__device__ __forceinline__ bool split_site(CTables *tb, const SplitTiling &tl, int lane, SplitRun &run,
                                            int &x, int &y) {
   const uint32_t k = blockIdx.x % 8, l = blockIdx.x / 8, per = (uint32_t)(tl.runs * tl.planes);
   const uint32_t t = k * (uint32_t)tl.chunk + l;
@@ -354,7 +354,7 @@ using XExchange = A[18][66];
 // before it, which keeps the loads in flight within the registers; float rows, half as long, are all
 // asked for at once (at 256^3 in groups 5.4 ms, at once 4.1).
 template <class ST, typename S, typename A, bool XCH>
-__device__ __forceinline__ void pull_shell3(const Tables *__restrict__ tb, const S *__restrict__ base, int64_t sites,
+__device__ __forceinline__ void pull_shell3(CTables *tb, const S *__restrict__ base, int64_t sites,
                                             int j, const SplitRun &run, int lane, int x, int y, XExchange<A> &ex,
                                             A (&f)[ST::NDIR]) {
   constexpr int ND = ST::NDIR;
@@ -496,7 +496,7 @@ __device__ __forceinline__ void pull_shell3(const Tables *__restrict__ tb, const
 
 // N^a and T^ab of the lane's site from the shells' sums.
 template <int W, typename A, bool DEV>
-__device__ __forceinline__ void split_moments(const Tables *__restrict__ tb, const A (&sums)[W][18 * 66], int lane,
+__device__ __forceinline__ void split_moments(CTables *tb, const A (&sums)[W][18 * 66], int lane,
                                               double (&Nv)[4], double (&T)[4][4]) {
   Moments3<A> mom;
 #pragma unroll
@@ -509,7 +509,7 @@ __device__ __forceinline__ void split_moments(const Tables *__restrict__ tb, con
   moments_to_state<DEV>(tb, mom, Nv, T);
 }
 // Steps 2-4, without the state in LDS.
-__device__ __forceinline__ Macro<3> split_state(const Tables *__restrict__ tb, const double (&Nv)[4], const double (&T)[4][4],
+__device__ __forceinline__ Macro<3> split_state(CTables *tb, const double (&Nv)[4], const double (&T)[4][4],
                                                 Ratios &rr) {
   Macro<3> mac;
   mac.ok = landau_frame<3, 3>(T, mac.eps, mac.U);
@@ -524,7 +524,7 @@ __device__ __forceinline__ Macro<3> split_state(const Tables *__restrict__ tb, c
 
 // The Maxwell-Juettner moments of the initial fields at a site; false where they are not physical.
 template <int N>
-__device__ __forceinline__ bool first_moments3(const Tables *__restrict__ tb, const double *__restrict__ n0,
+__device__ __forceinline__ bool first_moments3(CTables *tb, const double *__restrict__ n0,
                                                const double *__restrict__ T0, const double *__restrict__ u0, uint32_t site,
                                                double (&M)[BasisDef<3, N>::NM]) {
   double U[4], uu = 0.0;
@@ -560,7 +560,7 @@ __device__ __forceinline__ void put_state(X &sh, int lane, double n, double T, c
 // A wall site (wallT >= 0, see site_wall) relaxes fully to the equilibrium at rest of its own n and its own or
 // the wall's T.
 template <bool EXT, typename A, class X>
-__device__ __forceinline__ void split_put(const Tables *__restrict__ tb, const Macro<3> &mac, const Ratios &rr, double tau,
+__device__ __forceinline__ void split_put(CTables *tb, const Macro<3> &mac, const Ratios &rr, double tau,
                                           double wallT, int lane, X &sh) {
   const bool wall = EXT && wallT >= 0.0;
   double Ue[4], Te = mac.T;
@@ -595,13 +595,13 @@ __device__ __forceinline__ void split_put(const Tables *__restrict__ tb, const M
 
 // a' = Linv^T Linv M' on parity class C (the block of the projection that its monomials span)
 template <int N, bool DEV, typename A, int C, class X>
-__device__ __forceinline__ void split_class(const Tables *__restrict__ tb, int lane, double n, double T,
+__device__ __forceinline__ void split_class(CTables *tb, int lane, double n, double T,
                                             const double (&U)[4], const Ratios &rr, X &sh) {
   constexpr ClassTable<3, N> CL{};
   constexpr int K = CL.cnt[C];
   if constexpr (K > 0) {
     const double m = tb->m;
-    const double *lp = tb->LinvP + CL.off[C];
+    CDouble *lp = tb->LinvP + CL.off[C];
     double mc[K], ak[K];
 #pragma unroll
     for (int t = 0; t < K; ++t) {
@@ -641,14 +641,14 @@ RLBM_HD constexpr int class_owner(int W, int c) {
 }
 
 template <int N, int W, bool DEV, typename A, class X, int... C>
-__device__ __forceinline__ void split_classes(const Tables *__restrict__ tb, int w, int lane, double n, double T,
+__device__ __forceinline__ void split_classes(CTables *tb, int w, int lane, double n, double T,
                                               const double (&U)[4], const Ratios &rr, X &sh,
                                               std::integer_sequence<int, C...>) {
   ((w == class_owner(W, C) ? split_class<N, DEV, A, C>(tb, lane, n, T, U, rr, sh) : (void)0), ...);
 }
 
 template <int N, int W, bool DEV, typename A, class X>
-__device__ __forceinline__ void split_coefficients(const Tables *__restrict__ tb, int w, int lane, X &sh) {
+__device__ __forceinline__ void split_coefficients(CTables *tb, int w, int lane, X &sh) {
   const double n = sh.mac[0][lane], T = sh.mac[1][lane];
   double U[4];
 #pragma unroll
@@ -691,7 +691,7 @@ __device__ __forceinline__ void put_moments(const Moments3<A> &mom, int lane, A 
 // The state of the lane's site from all waves' moments; fields and flag; and, for the relaxation, what the
 // equilibrium and Omega (and the force) are built from, to LDS over the moments.  A wall site: as split_put.
 template <int N, int W, typename S, bool DEV, bool RELAX, bool EXT>
-__device__ __forceinline__ void onlat_state(const Tables *__restrict__ tb, OnlatLds<N, W, S> &sh, int lane, bool live, int x,
+__device__ __forceinline__ void onlat_state(CTables *tb, OnlatLds<N, W, S> &sh, int lane, bool live, int x,
                                             int y, int z, uint32_t site, const void *__restrict__ tau_field,
                                             const FieldPtrs &fields, int *err) {
   const int64_t sites = tb->sites;

@@ -12,6 +12,7 @@
 //   192^3 float              1.68 ms    1.90
 //   40 x 33 x 30 double      0.030 ms   0.034
 // (occupancy targets: double 3 waves per SIMD, 2 gives 3.38 ms and 4 spills, 6.9; float 4, as fast as 3)
+#define RLBM_TABLES_PLAIN   // device_math.h
 #include <hip/hip_runtime.h>
 
 #include "device_math.h"
@@ -60,7 +61,7 @@ RLBM_HD constexpr bool wg_complete() {
 static_assert(wg_complete<Stencil<ST_MASSIVE3D, 3>>(), "every group has its wave");
 
 template <class ST, int P, typename S>
-__device__ __forceinline__ void load_groups(const Tables *__restrict__ tb, const S *__restrict__ fin, int x, int y, int z,
+__device__ __forceinline__ void load_groups(CTables *tb, const S *__restrict__ fin, int x, int y, int z,
                                             S (&f)[WaveGroups<ST>::MAX]) {
   constexpr int R = ST::RMAX;
   typedef const __attribute__((address_space(1))) char gchar;
@@ -86,7 +87,7 @@ __device__ __forceinline__ void load_groups(const Tables *__restrict__ tb, const
 
 // The moments of wave P's populations, to LDS.
 template <class ST, int P, typename A, class X>
-__device__ __forceinline__ void group_moments(const Tables *__restrict__ tb, const A (&f)[WaveGroups<ST>::MAX], int lane,
+__device__ __forceinline__ void group_moments(CTables *tb, const A (&f)[WaveGroups<ST>::MAX], int lane,
                                               X &sh) {
   Moments3<A> mom;
 #pragma unroll
@@ -141,7 +142,7 @@ __device__ __forceinline__ void group_moments(const Tables *__restrict__ tb, con
 
 // Steps 5 and 8 (and the force) of wave P's populations, and their store.
 template <class ST, int N, int P, typename S, bool DEV, bool EXT, bool NT, typename A, class X>
-__device__ __forceinline__ void relax_groups(const Tables *__restrict__ tb, const X &sh, int lane, const A (&f)[WaveGroups<ST>::MAX],
+__device__ __forceinline__ void relax_groups(CTables *tb, const X &sh, int lane, const A (&f)[WaveGroups<ST>::MAX],
                                              uint32_t site_off, S *__restrict__ fout) {
   constexpr AngTable<3, N> AT{};
   const int64_t sites = tb->sites;
@@ -221,7 +222,7 @@ __device__ __forceinline__ void for_wave(int w, F &&body) {
 
 // The update from wave w's pre-collision populations f on (RELAX = false: the fields alone).
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT, bool NT>
-__device__ __forceinline__ void onlat_update(const Tables *__restrict__ tb, OnlatLds<N, WaveGroups<ST>::W, S> &sh, int w, int lane,
+__device__ __forceinline__ void onlat_update(CTables *tb, OnlatLds<N, WaveGroups<ST>::W, S> &sh, int w, int lane,
                                              bool live, int x, int y, int z, const S (&f)[WaveGroups<ST>::MAX],
                                              S *__restrict__ fout, const void *__restrict__ tau_field, const FieldPtrs &fields,
                                              int *err) {
@@ -243,8 +244,9 @@ __device__ __forceinline__ void onlat_update(const Tables *__restrict__ tb, Onla
 
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT, bool NT>
 __global__ void __launch_bounds__(64 * WaveGroups<ST>::W) __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 3 : 4, 8)))
-k_step_onlat3d(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__restrict__ fout,
+k_step_onlat3d(const Tables *__restrict__ tabs, const S *__restrict__ fin, S *__restrict__ fout,
                const void *__restrict__ tau_field, FieldPtrs fields, int *err, SplitTiling tl) {
+  CTables *tb = (CTables *)tabs;
   constexpr int W = WaveGroups<ST>::W;
   __shared__ OnlatLds<N, W, S> sh;
   const int lane = threadIdx.x & 63;
@@ -260,9 +262,10 @@ k_step_onlat3d(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__re
 // f(x, 0) = f^eq(n0, T0, U(u0)) (1 + amp xi) from the projection rows, then collide; store f*(x, 0).
 template <class ST, int N, typename S, bool DEV, bool EXT>
 __global__ void __launch_bounds__(64 * WaveGroups<ST>::W) k_init_onlat3d(
-    const Tables *__restrict__ tb, const double *__restrict__ n0, const double *__restrict__ T0, const double *__restrict__ u0,
+    const Tables *__restrict__ tabs, const double *__restrict__ n0, const double *__restrict__ T0, const double *__restrict__ u0,
     const double *__restrict__ noise, double amp, S *__restrict__ fout, const void *__restrict__ tau_field, FieldPtrs fields,
     int *err, SplitTiling tl) {
+  CTables *tb = (CTables *)tabs;
   constexpr int W = WaveGroups<ST>::W;
   using B = BasisDef<3, N>;
   __shared__ OnlatLds<N, W, S> sh;

@@ -9,6 +9,7 @@
 // long as one block: what counts there is that few instructions have to be fetched (code that spelled out each
 // wave's populations was 84 KB, more than an instruction cache holds, and took 57 us a step on 6400 sites) and
 // that 288 loads go out at once.
+#define RLBM_TABLES_PLAIN   // device_math.h
 #include <hip/hip_runtime.h>
 
 #include "device_math.h"
@@ -69,7 +70,7 @@ __constant__ UnitTable c_units = kTable;
 
 // The populations of unit u at the site (x, y, z): f[2 q], f[2 q + 1] of pair q and its opposite; 0 where none.
 template <typename S>
-__device__ __forceinline__ void load_unit(const Tables *__restrict__ tb, const S *__restrict__ fin, const Unit &u, int x, int y,
+__device__ __forceinline__ void load_unit(CTables *tb, const S *__restrict__ fin, const Unit &u, int x, int y,
                                           int z, S (&f)[8]) {
   typedef const __attribute__((address_space(1))) char gchar;
   typedef const __attribute__((address_space(1))) S gS;
@@ -96,7 +97,7 @@ __device__ __forceinline__ void load_unit(const Tables *__restrict__ tb, const S
 }
 
 template <typename A>
-__device__ __forceinline__ void unit_moments(const Tables *__restrict__ tb, const Unit &u, const A (&f)[8], Moments3<A> &mom) {
+__device__ __forceinline__ void unit_moments(CTables *tb, const Unit &u, const A (&f)[8], Moments3<A> &mom) {
   const int g = u.g;
   const A a = (A)u.n[0], b = (A)u.n[1], c = (A)u.n[2];
   const A s0 = f[0] + f[1], s1 = f[2] + f[3], s2 = f[4] + f[5], s3 = f[6] + f[7];
@@ -151,7 +152,7 @@ __device__ __forceinline__ void relax_unit(const Unit &u, const S (&ce)[20], S a
 
 // The update from wave w's pre-collision populations f on (RELAX = false: the fields alone).
 template <typename S, bool DEV, bool RELAX, bool NT>
-__device__ __forceinline__ void ur3d_update(const Tables *__restrict__ tb, OnlatLds<3, kWaves, S> &sh, int w, int lane, bool live,
+__device__ __forceinline__ void ur3d_update(CTables *tb, OnlatLds<3, kWaves, S> &sh, int w, int lane, bool live,
                                             int x, int y, int z, const S (&f)[kUnits][8], S *__restrict__ fout,
                                             const void *__restrict__ tau_field, const FieldPtrs &fields, int *err) {
   constexpr AngTable<3, 3> AT{};
@@ -190,8 +191,9 @@ __device__ __forceinline__ void ur3d_update(const Tables *__restrict__ tb, Onlat
 
 template <typename S, bool DEV, bool RELAX, bool NT>
 __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 2 : 4, 8)))
-k_step_ur3d(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__restrict__ fout, const void *__restrict__ tau_field,
+k_step_ur3d(const Tables *__restrict__ tabs, const S *__restrict__ fin, S *__restrict__ fout, const void *__restrict__ tau_field,
             FieldPtrs fields, int *err, SplitTiling tl) {
+  CTables *tb = (CTables *)tabs;
   __shared__ OnlatLds<3, kWaves, S> sh;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -206,11 +208,12 @@ k_step_ur3d(const Tables *__restrict__ tb, const S *__restrict__ fin, S *__restr
 
 // f(x, 0) = f^eq(n0, T0, U(u0)) (1 + amp xi) from the projection rows, then collide; store f*(x, 0).
 template <typename S, bool DEV>
-__global__ void __launch_bounds__(64 * kWaves) k_init_ur3d(const Tables *__restrict__ tb, const double *__restrict__ n0,
+__global__ void __launch_bounds__(64 * kWaves) k_init_ur3d(const Tables *__restrict__ tabs, const double *__restrict__ n0,
                                                            const double *__restrict__ T0, const double *__restrict__ u0,
                                                            const double *__restrict__ noise, double amp, S *__restrict__ fout,
                                                            const void *__restrict__ tau_field, FieldPtrs fields, int *err,
                                                            SplitTiling tl) {
+  CTables *tb = (CTables *)tabs;
   using B = BasisDef<3, 3>;
   __shared__ OnlatLds<3, kWaves, S> sh;
   const int lane = threadIdx.x & 63;

@@ -88,7 +88,7 @@ struct StagePlan {
   uint32_t scol[2];       // and in the plane, of this lane's part of the side column
   bool slane[2];          // this lane takes part in the side load
 
-  __device__ __forceinline__ StagePlan(const Tables *__restrict__ tb, int x0, int y0) {
+  __device__ __forceinline__ StagePlan(CTables *tb, int x0, int y0) {
     const int nx = tb->nx, ny = tb->ny, openx = tb->open[0], openy = tb->open[1];
     const int lane = threadIdx.x;
     w = __builtin_amdgcn_readfirstlane(threadIdx.y);
@@ -191,7 +191,7 @@ __device__ __forceinline__ void stage_read(const __attribute__((address_space(3)
 }
 
 template <class ST, typename S, typename A>
-__device__ __forceinline__ void stage_interpolate(const Tables *__restrict__ tb, int j, const StageTaps<ST, S> &t,
+__device__ __forceinline__ void stage_interpolate(CTables *tb, int j, const StageTaps<ST, S> &t,
                                                   A (&fs)[ST::NDIR]) {
   const A v = tab<A>(tb->sv[j], tb->svf[j]);
   A pw[3][3];
@@ -226,12 +226,67 @@ __device__ __forceinline__ void stage_interpolate(const Tables *__restrict__ tb,
   }
 }
 
+// The taps of a shell's populations at a site, from global memory; TRANSPOSE mirrors them as pull_prod does.
+// stage_interpolate sums them.  fin: the shell's first plane; moved on to the next shell's.
+template <class ST, typename S, bool TRANSPOSE>
+__device__ __forceinline__ void load_taps(const S *&fin, int64_t sites, const Offs &o, StageTaps<ST, S> &t) {
+  typedef const __attribute__((address_space(1))) char gchar;
+  int m = 0;
+#pragma unroll
+  for (int k = 0; k < ST::NDIR; ++k) {
+    gchar *plane = (gchar *)fin + k * sites * (int64_t)sizeof(S);
+    const int dx = ST::dir(k, 0), dy = ST::dir(k, 1);
+    const int z = (dx != 0) + (dy != 0);
+#pragma unroll
+    for (int tap = 0; tap < (1 << z); ++tap) {
+      int bit = 0, ox = 0, oy = 0;
+      if (dx != 0) {
+        const int c = (tap >> bit++) & 1;
+        ox = dx > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
+      }
+      if (dy != 0) {
+        const int c = (tap >> bit++) & 1;
+        oy = dy > 0 ? (c ? 0 : -1) : (c ? 1 : 0);
+      }
+      if (TRANSPOSE) {
+        ox = -ox;
+        oy = -oy;
+      }
+      const uint32_t off = o.x[ox + 1] + o.y[oy + 1];
+      t.v[m++] = *(const __attribute__((address_space(1))) S *)(plane + off);
+    }
+  }
+  fin += ST::NDIR * sites;
+  one_after_another(fin);
+}
+
+// pull_prod with the loads of a shell asked for before the sums of the shell before it.
+template <class ST, typename S, typename A>
+__device__ __forceinline__ void pull_ahead(CTables *tb, const S *fin, int64_t sites, const Offs &o, A (&f)[ST::Q]) {
+  constexpr int KR = ST::NSHELL;
+  StageTaps<ST, S> t[2];
+  load_taps<ST, S, false>(fin, sites, o, t[0]);
+#pragma unroll
+  for (int j = 0; j < KR; ++j) {
+    if (j + 1 < KR) load_taps<ST, S, false>(fin, sites, o, t[(j + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    A fs[ST::NDIR];
+    stage_interpolate<ST, S, A>(tb, j, t[j & 1], fs);
+#pragma unroll
+    for (int k = 0; k < ST::NDIR; ++k) {
+      asm volatile("" : "+v"(fs[k]));   // summed here: its taps' registers are free again
+      f[j * ST::NDIR + k] = fs[k];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // The pre-collision populations of this thread's site (x0 + threadIdx.x, y0 + threadIdx.y) of a 64 x 4
 // tile.  Called by all threads of the block, also those of sites past the lattice's edge: they take part
 // in the loads and barriers, and their populations are not those of a site.  No vector memory access of
 // the caller may be in flight.
 template <class ST, typename S, typename A>
-__device__ __forceinline__ void stage_pull(const Tables *__restrict__ tb, const S *__restrict__ fin, int64_t sites, int x0,
+__device__ __forceinline__ void stage_pull(CTables *tb, const S *__restrict__ fin, int64_t sites, int x0,
                                            int y0, S *buf, A (&f)[ST::Q]) {
   using L = Stage2D<ST, S>;
   constexpr int KR = ST::NSHELL;

@@ -67,7 +67,7 @@ __device__ __forceinline__ void flag_error(int *err) {
 }
 
 template <typename S>
-__device__ __forceinline__ double site_tau(const Tables *__restrict__ tb, const void *tau_field, int64_t site) {
+__device__ __forceinline__ double site_tau(CTables *tb, const void *tau_field, int64_t site) {
   // the lattice's tau through a scalar load, chosen by value (a per-site load through a pointer
   // picked between the field and the table would be a vector load the wave waits for)
   const double tau = tb->tau;
@@ -79,14 +79,14 @@ __device__ __forceinline__ double site_tau(const Tables *__restrict__ tb, const 
 // Kernels
 // ---------------------------------------------------------------------------
 template <class ST, typename S>
-__device__ __forceinline__ Offs make_offs(const Tables *__restrict__ tb, int x, int y, int z) {
+__device__ __forceinline__ Offs make_offs(CTables *tb, int x, int y) {
   Offs o;
-  const uint32_t nx = tb->nx, nxy = (uint32_t)tb->nx * tb->ny;
+  const uint32_t nx = tb->nx;
 #pragma unroll
   for (int d = -1; d <= 1; ++d) {
     o.x[d + 1] = (uint32_t)wrap_or_clamp(x + d, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
     o.y[d + 1] = (uint32_t)wrap_or_clamp(y + d, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
-    o.z[d + 1] = ST::D == 3 ? (uint32_t)wrap_or_clamp(z + d, tb->nz, tb->open[2]) * nxy * (uint32_t)sizeof(S) : 0u;
+    o.z[d + 1] = 0u;
   }
   return o;
 }
@@ -98,11 +98,11 @@ template <class ST, typename S, int R, int... I>
 __device__ __forceinline__ void gather_onlat_impl(const S *__restrict__ fin, int64_t sites, const uint32_t (&ox)[2 * R + 1],
                                                   const uint32_t (&oy)[2 * R + 1], S (&f)[ST::Q],
                                                   std::integer_sequence<int, I...>) {
-  ((f[I] = *(const S *)((const char *)(fin + (int64_t)I * sites) + ox[R - ST::dir(I, 0)] + oy[R - ST::dir(I, 1)])), ...);
+  ((f[I] = *(const S *)((const char *)(fin + (int64_t)I * sites) + (ox[R - ST::dir(I, 0)] + oy[R - ST::dir(I, 1)]))), ...);
 }
 
 template <class ST, typename S>
-__device__ __forceinline__ void gather_onlat(const Tables *__restrict__ tb, const S *__restrict__ fin, int64_t sites,
+__device__ __forceinline__ void gather_onlat(CTables *tb, const S *__restrict__ fin, int64_t sites,
                                              int x, int y, S (&f)[ST::Q]) {
   constexpr int R = ST::RMAX;
   // byte offsets of the columns x + k - R and the rows y + k - R (k = 0 .. 2R)
@@ -119,13 +119,13 @@ __device__ __forceinline__ void gather_onlat(const Tables *__restrict__ tb, cons
 // pre-collision populations at the site, in the arithmetic type A (the storage type S, or double
 // for float deviations updated in double: product rules)
 template <class ST, typename S, typename A = S>
-__device__ __forceinline__ void gather(const Tables *__restrict__ tb, const S *__restrict__ fin, int64_t sites, int x,
-                                       int y, int z, A (&f)[ST::Q]) {
+__device__ __forceinline__ void gather(CTables *tb, const S *__restrict__ fin, int64_t sites, int x,
+                                       int y, A (&f)[ST::Q]) {
   if constexpr (ST::ONLAT) {
     static_assert(sizeof(A) == sizeof(S), "on-lattice rules compute in their storage type");
     gather_onlat<ST, S>(tb, fin, sites, x, y, f);
   } else {
-    const Offs o = make_offs<ST, S>(tb, x, y, z);
+    const Offs o = make_offs<ST, S>(tb, x, y);
     pull_prod<ST, S, false, A>(tb, fin, sites, o, f);
   }
 }
@@ -134,7 +134,7 @@ __device__ __forceinline__ void gather(const Tables *__restrict__ tb, const S *_
 // the F32_DEV mode) is replaced by f* in place; returns the macro state of the
 // pre-collision populations.  wallT: see site_wall (negative off the walls).
 template <class ST, int N, typename S, bool DEV, bool RELAX, bool EXT = false>
-__device__ __forceinline__ Macro<ST::D> collide_site(const Tables *__restrict__ tb, S (&f)[ST::Q], double tau,
+__device__ __forceinline__ Macro<ST::D> collide_site(CTables *tb, S (&f)[ST::Q], double tau,
                                                      double wallT = -1.0) {
   if constexpr (ST::ONLAT)
     return collide_massive<ST, N, S, DEV, RELAX, EXT>(tb, f, tau, wallT);
@@ -142,102 +142,59 @@ __device__ __forceinline__ Macro<ST::D> collide_site(const Tables *__restrict__ 
     return collide_prod<ST, N, S, DEV, RELAX, EXT>(tb, f, tau, wallT);
 }
 
-// post-collision populations of the site, rounded to the storage type
-template <class ST, typename S, bool NT = false, typename A = S>
-__device__ __forceinline__ void store_site(S *__restrict__ fout, int64_t sites, uint32_t site_off,
-                                           const A (&f)[ST::Q]) {
-#pragma unroll
-  for (int i = 0; i < ST::Q; ++i) put_pop<NT>(fout, sites, site_off, i, (S)f[i]);
+// Site of this thread.
+__device__ __forceinline__ bool site_coords(CTables *tb, const Tiling &tl, int &x, int &y) {
+  int x0, y0;
+  tile_origin(tl, x0, y0);
+  x = x0 + threadIdx.x;
+  y = y0 + threadIdx.y;
+  return x < tb->nx && y < tb->ny;
 }
 
-// Site of this thread.  Blocks form a 1D grid over tiles of tl.bx x tl.by x
-// tl.bz sites.  The hardware deals consecutive blocks
-// round-robin to the 8 XCDs, each with its own L2.  Tile orders:
-//   xcd == 0: x fastest, then y, then z, as dealt;
-//   xcd == 1: each XCD receives a contiguous range of that order (a band of
-//             neighbouring rows whose halo rows stay in its L2);
-//   xcd == 2: (3D) the rows are grouped in patches of kPatch x kPatch rows in
-//             (y, z); XCD k takes patches k, k + 8, ... and walks each patch
-//             with x fastest, so the blocks in flight on an XCD cover one
-//             compact patch and read each other's y and z halo rows while
-//             they are still in its L2.  The grid then has 8 * ceil(patches /
-//             8) * tiles-per-patch blocks; those past the lattice return.
-constexpr int kPatch = 8;
-
-// The launch shape as kernel arguments (scalar registers): blockDim and gridDim would be read from
-// the dispatch packet by vector loads that every wave waits for before its first tap load.
-struct Tiling {
-  int bx, by, bz;   // block shape
-  int nb;           // blocks in the grid
-  int order;        // tile order (0, 1, 2 as above)
-};
-
-// tile of block t when each XCD takes a contiguous band of the nb tiles
-__device__ __forceinline__ uint32_t band_tile(uint32_t t, uint32_t nb) {
-  const uint32_t q = nb / 8, r = nb % 8, k = t % 8, l = t / 8;
-  return k * q + (k < r ? k : r) + l;
-}
-
-__device__ __forceinline__ bool site_coords(const Tables *__restrict__ tb, const Tiling &tl, int &x, int &y, int &z) {
-  const uint32_t bx = tl.bx, by = tl.by, bz = tl.bz;
-  const uint32_t gx = (tb->nx + bx - 1) / bx;
-  const uint32_t gy = (tb->ny + by - 1) / by;
-  const uint32_t nb = tl.nb;
-  const int xcd = tl.order;
-  uint32_t t = blockIdx.x;
-  uint32_t tx, ty, tz;
-  if (xcd == 2) {
-    const uint32_t py = max(1u, kPatch / by), pz = max(1u, kPatch / bz);   // tile rows per patch
-    const uint32_t npy = (gy + py - 1) / py;
-    const uint32_t per = gx * py * pz;                                     // tiles per patch
-    const uint32_t k = t % 8, l = t / 8;
-    const uint32_t p = (l / per) * 8 + k, w = l % per;
-    tx = w % gx;
-    ty = (p % npy) * py + (w / gx) % py;
-    tz = (p / npy) * pz + w / (gx * py);
-  } else {
-    if (xcd) t = band_tile(t, nb);
-    tx = t % gx;
-    ty = (t / gx) % gy;
-    tz = t / (gx * gy);
-  }
-  x = tx * bx + threadIdx.x;
-  y = ty * by + threadIdx.y;
-  z = tz * bz + threadIdx.z;
-  return x < tb->nx && y < tb->ny && z < tb->nz;
-}
-
+// The register kernel: one site per thread, all taps asked for at once.  Where the two states fit the Infinity Cache
+// it is bound by the vector instructions a SIMD's waves issue (4 clocks each; order 3 in float 1240 a wave, 8 of 17 us
+// at 512 x 512), by the taps' latency before them and by the launch, not by memory.  A fifth of those instructions
+// used to move scalars that did not fit the scalar registers (all planes' addresses and all tables at once) and to
+// form quotients for the tile's place: see one_after_another, from_here_on and tile_origin.  Per step, before ->
+// after: float 512 x 512 19.2 -> 17.1 us, 1024 x 1024 59 -> 53; float with double arithmetic 512 x 512 24.3 -> 19.8;
+// double 64 x 64 7.5 -> 5.7, 300 x 301 13.9 -> 12.4, walls and force 515 x 1021 67 -> 59; massive order 3 512 x 512
+// 39 -> 35 (a copy of its bytes takes 36); massless order 3 512 x 512 38 -> 34.
 template <class ST, int N, typename S, bool DEV, int OCC, bool EXT, bool NT, typename A = S>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 1, 8))) k_step(const Tables *__restrict__ tb, const S *__restrict__ fin,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 1, 8))) k_step(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                               S *__restrict__ fout, const void *__restrict__ tau_field,
                                               FieldPtrs last, int *err, Tiling tl) {
-  int x, y, z;
-  if (!site_coords(tb, tl, x, y, z)) return;
+  CTables *tb = (CTables *)tabs;
+  int x, y;
+  if (!site_coords(tb, tl, x, y)) return;
   const int64_t sites = tb->sites;
-  const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
+  const int64_t site = (int64_t)y * tb->nx + x;
+  // asked for with the populations: without a field a place in the state instead, unused (a load under a condition
+  // would be waited for at once, with all the others)
+  const S tau1 = (tau_field != nullptr ? (const S *)tau_field : fin)[site];
   A f[ST::Q];
-  gather<ST, S, A>(tb, fin, sites, x, y, z, f);
-  const double tau = site_tau<S>(tb, tau_field, site);
-  const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, z) : -1.0);
+  gather<ST, S, A>(tb, fin, sites, x, y, f);
+  const double tau = tau_field != nullptr ? (double)tau1 : tb->tau;
+  const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
   if (!mac.ok) flag_error(err);
-  store_site<ST, S, NT, A>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
+  put_pops<NT>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (last.any) write_fields<ST::D>(last, site, sites, mac);
 }
 
 // One 64 x 4 tile per block in the band order, its populations pulled through LDS (stage2d.h).  Bound by
 // HBM where the two states do not fit the Infinity Cache: the register kernels fetch every row of a
 // window once per wave that reads it, which there costs memory traffic and lines in flight.  Per step,
-// order 3: 105 us at 1024 x 1024 in double (5.1 TB/s of what a step has to move; register kernel 121,
-// windows of 5 full rows in 16-byte chunks 106), 113 with walls and a force (register 124), 119 at
-// 1023 x 1025 (130), 369 at 2048 x 2048 (windows of full rows 382); order 2 at 1025 x 1023 86 (107).
+// order 3: 103 us at 1024 x 1024 in double (5.2 TB/s of what a step has to move, a copy's rate; register
+// kernel 121, windows of 5 full rows in 16-byte chunks 107), 60 with walls and a force at 700 x 801
+// (register 76), 119 at 1023 x 1025 (130), 373 at 2048 x 2048 (windows of full rows 394); order 2 at
+// 1025 x 1023 86 (107).
 template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, typename A = S>
-__global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tb, const S *__restrict__ fin,
+__global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                                   S *__restrict__ fout, const void *__restrict__ tau_field,
                                                   FieldPtrs last, int *err, Tiling tl) {
+  CTables *tb = (CTables *)tabs;
   __shared__ S buf[2 * Stage2D<ST, S>::E];
-  const uint32_t gx = (tb->nx + 63) / 64;
-  const uint32_t t = band_tile(blockIdx.x, tl.nb);
-  const int x0 = (int)(t % gx) * 64, y0 = (int)(t / gx) * 4;
+  int x0, y0;
+  tile_origin(tl, x0, y0);
   const int x = x0 + threadIdx.x, y = y0 + threadIdx.y;
   const int64_t sites = tb->sites;
   A f[ST::Q];
@@ -247,19 +204,20 @@ __global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tb,
   const double tau = site_tau<S>(tb, tau_field, site);
   const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
   if (!mac.ok) flag_error(err);
-  store_site<ST, S, NT, A>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
+  put_pops<NT>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (last.any) write_fields<ST::D>(last, site, sites, mac);
 }
 
 template <class ST, int N, typename S, bool DEV, typename A = S>
-__global__ void __launch_bounds__(256) k_moments(const Tables *__restrict__ tb, const S *__restrict__ fin,
+__global__ void __launch_bounds__(256) k_moments(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                                  FieldPtrs out, int *err, Tiling tl) {
-  int x, y, z;
-  if (!site_coords(tb, tl, x, y, z)) return;
+  CTables *tb = (CTables *)tabs;
+  int x, y;
+  if (!site_coords(tb, tl, x, y)) return;
   const int64_t sites = tb->sites;
-  const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
+  const int64_t site = (int64_t)y * tb->nx + x;
   A f[ST::Q];
-  gather<ST, S, A>(tb, fin, sites, x, y, z, f);
+  gather<ST, S, A>(tb, fin, sites, x, y, f);
   const Macro<ST::D> mac = collide_site<ST, N, A, DEV, false>(tb, f, 1.0);
   if (!mac.ok) flag_error(err);
   write_fields<ST::D>(out, site, sites, mac);
@@ -267,17 +225,18 @@ __global__ void __launch_bounds__(256) k_moments(const Tables *__restrict__ tb, 
 
 // f(x, 0) = f^eq(n0, T0, U(u0)) (1 + amp xi), then collide; store f*(x, 0).
 template <class ST, int N, typename S, bool DEV, typename A = S>
-__global__ void __launch_bounds__(256) k_init(const Tables *__restrict__ tb, const double *__restrict__ n0,
+__global__ void __launch_bounds__(256) k_init(const Tables *__restrict__ tabs, const double *__restrict__ n0,
                                               const double *__restrict__ T0, const double *__restrict__ u0,
                                               const double *__restrict__ noise, double amp, S *__restrict__ fout,
                                               const void *__restrict__ tau_field, FieldPtrs fields0, int *err,
                                               Tiling tl) {
+  CTables *tb = (CTables *)tabs;
   constexpr int D = ST::D, Q = ST::Q, NP = Q / 2;
   using B = BasisDef<D, N>;
-  int x, y, z;
-  if (!site_coords(tb, tl, x, y, z)) return;
+  int x, y;
+  if (!site_coords(tb, tl, x, y)) return;
   const int64_t sites = tb->sites;
-  const int64_t site = ((int64_t)z * tb->ny + y) * tb->nx + x;
+  const int64_t site = (int64_t)y * tb->nx + x;
   double U[D + 1], uu = 0.0;
 #pragma unroll
   for (int a = 0; a < D; ++a) {
@@ -321,9 +280,9 @@ __global__ void __launch_bounds__(256) k_init(const Tables *__restrict__ tb, con
 #pragma unroll
   for (int i = 0; i < Q; ++i) f[i] = DEV ? (A)(fd[i] - tb->fref[i]) : (A)fd[i];
   const double tau = site_tau<S>(tb, tau_field, site);
-  const Macro<D> mac = collide_site<ST, N, A, DEV, true, true>(tb, f, tau, site_wall(tb, x, y, z));
+  const Macro<D> mac = collide_site<ST, N, A, DEV, true, true>(tb, f, tau, site_wall(tb, x, y, 0));
   if (!mac.ok) flag_error(err);
-  store_site<ST, S, false, A>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
+  put_pops<false>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (fields0.any) write_fields<D>(fields0, site, sites, mac);
 }
 
@@ -333,18 +292,8 @@ __global__ void __launch_bounds__(256) k_init(const Tables *__restrict__ tb, con
 template <class ST, int N, typename S, bool DEV, typename A = S>
 static hipError_t launch_t(const LaunchArgs &a) {
   const Variant vr = kVariants[(a.op == OP_STEP && a.variant >= 0 && a.variant < kNumVariants) ? a.variant : 0];
-  const int by = ST::D == 2 ? vr.by * vr.bz : vr.by, bz = ST::D == 2 ? 1 : vr.bz;
-  dim3 block(vr.bx, by, bz);
-  const long gx = (a.nx + vr.bx - 1) / vr.bx, gy = (a.ny + by - 1) / by, gz = (a.nz + bz - 1) / bz;
-  const int order = (ST::D == 2 && vr.xcd == 2) ? 1 : vr.xcd;
-  long nb = gx * gy * gz;
-  if (order == 2) {
-    const long py = std::max(1, kPatch / by), pz = std::max(1, kPatch / bz);
-    const long npatch = ((gy + py - 1) / py) * ((gz + pz - 1) / pz);
-    nb = 8 * ((npatch + 7) / 8) * gx * py * pz;
-  }
-  dim3 grid((unsigned)nb, 1, 1);
-  const Tiling tl{vr.bx, by, bz, (int)nb, order};
+  const Tiling tl = tiling(a.nx, a.ny, vr.bx, vr.by * vr.bz, vr.xcd != 0);
+  const dim3 block(tl.bx, tl.by, 1), grid((unsigned)tl.nb, 1, 1);
   static_assert(ST::D == 2, "the 3D rules: split.hip, split_onlat.hip, split_ur3d.hip");
   switch (a.op) {
     case OP_STEP: {
@@ -363,11 +312,10 @@ static hipError_t launch_t(const LaunchArgs &a) {
       const bool ext = a.ext;
       if constexpr (!ST::ONLAT) {
         if (vr.lds || a.staged) {
-          const long ntile = ((a.nx + 63) / 64) * (long)((a.ny + 3) / 4);
-          const Tiling ltl{64, 4, 1, (int)ntile, 1};
+          const Tiling ltl = tiling(a.nx, a.ny, 64, 4, 1);
           auto lds = [&](auto ext, auto nt) {
             constexpr bool E = decltype(ext)::value, T = decltype(nt)::value;
-            hipLaunchKernelGGL((k_step_lds<ST, N, S, DEV, E, T, A>), dim3((unsigned)ntile, 1, 1), dim3(64, 4, 1), 0,
+            hipLaunchKernelGGL((k_step_lds<ST, N, S, DEV, E, T, A>), dim3((unsigned)ltl.nb, 1, 1), dim3(64, 4, 1), 0,
                                a.stream, a.tb, (const S *)a.fin, (S *)a.fout, a.tau_field, a.fields, a.err, ltl);
           };
           if (ext) {
