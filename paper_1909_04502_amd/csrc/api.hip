@@ -125,6 +125,7 @@ rlbm::LaunchArgs base_args(const rlbm_lattice *h, hipStream_t stream) {
   a.stream = stream;
   a.variant = h->variant;
   a.staged = h->variant == h->staged_variant;
+  a.open_x = h->cfg.bc[0] != RLBM_PERIODIC;
   a.ext = lattice_ext(h);
   a.nt = uses_nontemporal(h);
   return a;

@@ -89,7 +89,7 @@ __global__ void __launch_bounds__(256) k_step_batch_lds(const Tables *__restrict
   const int x0 = (d.y % gx) * 64, y0 = (d.y / gx) * 4;
   const int x = x0 + threadIdx.x, y = y0 + threadIdx.y;
   A f[ST::Q];
-  stage_pull<ST, S, A>(tb, fin + elem_off[d.x], sites, x0, y0, buf, f);
+  stage_pull<ST, S, A, false>(tb, fin + elem_off[d.x], sites, x0, y0, buf, f);
   if (x >= nx || y >= ny) return;
   const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
   if (!mac.ok) *err = 1;

@@ -43,6 +43,7 @@ struct LaunchArgs {
   double amp = 0.0;
   int *err = nullptr;               // device error flag
   int ext = 0;                      // the lattice has an external force or no-slip walls
+  int open_x = 0;                   // reads clamp at the edges of the x axis
   int staged = 0;                   // 2D product rules: the LDS-staged step kernel, whatever the variant
   int nt = 0;                       // step kernels store the populations non-temporally
   hipStream_t stream = 0;

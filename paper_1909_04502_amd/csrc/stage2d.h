@@ -5,7 +5,7 @@
 // only what its direction reads: the tile's 4 rows, a fifth row on the upstream side where n_y != 0, and
 // one column element per row on the upstream side where n_x != 0.  Rows are loaded 4 bytes per lane, so
 // that any row start and any x extent will do, and lanes address their columns one by one, so that
-// periodic and open axes wrap and clamp as in the register kernels.  Two buffers alternate: the loads of
+// periodic and open axes wrap and clamp as in the register kernels (or, WIDE, 16 bytes per lane: stage_wide).  Two buffers alternate: the loads of
 // shell j + 1 are in flight while the taps of shell j are read from LDS and summed; the block's four
 // waves share each window.  The taps, weights and summation order are those of pull_prod, so the
 // populations are the same values to the last bit.
@@ -32,12 +32,15 @@ struct Stage2D {
     return o + (side(k) ? kSide : 0);
   }
   static constexpr int E = body(7) + 64 * rows(7);   // elements of one buffer
-  static constexpr int loads(int w) {                // load instructions of wave w per shell
-    return H * (rows(w) + rows(w + 4)) + side(w) + side(w + 4);
-  }
-  static constexpr int min_loads() {
-    int m = loads(0);
-    for (int w = 1; w < 4; ++w) m = loads(w) < m ? loads(w) : m;
+  // 16 bytes per lane: lanes per row, rows per instruction
+  static constexpr int LPR = 64 * (int)sizeof(S) / 16, RPI = 64 / LPR;
+  static constexpr int row_loads(bool wide, int k) { return wide ? (rows(k) + RPI - 1) / RPI : H * rows(k); }
+  static constexpr int min_loads(bool wide) {        // load instructions of a wave per shell, the fewest
+    int m = 99;
+    for (int w = 0; w < 4; ++w) {
+      const int l = row_loads(wide, w) + row_loads(wide, w + 4) + side(w) + side(w + 4);
+      m = l < m ? l : m;
+    }
     return m;
   }
 };
@@ -52,19 +55,24 @@ __device__ __forceinline__ void wait_vm_lgkm() {
 }
 __device__ __forceinline__ void wait_lgkm() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (0x7 << 4)); }
 
-// One direct global-to-LDS load: each active lane l reads the 4 bytes at base + voff and writes
-// them to LDS at byte lds + 4 l (base and lds wave-uniform; m0 holds the LDS address, and one
+// One direct global-to-LDS load: each active lane l reads the 4 (16) bytes at base + voff and writes
+// them to LDS at byte lds + 4 l (16 l) (base and lds wave-uniform; m0 holds the LDS address, and one
 // wait state separates its write from the load).  Written as asm so that the compiler does not
 // track these loads: it would make every LDS read of the kernel wait for all of them.  The kernel
 // waits for them itself (wait_vm_lgkm); they have no register results.
-__device__ __forceinline__ void stage_load4(const char *base, uint32_t voff, uint32_t lds) {
+template <bool WIDE>
+__device__ __forceinline__ void stage_load(const char *base, uint32_t voff, uint32_t lds) {
   // both uniform operands pass through readfirstlane: the compiler may otherwise hold a uniform
   // value it cannot prove uniform in a vector register, which an "s" operand does not accept
   const uint64_t b = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)base >> 32)) << 32) |
                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)base);
   const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, %0" : : "s"(b), "v"(voff), "s"(m)
-               : "memory", "m0");
+  if constexpr (WIDE)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" : : "s"(b), "v"(voff), "s"(m)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, %0" : : "s"(b), "v"(voff), "s"(m)
+                 : "memory", "m0");
 }
 
 __device__ __forceinline__ int stage_wrap(int v, int n, int open) {
@@ -76,13 +84,15 @@ __device__ __forceinline__ int stage_wrap(int v, int n, int open) {
 // What a wave loads of every shell: planes w and w + 4, from which rows and columns.  Rows and columns
 // past the one upstream of the lattice's edge belong to no site; they repeat that one, so every address
 // lies inside the plane.
-template <class ST, typename S>
+template <class ST, typename S, bool WIDE>
 struct StagePlan {
   using L = Stage2D<ST, S>;
   int w;                  // wave of the block (uniform)
   int plane[2], nrow[2];  // uniform
   bool side[2];           // uniform
-  int64_t row[2][5];      // byte offsets of the window rows (uniform)
+  int64_t row[2][5];      // byte offsets of the window rows (uniform; 4 bytes per lane)
+  uint32_t wide[2][3];    // byte offset of this lane's 16 bytes in the plane, for each of the rows' instructions
+  bool wlane[2][3];       // and whether they belong to a window row
   uint32_t lds[2];        // LDS byte offset of the window's first row in a buffer (uniform)
   uint32_t col[L::H];     // byte offset of this lane's 4 bytes in a row
   uint32_t scol[2];       // and in the plane, of this lane's part of the side column
@@ -114,6 +124,13 @@ struct StagePlan {
 #pragma unroll
       for (int r = 0; r < 5; ++r)
         row[e][r] = (int64_t)stage_wrap(min(yf + r, ny), ny, openy) * nx * (int64_t)sizeof(S);
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        const int r = n * L::RPI + lane / L::LPR, c = lane % L::LPR * (16 / (int)sizeof(S));
+        wide[e][n] = ((uint32_t)stage_wrap(min(yf + r, ny), ny, openy) * (uint32_t)nx +
+                      (uint32_t)stage_wrap(min(x0 + c, nx), nx, openx)) * (uint32_t)sizeof(S);
+        wlane[e][n] = r < nrow[e];
+      }
       const int r = lane / L::H;      // the row of this lane's part of the side column
       const int ys = stage_wrap(min(yf + r, ny), ny, openy), xs = stage_wrap(min(dx > 0 ? x0 - 1 : x0 + 64, nx), nx, openx);
       scol[e] = ((uint32_t)ys * (uint32_t)nx + (uint32_t)xs) * (uint32_t)sizeof(S) + (lane % L::H) * 4u;
@@ -126,14 +143,20 @@ struct StagePlan {
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const char *p = (const char *)(fin + (int64_t)(shell * ST::NDIR + plane[e]) * sites);
+      if constexpr (WIDE) {
 #pragma unroll
-      for (int r = 0; r < 5; ++r) {
-        if (r == 4 && nrow[e] == 4) break;
+        for (int n = 0; n * L::RPI < 5; ++n)
+          if (wlane[e][n]) stage_load<true>(p, wide[e][n], buf + lds[e] + (uint32_t)(n * 1024));
+      } else {
 #pragma unroll
-        for (int h = 0; h < L::H; ++h)
-          stage_load4(p + row[e][r], col[h], buf + lds[e] + (uint32_t)(r * 64 * (int)sizeof(S) + h * 256));
+        for (int r = 0; r < 5; ++r) {
+          if (r == 4 && nrow[e] == 4) break;
+#pragma unroll
+          for (int h = 0; h < L::H; ++h)
+            stage_load<false>(p + row[e][r], col[h], buf + lds[e] + (uint32_t)(r * 64 * (int)sizeof(S) + h * 256));
+        }
       }
-      if (side[e] && slane[e]) stage_load4(p, scol[e], buf + lds[e] - (uint32_t)(L::kSide * (int)sizeof(S)));
+      if (side[e] && slane[e]) stage_load<false>(p, scol[e], buf + lds[e] - (uint32_t)(L::kSide * (int)sizeof(S)));
     }
   }
 };
@@ -285,7 +308,7 @@ __device__ __forceinline__ void pull_ahead(CTables *tb, const S *fin, int64_t si
 // tile.  Called by all threads of the block, also those of sites past the lattice's edge: they take part
 // in the loads and barriers, and their populations are not those of a site.  No vector memory access of
 // the caller may be in flight.
-template <class ST, typename S, typename A>
+template <class ST, typename S, typename A, bool WIDE>
 __device__ __forceinline__ void stage_pull(CTables *tb, const S *__restrict__ fin, int64_t sites, int x0,
                                            int y0, S *buf, A (&f)[ST::Q]) {
   using L = Stage2D<ST, S>;
@@ -293,7 +316,7 @@ __device__ __forceinline__ void stage_pull(CTables *tb, const S *__restrict__ fi
   static_assert(KR >= 2, "two shells in flight");
   typedef __attribute__((address_space(3))) S lds_t;
   const uint32_t lds = (uint32_t)(uintptr_t)(lds_t *)buf;   // LDS byte address of the buffers
-  const StagePlan<ST, S> plan(tb, x0, y0);
+  const StagePlan<ST, S, WIDE> plan(tb, x0, y0);
   plan.load(fin, sites, 0, lds);
   plan.load(fin, sites, 1, lds + L::E * (int)sizeof(S));
   const StageAt at(L::kSide);
@@ -302,7 +325,7 @@ __device__ __forceinline__ void stage_pull(CTables *tb, const S *__restrict__ fi
     // shell j has landed in this wave's part of its buffer once at most the loads of shell j + 1
     // are in flight (no other vector memory access is issued before the last shell; the fewest that a
     // wave of the block has of a shell); the barrier extends that to the whole block
-    if (j + 1 < KR) wait_vm_lgkm<L::min_loads()>();
+    if (j + 1 < KR) wait_vm_lgkm<L::min_loads(WIDE)>();
     else wait_vm_lgkm<0>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -328,6 +351,15 @@ __device__ __forceinline__ void stage_pull(CTables *tb, const S *__restrict__ fi
       f[j * ST::NDIR + k] = fs[k];
     }
   }
+}
+
+// Rows may be loaded 16 bytes per lane: every row of every plane starts on 16 bytes and every chunk of 16 lies inside
+// the lattice or past its edge as a whole (an open x axis repeats its last site, so no chunk may lie past it).
+// Taken in double storage without walls and force, where a wave then issues 7 loads a shell instead of 20 (even in
+// time: 371.5 against 372.3 us at 2048 x 2048, 103.3 against 102.9 at 1024 x 1024); in float storage and with walls
+// the 4-byte loads are ahead (float 2048 x 2048 210 against 211.6 us, walls at 1024 x 1024 106.7 against 107.5).
+inline bool stage_wide(const void *fin, int nx, int elem, bool openx) {
+  return (uintptr_t)fin % 16 == 0 && nx * elem % 16 == 0 && (!openx || nx % 64 == 0);
 }
 
 }  // namespace rlbm

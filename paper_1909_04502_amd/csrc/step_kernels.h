@@ -187,18 +187,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 
 // kernel 121, windows of 5 full rows in 16-byte chunks 107), 60 with walls and a force at 700 x 801
 // (register 76), 119 at 1023 x 1025 (130), 373 at 2048 x 2048 (windows of full rows 394); order 2 at
 // 1025 x 1023 86 (107).
-template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, typename A = S>
+template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, bool WIDE, typename A = S>
 __global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                                   S *__restrict__ fout, const void *__restrict__ tau_field,
                                                   FieldPtrs last, int *err, Tiling tl) {
   CTables *tb = (CTables *)tabs;
-  __shared__ S buf[2 * Stage2D<ST, S>::E];
+  __shared__ __attribute__((aligned(16))) S buf[2 * Stage2D<ST, S>::E];
   int x0, y0;
   tile_origin(tl, x0, y0);
   const int x = x0 + threadIdx.x, y = y0 + threadIdx.y;
   const int64_t sites = tb->sites;
   A f[ST::Q];
-  stage_pull<ST, S, A>(tb, fin, sites, x0, y0, buf, f);
+  stage_pull<ST, S, A, WIDE>(tb, fin, sites, x0, y0, buf, f);
   if (x >= tb->nx || y >= tb->ny) return;
   const int64_t site = (int64_t)y * tb->nx + x;
   const double tau = site_tau<S>(tb, tau_field, site);
@@ -313,10 +313,15 @@ static hipError_t launch_t(const LaunchArgs &a) {
       if constexpr (!ST::ONLAT) {
         if (vr.lds || a.staged) {
           const Tiling ltl = tiling(a.nx, a.ny, 64, 4, 1);
-          auto lds = [&](auto ext, auto nt) {
-            constexpr bool E = decltype(ext)::value, T = decltype(nt)::value;
-            hipLaunchKernelGGL((k_step_lds<ST, N, S, DEV, E, T, A>), dim3((unsigned)ltl.nb, 1, 1), dim3(64, 4, 1), 0,
+          auto launch_lds = [&](auto ext, auto nt, auto wd) {
+            constexpr bool E = decltype(ext)::value, T = decltype(nt)::value, W = decltype(wd)::value;
+            hipLaunchKernelGGL((k_step_lds<ST, N, S, DEV, E, T, W, A>), dim3((unsigned)ltl.nb, 1, 1), dim3(64, 4, 1), 0,
                                a.stream, a.tb, (const S *)a.fin, (S *)a.fout, a.tau_field, a.fields, a.err, ltl);
+          };
+          auto lds = [&](auto ext, auto nt) {
+            if constexpr (sizeof(S) == 8 && !decltype(ext)::value)
+              if (stage_wide(a.fin, a.nx, (int)sizeof(S), a.open_x)) return launch_lds(ext, nt, T{});
+            launch_lds(ext, nt, F{});
           };
           if (ext) {
             if (a.nt) lds(T{}, T{});
