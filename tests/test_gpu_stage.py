@@ -20,6 +20,9 @@ PP = ("periodic", "periodic")
     (3, "f64", (1, 1), PP, None),
     (3, "f64", (63, 3), PP, None),
     (2, "f64", (65, 5), ("open", "open"), None),
+    (3, "f64", (128, 6), ("open", "periodic"), None),   # 16 bytes per lane: whole tiles; a row of one chunk
+    (2, "f64", (2, 3), PP, None),
+    (3, "f64", (66, 5), ("open", "periodic"), None),
     (3, "f64", (129, 9), ("wall", "periodic"), (0.0, 3e-4)),
     (3, "f32dev", (61, 4), ("periodic", "wall"), (2e-4, 0.0)),
     (2, "f32dev", (127, 6), ("open", "periodic"), None),
