@@ -18,6 +18,7 @@
 // the Jacobi matrix of the weight's orthogonal polynomials are the nodes.
 #include "precompute.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -392,17 +393,16 @@ static void pack_linv(Tables &t) {
       for (int j = 0; j <= i; ++j) t.LinvP[CL.off[c] + i * (i + 1) / 2 + j] = t.Linv[CL.idx[c][i]][CL.idx[c][j]];
 }
 
-// Chebyshev coefficients of f on [-1, 1] (n terms, long double nodes).
-// the k-th of kFitNodes Chebyshev nodes, and the first kEosTerms coefficients of the series through values at
-// all of them (more nodes than terms: the values' own rounding averages out)
+// the k-th of kFitNodes Chebyshev nodes, and the coefficients of the series through values at all of them
 constexpr int kFitNodes = 44;
+static_assert(kFitNodes >= kEosTerms, "the kernels evaluate the first terms of the series");
 static ld cheb_node(int k) {
   const ld pi = 3.141592653589793238462643383279502884L;
   return cosl(pi * (k + 0.5L) / kFitNodes);
 }
 static void cheb_coefficients(const ld *fk, double *coef) {
   const ld pi = 3.141592653589793238462643383279502884L;
-  for (int j = 0; j < kEosTerms; ++j) {
+  for (int j = 0; j < kFitNodes; ++j) {
     ld c = 0.0L;
     for (int k = 0; k < kFitNodes; ++k) c += fk[k] * cosl(pi * j * (k + 0.5L) / kFitNodes);
     c *= 2.0L / kFitNodes;
@@ -434,11 +434,12 @@ static int cheb_piece(ld u, ld &s) {
 }
 static ld cheb_global(int p, ld s) { return ((s + 1.0L) * 0.5L + p) * (2.0L / kEosPieces) - 1.0L; }
 
-// `stride`: doubles from a piece's series to the next piece's
-static ld cheb_eval_pieces(const double *coef, int stride, int n, ld u) {
+// one series per piece, and its first n terms at u
+typedef double Series[kEosPieces][kFitNodes];
+static ld cheb_eval_pieces(const Series &coef, int n, ld u) {
   ld s;
   const int p = cheb_piece(u, s);
-  return cheb_eval(coef + p * stride, n, s);
+  return cheb_eval(coef[p], n, s);
 }
 
 // e - m = m (r(m/T) - 1) + 3 T for d = 3 (e = eps/n = T (G_3 - 1), G_3 = z r + 4), with r from
@@ -449,23 +450,23 @@ static ld kinetic_exact(ld m, ld T, ld &dk) {
   return m * (r - 1.0L) + 3.0L * T;
 }
 
-// r(z) = K1/K2 from the fitted series (what the kernels evaluate), and the kinetic energy from it
-static ld r_fitted(const Tables &t, ld z) {
+// r(z) = K1/K2 from the fitted series h on the range of t
+static ld r_fitted(const Tables &t, const Series &h, ld z) {
   const ld u = (2.0L * logl(z) - ((ld)t.cheb_lo + (ld)t.cheb_hi)) / ((ld)t.cheb_hi - (ld)t.cheb_lo);
-  return cheb_eval_pieces(t.cheb[0], kEosTerms, t.cheb_n, u) * z / (z + 2.0L);
+  return cheb_eval_pieces(h, kFitNodes, u) * z / (z + 2.0L);
 }
 
 // the temperature of kinetic energy d per particle.  kinetic(T) increases in T from 1.5 T (cold)
 // to 3 T (hot), so the root lies in [d/3, d/1.5]: bisection on the kinetic energy of the fitted r
 // (cheap, and good to about 1e-12 where the cold cancellation magnifies the fit's rounding), then
 // safeguarded Newton steps on the exact kinetic energy
-static ld temperature_exact(const Tables &t, ld m, ld d) {
+static ld temperature_exact(const Tables &t, const Series &h, ld m, ld d) {
   ld lo = d / 3.05L, hi = d / 1.45L;
   {
     ld a = fmaxl(lo, (ld)kEosTmin), b = fminl(hi, (ld)kEosTmax);
     for (int it = 0; it < 200 && b - a > 1e-18L * b; ++it) {
       const ld mid = 0.5L * (a + b);
-      if (m * (r_fitted(t, m / mid) - 1.0L) + 3.0L * mid < d) a = mid;
+      if (m * (r_fitted(t, h, m / mid) - 1.0L) + 3.0L * mid < d) a = mid;
       else b = mid;
     }
     lo = fmaxl(lo, 0.5L * (a + b) * (1.0L - 1e-6L));
@@ -498,17 +499,23 @@ int build_eos_fit(double m, Tables &t, std::string &err) {
     const ld z = expl(0.5L * (hi + lo) + 0.5L * (hi - lo) * u);
     return bessel_k(1.0L, z) / bessel_k(2.0L, z) * (z + 2.0L) / z;
   };
+  // A mass is taken where the series of all kFitNodes terms holds the bounds below, whatever the terms that the
+  // kernels evaluate: from masses of about 28 on the rounding of the temperatures that the inverse is fitted to
+  // (they cancel to 1e-15 in long double) decides, and would decide otherwise for another number of terms.
+  Series hs, ts;
   for (int p = 0; p < kEosPieces; ++p) {
     ld h[kFitNodes];
     for (int k = 0; k < kFitNodes; ++k) h[k] = hfun(cheb_global(p, cheb_node(k)));
-    cheb_coefficients(h, t.cheb[p]);
+    cheb_coefficients(h, hs[p]);
+    std::copy(hs[p], hs[p] + n, t.cheb[p]);
   }
   t.cheb_n = n;
   t.cheb_lo = (double)lo;
   t.cheb_hi = (double)hi;
   for (int k = 0; k <= 64 * kEosPieces; ++k) {
     const ld u = -1.0L + 2.0L * k / (64.0L * kEosPieces), ref = hfun(u);
-    if (fabsl(cheb_eval_pieces(t.cheb[0], kEosTerms, n, u) - ref) > 5e-16L * fabsl(ref)) {
+    if (fabsl(cheb_eval_pieces(hs, kFitNodes, u) - ref) > 5e-16L * fabsl(ref) ||
+        fabsl(cheb_eval_pieces(hs, n, u) - ref) > 5e-16L * fabsl(ref)) {
       err = "equation-of-state fit failed";
       return RLBM_ERR_QUADRATURE;
     }
@@ -520,26 +527,31 @@ int build_eos_fit(double m, Tables &t, std::string &err) {
   const ld xlo = logl(kinetic_exact(m, tmin, dk)), xhi = logl(kinetic_exact(m, tmax, dk));
   // T/(e - m) and h(m/T) at the variable u of the whole range
   auto state = [&](ld u, ld &tq, ld &h) {
-    const ld d = expl(0.5L * (xhi + xlo) + 0.5L * (xhi - xlo) * u), T = temperature_exact(t, m, d), z = m / T;
+    const ld d = expl(0.5L * (xhi + xlo) + 0.5L * (xhi - xlo) * u), T = temperature_exact(t, hs, m, d), z = m / T;
     tq = T / d;
     h = bessel_k(1.0L, z) / bessel_k(2.0L, z) * (z + 2.0L) / z;
   };
   for (int p = 0; p < kEosPieces; ++p) {
     ld tq[kFitNodes], h[kFitNodes];
+    double full[kFitNodes];
     for (int k = 0; k < kFitNodes; ++k) state(cheb_global(p, cheb_node(k)), tq[k], h[k]);
-    cheb_coefficients(tq, t.chebT[p][0]);
-    cheb_coefficients(h, t.chebT[p][1]);
+    cheb_coefficients(tq, ts[p]);
+    std::copy(ts[p], ts[p] + n, t.chebT[p][0]);
+    cheb_coefficients(h, full);
+    std::copy(full, full + n, t.chebT[p][1]);
   }
   t.chebT_n = n;
   t.chebT_lo = (double)xlo;
   t.chebT_hi = (double)xhi;
   for (int k = 0; k <= 64 * kEosPieces; ++k) {
     const ld u = -1.0L + 2.0L * k / (64.0L * kEosPieces);
-    ld tq, h;
+    ld tq, h, s;
     state(u, tq, h);
-    const int st = 2 * kEosTerms;
-    if (fabsl(cheb_eval_pieces(t.chebT[0][0], st, n, u) - tq) > 1e-15L * fabsl(tq) ||
-        fabsl(cheb_eval_pieces(t.chebT[0][1], st, n, u) - h) > 5e-16L * fabsl(h)) {
+    const int p = cheb_piece(u, s);
+    // (the first terms: to the bound and the rounding of the temperatures, so that only a series cut too short fails)
+    if (fabsl(cheb_eval_pieces(ts, kFitNodes, u) - tq) > 1e-15L * fabsl(tq) ||
+        fabsl(cheb_eval(t.chebT[p][0], n, s) - tq) > 4e-15L * fabsl(tq) ||
+        fabsl(cheb_eval(t.chebT[p][1], n, s) - h) > 5e-16L * fabsl(h)) {
       err = "inverse equation-of-state fit failed";
       return RLBM_ERR_QUADRATURE;
     }

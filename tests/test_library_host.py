@@ -228,6 +228,25 @@ def test_create_validates_massive_lattices(rlbm_lib):
     assert rlbm_lib.rlbm_create(ctypes.byref(ur), ctypes.byref(h)) == R.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("zeta,taken", [(10.0, True), (26.0, True), (27.0, True), (29.5, True), (30.5, True),
+                                        (34.5, True), (39.75, True), (20.5, False), (28.5, False), (32.75, False),
+                                        (35.0, False), (36.5, False)])
+def test_create_takes_the_masses_whose_full_series_hold(rlbm_lib, zeta, taken):
+    """From masses of about 20 on, the rounding of the temperatures that the 3D equation of state is fitted to
+    decides whether the series of 44 terms holds its bound; the kernels evaluate its first 24, which does not
+    move the line between the masses that are taken and those that are refused."""
+    from paper_1909_04502_amd import rlbm as R
+    cfg = R.Config()
+    cfg.model = R.Model(d=3, order=2, kind=R.KIND["product"], pad_=0, zeta=zeta, v0=0.0)
+    cfg.extent[0], cfg.extent[1], cfg.extent[2] = 8, 8, 8
+    cfg.tau = 0.8
+    h = ctypes.c_void_p()
+    status = rlbm_lib.rlbm_create(ctypes.byref(cfg), ctypes.byref(h))   # without a GPU: ERR_DEVICE, after the fits
+    if status == R.OK:
+        rlbm_lib.rlbm_destroy(h)
+    assert status in ((R.OK, R.ERR_DEVICE) if taken else (R.ERR_QUADRATURE,))
+
+
 def test_lds_loads_take_uniform_operands(rlbm_lib, tmp_path):
     """The LDS-staged step loads its windows with inline-assembly global-to-LDS loads: each sets m0
     (the LDS address) from a scalar register, waits one state, and loads with a scalar address pair
