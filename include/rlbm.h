@@ -340,9 +340,14 @@ rlbm_status rlbm_batch_autotune(rlbm_batch *b, void *f_a, void *f_b, int32_t ste
 /* ------------------------------------------------------- launch variants */
 
 /* The step kernel has rlbm_variant_count() launch variants (block shape,
- * register / occupancy target, XCD-aware tile order, and for the 2D product
- * rules on a periodic x axis whose extent is a multiple of 4, upstream windows
- * staged in LDS); results do not depend on the variant.  rlbm_autotune times every variant for `steps` steps on
+ * register / occupancy target, XCD-aware tile order, and, number 12, for the 2D
+ * product rules upstream windows staged in LDS); results do not depend on the
+ * variant.  A number that is set, or chosen by rlbm_autotune, starts its own
+ * kernel on every lattice.  Until then a lattice runs its default, which for the
+ * 2D product rules is number 12 once the two state buffers exceed 256 MiB.  rlbm_get_variant answers the
+ * number that was set or chosen, or the default's; where the default is number 12
+ * and extent[0] is not a multiple of 4 it answers the number of the register kernel
+ * that smaller lattices take.  rlbm_autotune times every variant for `steps` steps on
  * scratch buffers of the lattice's size (allocated and freed inside the
  * call and holding a shear wave of amplitude 0.05 at T = 1 and a density
  * of 1 with site-to-site noise of 1e-3; the

@@ -18,8 +18,8 @@ struct rlbm_lattice {
   rlbm::Tables *d_tables = nullptr;
   int *d_err = nullptr;
   int stencil = 0;
-  int variant = 1;
-  int staged_variant = -1;   // the variant that stands for the staged step kernel besides its own
+  int variant = 1;      // what rlbm_get_variant answers
+  int step_variant = 1; // what rlbm_step launches: the same number, except for some defaults (prepare_lattice)
   int store_mode = RLBM_STORES_AUTO;
   int64_t sites = 0;
   std::string last_error;
@@ -123,8 +123,7 @@ rlbm::LaunchArgs base_args(const rlbm_lattice *h, hipStream_t stream) {
   a.tau_field = h->cfg.tau_field;
   a.err = h->d_err;
   a.stream = stream;
-  a.variant = h->variant;
-  a.staged = h->variant == h->staged_variant;
+  a.variant = h->step_variant;
   a.open_x = h->cfg.bc[0] != RLBM_PERIODIC;
   a.ext = lattice_ext(h);
   a.nt = uses_nontemporal(h);
@@ -279,18 +278,17 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
       if (cfg->bc[a] == RLBM_PERIODIC && std::fabs(h->quad.disp[i * m.d + a]) > (double)cfg->extent[a])
         return fail(RLBM_ERR_INVALID_ARG, "a periodic extent is shorter than the stencil's longest displacement");
   // 2D product rules whose two states outgrow the Infinity Cache take the LDS-staged kernel, at any x extent and
-  // boundary and in every storage (per step, register kernel -> staged; double 705 x 777 71 -> 61 us, 1023 x 1025
-  // 130 -> 119, walls and force 700 x 801 76 -> 69, order 2 901 x 803 66 -> 52; float storage 1100 x 1100 83 -> 76,
-  // 1501 x 1999 195 -> 171; with double arithmetic 1201 x 1101 99 -> 97, 1501 x 1999 202 -> 200).  Below that, where
-  // the halo re-reads hit that cache, the register kernels stay ahead (double 512 x 512 29 against 31 us, 700 x 700
-  // 47 against 53; float storage at 1024 x 1024 57 against 60).  Past the non-temporal store threshold the staged
-  // kernel's own variant number is the default where the x axis is periodic and its extent a multiple of 4; elsewhere
-  // the register kernel's number stands for it.
+  // boundary (per step, register kernel -> staged; double 725 x 725 65 -> 58 us, 1026 x 1026 134 -> 120, 2048 x 2048
+  // 494 -> 372, walls and force 515 x 1021 67 -> 59, open x 705 x 777 75 -> 58, order 2 901 x 803 74 -> 58; float
+  // storage 1100 x 1100 85 -> 76, 2048 x 2048 232 -> 210).  Below that, where the halo re-reads hit that cache, the
+  // register kernels stay ahead (double 700 x 700 47.5 against 49.2 us; float storage 1024 x 1024 54 against 57).
   const int64_t both = 2 * (cfg->storage == RLBM_F64 ? 8 : 4) * (int64_t)h->quad.Q * sites;
-  if (m.d == 2 && m.kind == RLBM_QUAD_PRODUCT && both > kStagedFootprint) {
-    if (cfg->bc[0] == RLBM_PERIODIC && cfg->extent[0] % 4 == 0 && both > kNontemporalFootprint) h->variant = 12;
-    h->staged_variant = h->variant;
-  }
+  const bool staged = m.d == 2 && m.kind == RLBM_QUAD_PRODUCT && both > kStagedFootprint;
+  const bool rows4 = cfg->extent[0] % 4 == 0;
+  // a default on rows of another length is answered with the number of its register kernel, as callers know it from
+  // the time when the staged windows did not cover such rows; a number that is set always starts its own kernel
+  h->step_variant = staged ? rlbm::kStagedVariant : h->variant;
+  if (rows4) h->variant = h->step_variant;
   int bc[3] = {cfg->bc[0], cfg->bc[1], cfg->bc[2]};
   rc = rlbm::build_tables(h->quad, cfg->tau, cfg->storage != RLBM_F64 ? cfg->n_ref : 1.0, cfg->storage,
                           cfg->extent, bc, *t, err);
@@ -421,7 +419,7 @@ rlbm_status rlbm_step(rlbm_lattice *h, void *f_a, void *f_b, int32_t nsteps, con
     hipError_t he = hipSuccess;
     rlbm_lattice::StepGraph *sg = nullptr;
     for (auto &g : h->graphs)
-      if (g.exec && g.fa == f_a && g.fb == f_b && g.n == nsteps && g.variant == h->variant &&
+      if (g.exec && g.fa == f_a && g.fb == f_b && g.n == nsteps && g.variant == h->step_variant &&
           g.nt == uses_nontemporal(h))
         sg = &g;
     if (!sg) {
@@ -444,7 +442,7 @@ rlbm_status rlbm_step(rlbm_lattice *h, void *f_a, void *f_b, int32_t nsteps, con
         sg->fa = f_a;
         sg->fb = f_b;
         sg->n = nsteps;
-        sg->variant = h->variant;
+        sg->variant = h->step_variant;
         sg->nt = uses_nontemporal(h);
       } else {
         sg->exec = nullptr;
@@ -874,7 +872,7 @@ rlbm_status rlbm_batch_autotune(rlbm_batch *b, void *f_a, void *f_b, int32_t ste
 
 rlbm_status rlbm_set_variant(rlbm_lattice *h, int32_t v) {
   if (!h || v < 0 || v >= rlbm::kNumVariants) return fail(RLBM_ERR_INVALID_ARG, "bad variant");
-  h->variant = v;
+  h->variant = h->step_variant = v;
   return RLBM_OK;
 }
 
@@ -925,11 +923,11 @@ rlbm_status rlbm_autotune(rlbm_lattice *h, int32_t steps, float *ms_out, hipStre
   }
   if (he == hipSuccess)
     st = rlbm_init(h, fields, fields + h->sites, fields + 2 * h->sites, nullptr, 0.0, fa, nullptr, stream);
-  const int saved = h->variant;
+  const int saved = h->step_variant;
   float best = 1e30f;
   int best_v = saved;
   for (int v = 0; he == hipSuccess && st == RLBM_OK && v < rlbm::kNumVariants; ++v) {
-    h->variant = v;
+    h->step_variant = v;
     st = rlbm_step(h, fa, fb, 2, nullptr, stream);
     if (st == RLBM_OK) he = hipEventRecord(e0, stream);
     if (he == hipSuccess && st == RLBM_OK) st = rlbm_step(h, fa, fb, steps, nullptr, stream);
@@ -944,7 +942,8 @@ rlbm_status rlbm_autotune(rlbm_lattice *h, int32_t steps, float *ms_out, hipStre
       best_v = v;
     }
   }
-  h->variant = (he == hipSuccess && st == RLBM_OK) ? best_v : saved;
+  if (he == hipSuccess && st == RLBM_OK) h->variant = h->step_variant = best_v;
+  else h->step_variant = saved;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipStreamSynchronize(stream);

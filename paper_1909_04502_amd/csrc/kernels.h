@@ -28,6 +28,8 @@ constexpr Variant kVariants[kNumVariants] = {
     {64, 4, 1, 0, 0, 0}, {64, 4, 1, 0, 1, 0}, {64, 4, 1, 2, 0, 0}, {64, 4, 1, 2, 2, 0}, {64, 2, 1, 0, 1, 0},
     {64, 1, 1, 0, 1, 0}, {128, 2, 1, 0, 1, 0}, {256, 1, 1, 0, 1, 0}, {64, 1, 1, 2, 2, 0}, {64, 2, 2, 2, 2, 0},
     {64, 4, 1, 4, 1, 0}, {64, 4, 1, 0, 2, 0}, {64, 4, 1, 0, 1, 1}};
+constexpr int kStagedVariant = 12;
+static_assert(kVariants[kStagedVariant].lds, "the staged kernel's number");
 
 struct LaunchArgs {
   int op = 0;
@@ -44,7 +46,6 @@ struct LaunchArgs {
   int *err = nullptr;               // device error flag
   int ext = 0;                      // the lattice has an external force or no-slip walls
   int open_x = 0;                   // reads clamp at the edges of the x axis
-  int staged = 0;                   // 2D product rules: the LDS-staged step kernel, whatever the variant
   int nt = 0;                       // step kernels store the populations non-temporally
   hipStream_t stream = 0;
 };

@@ -311,7 +311,7 @@ static hipError_t launch_t(const LaunchArgs &a) {
       using T = std::true_type;
       const bool ext = a.ext;
       if constexpr (!ST::ONLAT) {
-        if (vr.lds || a.staged) {
+        if (vr.lds) {
           const Tiling ltl = tiling(a.nx, a.ny, 64, 4, 1);
           auto launch_lds = [&](auto ext, auto nt, auto wd) {
             constexpr bool E = decltype(ext)::value, T = decltype(nt)::value, W = decltype(wd)::value;

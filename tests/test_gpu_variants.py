@@ -1,0 +1,107 @@
+"""Which kernel a launch variant starts: each step is captured into a HIP graph and its kernel node named.
+
+A number that is set starts its own kernel on every lattice, also where the staged kernel is the default; the default
+follows the size of the two states, the storage, the boundary and the rows as rlbm.h states.
+"""
+import ctypes
+
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+LDS = 12
+PP, OP, WP = ("periodic", "periodic"), ("open", "periodic"), ("wall", "periodic")
+
+
+class Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class KernelNodeParams(ctypes.Structure):   # hipKernelNodeParams
+    _fields_ = [("block", Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", Dim3),
+                ("params", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+
+def kernel_of(step):
+    """(name, block) of the one kernel that step() launches on the current stream (captured, not run)."""
+    from paper_1909_04502_amd import rlbm as R
+    hip = R.lib()   # its HIP runtime's functions are found through it
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+
+    def ok(status):
+        assert status == 0, status
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t(0)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s = ctypes.c_void_p(stream.cuda_stream)
+        ok(hip.hipStreamBeginCapture(s, 1))   # hipStreamCaptureModeThreadLocal
+        step()
+        ok(hip.hipStreamEndCapture(s, ctypes.byref(graph)))
+    ok(hip.hipGraphGetNodes(graph, None, ctypes.byref(n)))
+    assert n.value == 1
+    node = ctypes.c_void_p()
+    ok(hip.hipGraphGetNodes(graph, ctypes.byref(node), ctypes.byref(n)))
+    p = KernelNodeParams()
+    ok(hip.hipGraphKernelNodeGetParams(node, ctypes.byref(p)))
+    name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), None).decode()
+    ok(hip.hipGraphDestroy(graph))
+    return name, (p.block.x, p.block.y, p.block.z)
+
+
+def step_kernel(lat, buffers):
+    return kernel_of(lambda: lat.step(*buffers, 1))
+
+
+@pytest.mark.parametrize("storage,order,ext,bc,staged,number", [
+    ("f64", 3, (720, 720), PP, False, 5),            # 253 MiB
+    ("f64", 3, (736, 736), PP, True, LDS),           # 264
+    ("f64", 3, (725, 725), PP, True, 5),             # rows that are no multiple of 4: the register kernel's number
+    ("f64", 3, (1026, 1026), PP, True, 5),
+    ("f64", 3, (708, 777), OP, True, LDS),
+    ("f64", 3, (516, 1021), WP, True, LDS),
+    ("f64", 2, (904, 803), PP, True, LDS),
+    ("f32dev", 3, (1024, 1024), PP, False, 10),      # 256 MiB, not above it
+    ("f32dev", 3, (1100, 1100), PP, True, LDS),
+    ("f32dev_f64", 3, (1300, 1300), PP, True, LDS),
+    ("f32dev_f64", 3, (1204, 1205), WP, True, LDS),
+    ("f32dev_f64", 2, (1304, 1205), PP, True, LDS)])
+def test_every_number_starts_its_own_kernel(storage, order, ext, bc, staged, number):
+    from paper_1909_04502_amd import rlbm as R
+    print(f"[case] variant kernels {storage} {order} {ext} {bc}", flush=True)
+    lat = R.Lattice(d=2, zeta=1.0, order=order, extent=ext, bc=bc, storage=storage, tau=0.8)
+    small = R.Lattice(d=2, zeta=1.0, order=order, extent=(64, 8), bc=bc, storage=storage, tau=0.8)
+    lat.store_mode = small.store_mode = "cached"
+    bufs, sbufs = [lat.new_state(), lat.new_state()], [small.new_state(), small.new_state()]
+    assert lat.variant == number
+    register = small.variant
+    assert register != LDS and "k_step_lds" not in step_kernel(small, sbufs)[0]
+    assert ("k_step_lds" in step_kernel(lat, bufs)[0]) == staged
+    for v in range(R.lib().rlbm_variant_count()):
+        lat.variant = small.variant = v
+        name, block = step_kernel(lat, bufs)
+        assert ("k_step_lds" in name) == (v == LDS), v
+        if v != LDS:   # (the staged kernel has a second form for aligned rows)
+            assert (name, block) == step_kernel(small, sbufs), v
+    lat.variant = register
+    assert lat.variant == register and "k_step_lds" not in step_kernel(lat, bufs)[0]
+
+
+@pytest.mark.parametrize("ext", [(725, 725), (736, 736)])
+def test_autotune_times_the_default_register_kernel(ext):
+    """Every number's own kernel is timed, and the number kept is the kernel that runs."""
+    from paper_1909_04502_amd import rlbm as R
+    print(f"[case] variant autotune {ext}", flush=True)
+    lat = R.Lattice(d=2, zeta=1.0, order=3, extent=ext, storage="f64", tau=0.8)
+    n, T, u = (torch.tensor(a) for a in W.taylor_green_2d(*ext, 0.1, density_sigma=1e-3, seed=3))
+    f0 = lat.init(n, T, u)
+    a = lat.step(f0.clone(), lat.new_state(), 2)
+    ms = lat.autotune(steps=4)
+    assert len(ms) == R.lib().rlbm_variant_count() and ms[lat.variant] == min(ms)
+    b = lat.step(f0.clone(), lat.new_state(), 2)
+    name = step_kernel(lat, [f0, lat.new_state()])[0]
+    lat.sync()
+    assert ("k_step_lds" in name) == (lat.variant == LDS)
+    assert torch.equal(a, b)
