@@ -344,7 +344,9 @@ rlbm_status rlbm_batch_autotune(rlbm_batch *b, void *f_a, void *f_b, int32_t ste
  * product rules upstream windows staged in LDS); results do not depend on the
  * variant.  A number that is set, or chosen by rlbm_autotune, starts its own
  * kernel on every lattice.  Until then a lattice runs its default, which for the
- * 2D product rules is number 12 once the two state buffers exceed 256 MiB.  rlbm_get_variant answers the
+ * 2D product rules is number 12 once the two state buffers exceed 256 MiB (float
+ * storage with double arithmetic at order 3 without walls and force: 384 MiB, on a
+ * periodic x axis whose extent is a multiple of 4).  rlbm_get_variant answers the
  * number that was set or chosen, or the default's; where the default is number 12
  * and extent[0] is not a multiple of 4 it answers the number of the register kernel
  * that smaller lattices take.  rlbm_autotune times every variant for `steps` steps on

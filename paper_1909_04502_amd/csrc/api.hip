@@ -282,9 +282,16 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   // 494 -> 372, walls and force 515 x 1021 67 -> 59, open x 705 x 777 75 -> 58, order 2 901 x 803 74 -> 58; float
   // storage 1100 x 1100 85 -> 76, 2048 x 2048 232 -> 210).  Below that, where the halo re-reads hit that cache, the
   // register kernels stay ahead (double 700 x 700 47.5 against 49.2 us; float storage 1024 x 1024 54 against 57).
+  // Float storage with double arithmetic gains from it with walls or a force (1203 x 1205 111 -> 105) and at order 2
+  // (1303 x 1205 80 -> 76); elsewhere the two are even to within the boxes' spread (1201 x 1101 91.2 and 91.2,
+  // 2048 x 2048 241 and 244, 250 and 254, once 277 and 310), and it stays with the register kernel except where the
+  // staged one has been its default all along: past the non-temporal store threshold, on a periodic x axis of a
+  // multiple of 4 sites.
   const int64_t both = 2 * (cfg->storage == RLBM_F64 ? 8 : 4) * (int64_t)h->quad.Q * sites;
-  const bool staged = m.d == 2 && m.kind == RLBM_QUAD_PRODUCT && both > kStagedFootprint;
+  bool staged = m.d == 2 && m.kind == RLBM_QUAD_PRODUCT && both > kStagedFootprint;
   const bool rows4 = cfg->extent[0] % 4 == 0;
+  if (cfg->storage == RLBM_F32_DEV_F64 && m.order == 3 && !lattice_ext(h))
+    staged = staged && both > kNontemporalFootprint && cfg->bc[0] == RLBM_PERIODIC && rows4;
   // a default on rows of another length is answered with the number of its register kernel, as callers know it from
   // the time when the staged windows did not cover such rows; a number that is set always starts its own kernel
   h->step_variant = staged ? rlbm::kStagedVariant : h->variant;

@@ -65,6 +65,9 @@ def step_kernel(lat, buffers):
     ("f64", 2, (904, 803), PP, True, LDS),
     ("f32dev", 3, (1024, 1024), PP, False, 10),      # 256 MiB, not above it
     ("f32dev", 3, (1100, 1100), PP, True, LDS),
+    ("f32dev_f64", 3, (1201, 1101), PP, False, 9),   # 323 MiB
+    ("f32dev_f64", 3, (1501, 1999), PP, False, 9),
+    ("f32dev_f64", 3, (1300, 1300), OP, False, 9),   # 413 MiB
     ("f32dev_f64", 3, (1300, 1300), PP, True, LDS),
     ("f32dev_f64", 3, (1204, 1205), WP, True, LDS),
     ("f32dev_f64", 2, (1304, 1205), PP, True, LDS)])
