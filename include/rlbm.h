@@ -328,9 +328,10 @@ rlbm_status rlbm_batch_step(rlbm_batch *b, void *f_a, void *f_b, int32_t nsteps,
                             hipStream_t stream);
 rlbm_status rlbm_batch_moments(rlbm_batch *b, const void *f, const rlbm_fields *out, hipStream_t stream);
 rlbm_status rlbm_batch_sync(rlbm_batch *b, hipStream_t stream);
-/* Batch launch variants: tile shape x persistent grid size.  rlbm_batch_autotune
- * times each on the caller's state (an even number of steps per variant, so the
- * evolved state ends in f_a) and keeps the fastest. */
+/* Batch launch variants: tile shape x persistent grid size; 0, 4 and 8 are the
+ * same kernel (64 x 4 tiles staged in LDS, one block per tile), timed once.
+ * rlbm_batch_autotune times each on the caller's state (an even number of steps
+ * per variant, so the evolved state ends in f_a) and keeps the fastest. */
 int32_t rlbm_batch_variant_count(void);
 rlbm_status rlbm_batch_set_variant(rlbm_batch *b, int32_t variant);
 rlbm_status rlbm_batch_get_variant(const rlbm_batch *b, int32_t *variant);
@@ -355,7 +356,8 @@ rlbm_status rlbm_batch_autotune(rlbm_batch *b, void *f_a, void *f_b, int32_t ste
  * of 1 with site-to-site noise of 1e-3; the
  * caller's buffers are not touched), selects the fastest and
  * returns after synchronising the stream.  ms_out (host, may be NULL)
- * receives rlbm_variant_count() milliseconds per step. */
+ * receives rlbm_variant_count() milliseconds per step.  The 3D rules have one
+ * kernel under every number: it is timed once, and the number stays. */
 int32_t rlbm_variant_count(void);
 rlbm_status rlbm_set_variant(rlbm_lattice *h, int32_t variant);
 rlbm_status rlbm_get_variant(const rlbm_lattice *h, int32_t *variant);

@@ -247,7 +247,8 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   h->stencil = stencil_of(m);
   // default launch shapes (from sweeps of every variant on MI355X):
   //  * 3D rules: every variant launches the same kernel in the same shape (split.hip,
-  //    split_onlat.hip, split_ur3d.hip);
+  //    split_onlat.hip, split_ur3d.hip), so the numbers below only are what rlbm_get_variant has
+  //    always answered;
   //  * 2D product rules in double: rows of 64 sites; float storage with double arithmetic: 64 x 4
   //    band tiles of the occupancy-2 build (4 % faster than rows of 64); float storage and
   //    arithmetic: 64 x 4 band tiles of the occupancy-4 build (0.057 against 0.060 ms at 1024^2 for
@@ -848,9 +849,13 @@ rlbm_status rlbm_batch_autotune(rlbm_batch *b, void *f_a, void *f_b, int32_t ste
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);
-  float best = 1e30f;
+  float best = 1e30f, staged_ms = 0.0f;
   int best_v = b->variant;
   for (int v = 0; he == hipSuccess && v < kNumBatchVariants; ++v) {
+    if (v != 0 && v % 4 == 0) {   // staged tiles: one block per tile under every grid size
+      if (ms_out) ms_out[v] = staged_ms;
+      continue;
+    }
     if (rlbm_batch_set_variant(b, v) != RLBM_OK) {
       he = hipErrorUnknown;
       break;
@@ -863,6 +868,7 @@ rlbm_status rlbm_batch_autotune(rlbm_batch *b, void *f_a, void *f_b, int32_t ste
     float ms = 0.0f;
     if (he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
     ms /= ev;
+    if (v == 0) staged_ms = ms;
     if (ms_out) ms_out[v] = ms;
     if (he == hipSuccess && ms < best) {
       best = ms;
@@ -931,9 +937,11 @@ rlbm_status rlbm_autotune(rlbm_lattice *h, int32_t steps, float *ms_out, hipStre
   if (he == hipSuccess)
     st = rlbm_init(h, fields, fields + h->sites, fields + 2 * h->sites, nullptr, 0.0, fa, nullptr, stream);
   const int saved = h->step_variant;
+  // every number of a 3D lattice starts the same kernel: timed once, and the number stays
+  const int timed = d == 3 ? 1 : rlbm::kNumVariants;
   float best = 1e30f;
   int best_v = saved;
-  for (int v = 0; he == hipSuccess && st == RLBM_OK && v < rlbm::kNumVariants; ++v) {
+  for (int v = 0; he == hipSuccess && st == RLBM_OK && v < timed; ++v) {
     h->step_variant = v;
     st = rlbm_step(h, fa, fb, 2, nullptr, stream);
     if (st == RLBM_OK) he = hipEventRecord(e0, stream);
@@ -943,14 +951,15 @@ rlbm_status rlbm_autotune(rlbm_lattice *h, int32_t steps, float *ms_out, hipStre
     float ms = 0.0f;
     if (he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
     ms /= steps;
-    if (ms_out) ms_out[v] = ms;
-    if (he == hipSuccess && ms < best) {
+    if (ms_out)
+      for (int e = v; e < (d == 3 ? rlbm::kNumVariants : v + 1); ++e) ms_out[e] = ms;
+    if (he == hipSuccess && d != 3 && ms < best) {
       best = ms;
       best_v = v;
     }
   }
-  if (he == hipSuccess && st == RLBM_OK) h->variant = h->step_variant = best_v;
-  else h->step_variant = saved;
+  h->step_variant = saved;
+  if (he == hipSuccess && st == RLBM_OK && d != 3) h->variant = h->step_variant = best_v;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipStreamSynchronize(stream);

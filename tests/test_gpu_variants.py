@@ -108,3 +108,28 @@ def test_autotune_times_the_default_register_kernel(ext):
     lat.sync()
     assert ("k_step_lds" in name) == (lat.variant == LDS)
     assert torch.equal(a, b)
+
+
+def test_autotune_keeps_the_number_of_a_3d_lattice():
+    """One kernel under every number: one time for all of them, and no number chosen by chance."""
+    from paper_1909_04502_amd import rlbm as R
+    print("[case] variant autotune 3d", flush=True)
+    for storage in ("f64", "f32dev"):
+        lat = R.Lattice(d=3, zeta=1.0, order=2, extent=(65, 9, 10), storage=storage, tau=0.8)
+        for number in (lat.variant, 7):
+            lat.variant = number
+            ms = lat.autotune(steps=2)
+            assert len(ms) == R.lib().rlbm_variant_count() and ms[0] > 0 and set(ms) == {ms[0]}
+            assert lat.variant == number
+
+
+def test_batch_autotune_times_the_staged_tiles_once():
+    from paper_1909_04502_amd import rlbm as R
+    print("[case] variant autotune batch", flush=True)
+    sizes = [(64, 40), (130, 33), (65, 17)]
+    b = R.Batch([{"extent": e, "tau": 0.8, "zeta": 1.0} for e in sizes])
+    f = [[torch.tensor(a) for a in W.taylor_green_2d(*e, 0.05, density_sigma=1e-3, seed=5)] for e in sizes]
+    f0 = b.init(*[[x[k] for x in f] for k in range(3)])
+    ms = b.autotune(f0, b.new_state(), steps=2)
+    assert all(m > 0 for m in ms) and ms[0] == ms[4] == ms[8]
+    assert b.variant not in (4, 8) and ms[b.variant] == min(ms)
