@@ -261,17 +261,44 @@ struct SplitTiling {
   int planes;   // planes per patch
 };
 
-// The tiling of a lattice, and its blocks (0: more than a grid holds).
+// The tiling of a lattice, and its blocks (0: more than a grid holds).  The XCDs take whole patches in turn, or each
+// an eighth of the sequence of patches, whichever leaves the busiest XCD less to do: that is what a step's time
+// follows (whole patches against eighths in double: 64 x 48 x 48, whose busiest XCD has 1.11 times the blocks in whole
+// patches, 64 against 58 us; 97 x 56 x 56, 1.14 times, 178 against 162; 100 x 72 x 72, 1.09 times, 263 against 252;
+// 97 x 100 x 83, 0.97 times, 402 against 420; 100 x 44 x 41, 0.92 times, 104 against 111; the tube of 6400 x 1 x 1, one
+// patch, 52 against 14).  From 256 patches on that differs by less than 3 %, which the L2 hits of whole patches outweigh.
 inline SplitTiling split_tiling(int nx, int ny, int nz, unsigned &blocks) {
   const int rows = ny < kSlab ? ny : kSlab, planes = nz < kSlab ? nz : kSlab;
   SplitTiling tl{0, (ny + rows - 1) / rows, (int)(((int64_t)rows * nx + 63) / 64), rows, planes};
-  const int64_t npatch = (int64_t)tl.npy * ((nz + planes - 1) / planes), per = (int64_t)tl.runs * planes;
-  // whole patches in turn while an XCD has several of them (97 x 130 x 83 in double 0.60 ms, 0.64 in eighths of
-  // the sequence); a lattice of few patches is cut into eighths, which spreads it over all XCDs (the tube of
-  // 6400 x 1 x 1 is one patch: 0.052 ms on one XCD, 0.014 on eight)
-  const int64_t nb = npatch >= 32 ? 8 * ((npatch + 7) / 8) * per : 8 * ((npatch * per + 7) / 8);
+  const int npz = (nz + planes - 1) / planes;
+  const int64_t npatch = (int64_t)tl.npy * npz, per = (int64_t)tl.runs * planes, eighth = (npatch * per + 7) / 8;
+  bool whole = true;
+  if (npatch < 256) {
+    // runs that hold sites: of a plane of the last slab, of a plane of all slabs; and planes of the last patches
+    const int64_t last_runs = ((int64_t)(ny - (tl.npy - 1) * rows) * nx + 63) / 64, last_planes = nz - (npz - 1) * planes;
+    const int64_t all_runs = (tl.npy - 1) * (int64_t)tl.runs + last_runs;
+    auto runs_of = [&](int64_t py) { return py < tl.npy - 1 ? (int64_t)tl.runs : last_runs; };
+    auto planes_of = [&](int64_t pz) { return pz < npz - 1 ? (int64_t)planes : last_planes; };
+    // and of the first t of the sequence
+    auto before = [&](int64_t t) {
+      const int64_t p = t / per, w = t % per, pz = p / tl.npy, py = p % tl.npy, z = w / tl.runs, r = w % tl.runs;
+      if (p >= npatch) return nz * all_runs;
+      const int64_t n = pz * planes * all_runs + planes_of(pz) * py * tl.runs;
+      if (z >= planes_of(pz)) return n + planes_of(pz) * runs_of(py);
+      return n + z * runs_of(py) + (r < runs_of(py) ? r : runs_of(py));
+    };
+    int64_t load[8] = {0}, most_whole = 0, most_eighth = 0;
+    for (int64_t p = 0; p < npatch; ++p) load[p % 8] += runs_of(p % tl.npy) * planes_of(p / tl.npy);
+    for (int k = 0; k < 8; ++k) {
+      const int64_t e = before((k + 1) * eighth) - before(k * eighth);
+      if (load[k] > most_whole) most_whole = load[k];
+      if (e > most_eighth) most_eighth = e;
+    }
+    whole = most_whole <= most_eighth;
+  }
+  const int64_t nb = whole ? 8 * ((npatch + 7) / 8) * per : 8 * eighth;
   blocks = nb > 0x7fffffff ? 0u : (unsigned)nb;
-  tl.chunk = npatch >= 32 ? 0 : (int)(nb / 8);
+  tl.chunk = whole ? 0 : (int)eighth;
   return tl;
 }
 
@@ -299,7 +326,7 @@ __device__ __forceinline__ bool split_site(CTables *tb, const SplitTiling &tl, i
     x = at >= nx ? at - nx : at;
     y = run.y0 + (at >= nx);
   } else {
-    // at / nx of at < 128 by a float quotient, corrected
+    // at / nx by a float quotient, corrected (at < nx + 63; below 128 where nx < 64, else the quotient is 0 or 1)
     int r = (int)((float)at * __builtin_amdgcn_rcpf((float)nx));
     r -= r * nx > at;
     r += at - r * nx >= nx;

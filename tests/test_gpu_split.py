@@ -92,3 +92,21 @@ def test_split_massive_rule(extent, storage):
 def test_split_massless_rule(extent, bc, storage):
     print(f"[case] split massless {extent} {storage}", flush=True)
     check(extent, storage, zeta=0.0, quad=qd.ur_onlattice_3d(3), kind="ur_onlattice", bc=bc, tau=0.6, tau_T=0.3)
+
+
+@pytest.mark.parametrize("extent,storage", [((20, 41, 43), "f64"), ((67, 43, 41), "f32dev"), ((66, 48, 41), "f64"),
+                                            ((3, 130, 129), "f32dev_f64")])
+def test_split_step_of_many_patches(extent, storage):
+    """36 patches and more, cut off in y and z, in whole patches and in eighths, and 289 of them."""
+    print(f"[case] split patches {extent} {storage}", flush=True)
+    check(extent, storage, order=2, zeta=0.0)   # (the oracle's equation of state is fast without a mass)
+
+
+@pytest.mark.parametrize("kind", ["massive_onlattice", "ur_onlattice"])
+def test_split_onlattice_of_many_patches(kind):
+    print(f"[case] split patches {kind}", flush=True)
+    v0 = 0.2719557997821228
+    if kind == "massive_onlattice":
+        check((5, 41, 43), "f32dev", zeta=5.0, quad=qd.massive_onlattice(3, 5.0, 3, v0), kind=kind, v0=v0)
+    else:
+        check((9, 41, 43), "f64", zeta=0.0, quad=qd.ur_onlattice_3d(3), kind=kind, tau=0.6, tau_T=0.3)

@@ -26,7 +26,7 @@ class KernelNodeParams(ctypes.Structure):   # hipKernelNodeParams
 
 
 def kernel_of(step):
-    """(name, block) of the one kernel that step() launches on the current stream (captured, not run)."""
+    """(name, block, grid) of the one kernel that step() launches on the current stream (captured, not run)."""
     from paper_1909_04502_amd import rlbm as R
     hip = R.lib()   # its HIP runtime's functions are found through it
     hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
@@ -48,7 +48,7 @@ def kernel_of(step):
     ok(hip.hipGraphKernelNodeGetParams(node, ctypes.byref(p)))
     name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), None).decode()
     ok(hip.hipGraphDestroy(graph))
-    return name, (p.block.x, p.block.y, p.block.z)
+    return name, (p.block.x, p.block.y, p.block.z), p.grid.x * p.grid.y * p.grid.z
 
 
 def step_kernel(lat, buffers):
@@ -84,10 +84,10 @@ def test_every_number_starts_its_own_kernel(storage, order, ext, bc, staged, num
     assert ("k_step_lds" in step_kernel(lat, bufs)[0]) == staged
     for v in range(R.lib().rlbm_variant_count()):
         lat.variant = small.variant = v
-        name, block = step_kernel(lat, bufs)
+        name, block, _ = step_kernel(lat, bufs)
         assert ("k_step_lds" in name) == (v == LDS), v
         if v != LDS:   # (the staged kernel has a second form for aligned rows)
-            assert (name, block) == step_kernel(small, sbufs), v
+            assert (name, block) == step_kernel(small, sbufs)[:2], v
     lat.variant = register
     assert lat.variant == register and "k_step_lds" not in step_kernel(lat, bufs)[0]
 
@@ -133,3 +133,29 @@ def test_batch_autotune_times_the_staged_tiles_once():
     ms = b.autotune(f0, b.new_state(), steps=2)
     assert all(m > 0 for m in ms) and ms[0] == ms[4] == ms[8]
     assert b.variant not in (4, 8) and ms[b.variant] == min(ms)
+
+
+@pytest.mark.parametrize("ext,whole", [((64, 48, 48), False),     # 36 patches: five for the busiest XCD, 4.5 on average
+                                       ((97, 56, 56), False), ((128, 64, 64), True),
+                                       ((100, 44, 41), True),     # cut patches: eighths leave one XCD almost nothing
+                                       ((97, 130, 83), True), ((70, 129, 129), True), ((6400, 1, 1), False)])
+def test_3d_blocks_go_to_the_xcds_as_evenly_as_they_can(ext, whole):
+    """Whole patches of 8 x 8 rows in turn (the grid is rounded up to 8 patches), or eighths of the sequence (rounded up
+    to 8 blocks): the grid of either, and the order with the lesser maximum."""
+    from paper_1909_04502_amd import rlbm as R
+    print(f"[case] split order {ext}", flush=True)
+    nx, ny, nz = ext
+    rows, planes = min(ny, 8), min(nz, 8)
+    npy, npz, runs = -(-ny // rows), -(-nz // planes), -(-rows * nx // 64)
+    per, npatch = runs * planes, npy * npz
+    loads = [[0] * 8, [0] * 8]
+    for p in range(npatch):
+        live = -(-min(rows, ny - p % npy * rows) * nx // 64)
+        for w in range(per):
+            if p // npy * planes + w // runs < nz and w % runs < live:
+                loads[0][p % 8] += 1
+                loads[1][(p * per + w) // -(-npatch * per // 8)] += 1
+    assert whole == (npatch >= 256 or max(loads[0]) <= max(loads[1]))
+    lat = R.Lattice(d=3, zeta=1.0, order=2, extent=ext, storage="f32dev", tau=0.8)
+    grid = step_kernel(lat, [lat.new_state(), lat.new_state()])[2]
+    assert grid == (8 * -(-npatch // 8) * per if whole else 8 * -(-npatch * per // 8))
