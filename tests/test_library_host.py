@@ -274,3 +274,50 @@ def test_lds_loads_take_uniform_operands(rlbm_lib, tmp_path):
         assert lines[i - 1] == "s_nop 0", lines[i - 2:i + 1]
         assert re.fullmatch(r"s_mov_b32 m0, s\d+", lines[i - 2]), lines[i - 2:i + 1]
     shutil.rmtree(tmp_path, ignore_errors=True)
+
+
+def code_objects(blob, target="gfx950"):
+    """The device code objects of a .hip_fatbin section: one offload bundle per source, one after another."""
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := blob.find(magic, at)) >= 0:
+        word = lambda o: int.from_bytes(blob[o:o + 8], "little")   # noqa: E731
+        p = at + len(magic) + 8
+        for _ in range(word(at + len(magic))):
+            offset, size, n = word(p), word(p + 8), word(p + 16)
+            if blob[p + 24:p + 24 + n].decode().endswith(target):
+                yield blob[at + offset:at + offset + size]
+            p += 24 + n
+        at += len(magic)
+
+
+def test_lds_loads_of_every_code_object_take_uniform_operands(rlbm_lib, tmp_path):
+    """The same for both forms (4 and 16 bytes per lane) in the code objects of all sources: the step's (float storage,
+    walls, odd extents) and the batch's windows are loaded 4 bytes per lane.  A load under a condition may stand behind
+    the branch or the mask that skips it, but between the write of m0, the wait state and the load there is nothing."""
+    import subprocess
+    from paper_1909_04502_amd import build as b
+    objcopy, objdump = (os.path.join("/opt/rocm/llvm/bin", t) for t in ("llvm-objcopy", "llvm-objdump"))
+    if not (os.path.exists(objcopy) and os.path.exists(objdump)):
+        pytest.skip("LLVM binary tools not installed")
+    fat = tmp_path / "fatbin"
+    subprocess.run([objcopy, f"--dump-section=.hip_fatbin={fat}", b.LIB, str(tmp_path / "lib.so")], check=True,
+                   capture_output=True)
+    found, objects = [], list(code_objects(fat.read_bytes()))
+    assert len(objects) == sum(s.endswith(".hip") and "kernels.hip" not in s for s in b.SOURCES)
+    for co in objects:
+        (tmp_path / "co.o").write_bytes(co)
+        dis = subprocess.run([objdump, "-d", str(tmp_path / "co.o")], check=True, capture_output=True, text=True).stdout
+        lines = [t for t in (l.split("//")[0].strip() for l in dis.splitlines()) if t and not t.endswith(">:")]
+        forms = [0, 0]
+        for i, l in enumerate(lines):
+            if not re.match(r"(global|buffer)_load_(lds_|.*\blds\b)", l):
+                continue
+            m = re.fullmatch(r"global_load_lds_dword(x4)? v\d+, s\[\d+:\d+\]", l)
+            assert m, l
+            assert lines[i - 1] == "s_nop 0", lines[i - 2:i + 1]
+            assert re.fullmatch(r"s_mov_b32 m0, s\d+", lines[i - 2]), lines[i - 2:i + 1]
+            forms[m[1] is not None] += 1
+        if any(forms):
+            found.append(forms)
+    assert len(found) == 2 and all(f[0] for f in found), found   # step_prod2d.hip and batch.hip
+    assert any(f[1] for f in found), found
