@@ -53,8 +53,8 @@ __global__ void __launch_bounds__(BX * BY) k_step_batch(const Tables *__restrict
     Offs o;
 #pragma unroll
     for (int dd = -1; dd <= 1; ++dd) {
-      o.x[dd + 1] = (uint32_t)stage_wrap(x + dd, nx, tb->open[0]) * (uint32_t)sizeof(S);
-      o.y[dd + 1] = (uint32_t)stage_wrap(y + dd, ny, tb->open[1]) * (uint32_t)nx * (uint32_t)sizeof(S);
+      o.x[dd + 1] = (uint32_t)near_site(x + dd, nx, tb->open[0]) * (uint32_t)sizeof(S);
+      o.y[dd + 1] = (uint32_t)near_site(y + dd, ny, tb->open[1]) * (uint32_t)nx * (uint32_t)sizeof(S);
       o.z[dd + 1] = 0u;
     }
     A f[ST::Q];

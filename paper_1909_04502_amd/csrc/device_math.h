@@ -23,6 +23,13 @@ typedef const __attribute__((address_space(4))) Tables CTables;
 typedef const __attribute__((address_space(4))) double CDouble;
 #endif
 
+// The place of v on an axis of n sites (v at most n past its ends): one wrap, or the edge of an open axis.
+__device__ __forceinline__ int near_site(int v, int n, int open) {
+  if (open) return v < 0 ? 0 : (v >= n ? n - 1 : v);
+  v = v < 0 ? v + n : v;
+  return v >= n ? v - n : v;
+}
+
 __device__ __forceinline__ constexpr double eta_c(int a, int b) { return a != b ? 0.0 : (a == 0 ? 1.0 : -1.0); }
 
 // ---------------------------------------------------------------------------

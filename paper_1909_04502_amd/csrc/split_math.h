@@ -245,12 +245,6 @@ struct SplitRun {
   int brk;   // lane of the first site of the second row (64: none; rows of at least 64 sites have one at most)
 };
 
-__device__ __forceinline__ int near_site(int v, int n, int open) {
-  if (open) return v < 0 ? 0 : (v >= n ? n - 1 : v);
-  v = v < 0 ? v + n : v;
-  return v >= n ? v - n : v;
-}
-
 constexpr int kSlab = 8;   // rows of a run's slab, planes of a patch
 
 struct SplitTiling {

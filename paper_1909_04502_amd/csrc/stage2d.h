@@ -75,12 +75,6 @@ __device__ __forceinline__ void stage_load(const char *base, uint32_t voff, uint
                  : "memory", "m0");
 }
 
-__device__ __forceinline__ int stage_wrap(int v, int n, int open) {
-  if (open) return v < 0 ? 0 : (v >= n ? n - 1 : v);
-  v = v < 0 ? v + n : v;
-  return v >= n ? v - n : v;
-}
-
 // What a wave loads of every shell: planes w and w + 4, from which rows and columns.  Rows and columns
 // past the one upstream of the lattice's edge belong to no site; they repeat that one, so every address
 // lies inside the plane.
@@ -105,7 +99,7 @@ struct StagePlan {
 #pragma unroll
     for (int h = 0; h < L::H; ++h) {
       const int c = h * (64 / L::H) + lane / L::H;
-      col[h] = (uint32_t)stage_wrap(min(x0 + c, nx), nx, openx) * (uint32_t)sizeof(S) + (lane % L::H) * 4u;
+      col[h] = (uint32_t)near_site(min(x0 + c, nx), nx, openx) * (uint32_t)sizeof(S) + (lane % L::H) * 4u;
     }
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -123,16 +117,16 @@ struct StagePlan {
       const int yf = y0 - (dy > 0);   // the window's first row
 #pragma unroll
       for (int r = 0; r < 5; ++r)
-        row[e][r] = (int64_t)stage_wrap(min(yf + r, ny), ny, openy) * nx * (int64_t)sizeof(S);
+        row[e][r] = (int64_t)near_site(min(yf + r, ny), ny, openy) * nx * (int64_t)sizeof(S);
 #pragma unroll
       for (int n = 0; n < 3; ++n) {
         const int r = n * L::RPI + lane / L::LPR, c = lane % L::LPR * (16 / (int)sizeof(S));
-        wide[e][n] = ((uint32_t)stage_wrap(min(yf + r, ny), ny, openy) * (uint32_t)nx +
-                      (uint32_t)stage_wrap(min(x0 + c, nx), nx, openx)) * (uint32_t)sizeof(S);
+        wide[e][n] = ((uint32_t)near_site(min(yf + r, ny), ny, openy) * (uint32_t)nx +
+                      (uint32_t)near_site(min(x0 + c, nx), nx, openx)) * (uint32_t)sizeof(S);
         wlane[e][n] = r < nrow[e];
       }
       const int r = lane / L::H;      // the row of this lane's part of the side column
-      const int ys = stage_wrap(min(yf + r, ny), ny, openy), xs = stage_wrap(min(dx > 0 ? x0 - 1 : x0 + 64, nx), nx, openx);
+      const int ys = near_site(min(yf + r, ny), ny, openy), xs = near_site(min(dx > 0 ? x0 - 1 : x0 + 64, nx), nx, openx);
       scol[e] = ((uint32_t)ys * (uint32_t)nx + (uint32_t)xs) * (uint32_t)sizeof(S) + (lane % L::H) * 4u;
       slane[e] = r < nrow[e];
     }

@@ -33,12 +33,6 @@
 
 namespace rlbm {
 
-__device__ __forceinline__ int wrap_or_clamp(int v, int n, int open) {
-  if (open) return v < 0 ? 0 : (v >= n ? n - 1 : v);
-  v = v < 0 ? v + n : v;
-  return v >= n ? v - n : v;
-}
-
 // Moments of the shifted monomials (p^0 - m) p^e = p^0 p^e - m p^e, in place
 // (stencils whose projection rows act on the shifted basis).
 template <int D, int N>
@@ -84,8 +78,8 @@ __device__ __forceinline__ Offs make_offs(CTables *tb, int x, int y) {
   const uint32_t nx = tb->nx;
 #pragma unroll
   for (int d = -1; d <= 1; ++d) {
-    o.x[d + 1] = (uint32_t)wrap_or_clamp(x + d, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
-    o.y[d + 1] = (uint32_t)wrap_or_clamp(y + d, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
+    o.x[d + 1] = (uint32_t)near_site(x + d, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
+    o.y[d + 1] = (uint32_t)near_site(y + d, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
     o.z[d + 1] = 0u;
   }
   return o;
@@ -110,8 +104,8 @@ __device__ __forceinline__ void gather_onlat(CTables *tb, const S *__restrict__ 
   const uint32_t nx = tb->nx;
 #pragma unroll
   for (int k = 0; k <= 2 * R; ++k) {
-    ox[k] = (uint32_t)wrap_or_clamp(x + k - R, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
-    oy[k] = (uint32_t)wrap_or_clamp(y + k - R, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
+    ox[k] = (uint32_t)near_site(x + k - R, tb->nx, tb->open[0]) * (uint32_t)sizeof(S);
+    oy[k] = (uint32_t)near_site(y + k - R, tb->ny, tb->open[1]) * nx * (uint32_t)sizeof(S);
   }
   gather_onlat_impl<ST, S, R>(fin, sites, ox, oy, f, std::make_integer_sequence<int, ST::Q>{});
 }
