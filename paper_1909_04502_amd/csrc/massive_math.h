@@ -227,8 +227,12 @@ __device__ __forceinline__ Macro<ST::D> collide_massive(CTables *tb, S (&f)[ST::
   auto feq_full = [&](int i, A e) { return DEV ? e + tab<A>(tb->fref[i], tb->freff[i]) : e; };
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    if (N > 2 && g % 2 == 0)   // (order 2: all fit the scalar registers)
-      from_here_on(tb, g == 0 ? ap[0] : f[ST::gfirst(g - 2)]);
+    // (order 2: all fit the scalar registers; with walls, a force or in float every fourth group: asked for with every
+    // second one, the walls' build takes 270 registers instead of 233, one wave per SIMD instead of two, 50 instead of
+    // 37 us a step at 512 x 512, and the float one spills, 19.1 instead of 18.5; without them in double every second is
+    // ahead, 34.6 against 35.1)
+    constexpr int kGroups = sizeof(A) == 8 && !EXT ? 2 : 4;
+    if (N > 2 && g % kGroups == 0) from_here_on(tb, g == 0 ? ap[0] : f[ST::gfirst(g >= kGroups ? g - kGroups : 0)]);
     A ce[20];
 #pragma unroll
     for (int q = 0; q < AT.n; ++q) {

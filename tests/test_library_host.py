@@ -290,23 +290,57 @@ def code_objects(blob, target="gfx950"):
         at += len(magic)
 
 
+def built_objects(tmp_path):
+    """The library's device code objects as files."""
+    import subprocess
+    from paper_1909_04502_amd import build as b
+    objcopy = "/opt/rocm/llvm/bin/llvm-objcopy"
+    if not os.path.exists(objcopy):
+        pytest.skip("LLVM binary tools not installed")
+    fat, files = tmp_path / "fatbin", []
+    subprocess.run([objcopy, f"--dump-section=.hip_fatbin={fat}", b.LIB, str(tmp_path / "lib.so")], check=True,
+                   capture_output=True)
+    for k, co in enumerate(code_objects(fat.read_bytes())):
+        files.append(tmp_path / f"co{k}.o")
+        files[-1].write_bytes(co)
+    return files
+
+
+def kernel_resources(tmp_path):
+    """{mangled kernel name: (vector registers, bytes of scratch per lane)} of the library."""
+    import subprocess
+    found = {}
+    for co in built_objects(tmp_path):
+        notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", str(co)], check=True, capture_output=True,
+                               text=True).stdout
+        for k in notes.split("- .agpr_count:")[1:]:
+            def field(n):
+                return re.search(rf"\.{n}:\s+(\S+)", k)[1]
+            found[field("name")] = (int(field("vgpr_count")), int(field("private_segment_fixed_size")))
+    return found
+
+
+def test_2d_massive_order_3_keeps_its_waves(rlbm_lib, tmp_path):
+    """The 45-vector rule's double step and initial state hold two waves per SIMD (256 registers) in every build without
+    a four-wave target, walls and force among them, and its float step fits 128 registers without scratch."""
+    res = kernel_resources(tmp_path)
+    double = {n: r for n, r in res.items() if re.search(r"\dk_(step|init|moments)INS_7StencilILi3ELi3EEELi3EdLb0E", n)
+              and "EdLb0ELi4E" not in n}
+    assert len(double) == 8 and all(v <= 256 and scratch == 0 for v, scratch in double.values()), double
+    flt = {n: r for n, r in res.items() if re.search(r"\dk_stepINS_7StencilILi3ELi3EEELi3EfLb1E", n)}
+    assert len(flt) == 8 and all(v <= 128 and scratch == 0 for v, scratch in flt.values()), flt
+
+
 def test_lds_loads_of_every_code_object_take_uniform_operands(rlbm_lib, tmp_path):
     """The same for both forms (4 and 16 bytes per lane) in the code objects of all sources: the step's (float storage,
     walls, odd extents) and the batch's windows are loaded 4 bytes per lane.  A load under a condition may stand behind
     the branch or the mask that skips it, but between the write of m0, the wait state and the load there is nothing."""
     import subprocess
     from paper_1909_04502_amd import build as b
-    objcopy, objdump = (os.path.join("/opt/rocm/llvm/bin", t) for t in ("llvm-objcopy", "llvm-objdump"))
-    if not (os.path.exists(objcopy) and os.path.exists(objdump)):
-        pytest.skip("LLVM binary tools not installed")
-    fat = tmp_path / "fatbin"
-    subprocess.run([objcopy, f"--dump-section=.hip_fatbin={fat}", b.LIB, str(tmp_path / "lib.so")], check=True,
-                   capture_output=True)
-    found, objects = [], list(code_objects(fat.read_bytes()))
+    found, objects = [], built_objects(tmp_path)
     assert len(objects) == sum(s.endswith(".hip") and "kernels.hip" not in s for s in b.SOURCES)
     for co in objects:
-        (tmp_path / "co.o").write_bytes(co)
-        dis = subprocess.run([objdump, "-d", str(tmp_path / "co.o")], check=True, capture_output=True, text=True).stdout
+        dis = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", str(co)], check=True, capture_output=True, text=True).stdout
         lines = [t for t in (l.split("//")[0].strip() for l in dis.splitlines()) if t and not t.endswith(">:")]
         forms = [0, 0]
         for i, l in enumerate(lines):
