@@ -141,10 +141,18 @@ __device__ __forceinline__ void pull_prod(CTables *tb, const S *__restrict__ fin
 // plane of a wall axis the prescribed temperature of that plane, or 0 for the
 // site's own temperature.
 __device__ __forceinline__ double site_wall(CTables *tb, int x, int y, int z) {
-  if (tb->wall[0] && (x == 0 || x == tb->nx - 1)) return tb->wallT[0][x == 0 ? 0 : 1];
-  if (tb->wall[1] && (y == 0 || y == tb->ny - 1)) return tb->wallT[1][y == 0 ? 0 : 1];
-  if (tb->wall[2] && (z == 0 || z == tb->nz - 1)) return tb->wallT[2][z == 0 ? 0 : 1];
-  return -1.0;
+  double T = -1.0;
+  auto axis = [&](int a, int v, int n) {
+    // both planes' temperatures through scalar registers: a load of the lane's own would make every wave wait for the
+    // populations that it has in flight (massive order 2, double, walls at 512 x 512: 23.1 us a step instead of 21.6)
+    double lo = tb->wallT[a][0], hi = tb->wallT[a][1];
+    asm("" : "+s"(lo), "+s"(hi));
+    if (tb->wall[a]) T = v == 0 ? lo : (v == n - 1 ? hi : T);
+  };
+  axis(2, z, tb->nz);   // the first axis last: it decides on the edges
+  axis(1, y, tb->ny);
+  axis(0, x, tb->nx);
+  return T;
 }
 
 // The temperature and moment ratios the equilibrium is built from: the

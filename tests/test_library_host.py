@@ -355,3 +355,24 @@ def test_lds_loads_of_every_code_object_take_uniform_operands(rlbm_lib, tmp_path
             found.append(forms)
     assert len(found) == 2 and all(f[0] for f in found), found   # step_prod2d.hip and batch.hip
     assert any(f[1] for f in found), found
+
+
+def test_wall_temperatures_are_not_loaded_lane_by_lane(rlbm_lib, tmp_path):
+    """The step with walls and force loads its populations and its tau and nothing else through vector registers: a wall
+    temperature loaded by each lane would make the wave wait for every load it has in flight."""
+    import subprocess
+    from paper_1909_04502_amd import rlbm as R
+    Q = R.quadrature_build(2, 5.0, 2, "massive_onlattice", v0=0.0)[0].shape[0]
+    pattern = re.compile(r"\S*k_stepINS_7StencilILi3ELi2EEELi2EdLb0ELi0ELb1ELb[01]EdE\S*")
+    seen = 0
+    for co in built_objects(tmp_path):
+        syms = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "-sW", str(co)], check=True, capture_output=True,
+                              text=True).stdout
+        for line in syms.splitlines():
+            if " FUNC " not in line or not pattern.fullmatch(line.split()[-1]):
+                continue
+            dis = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", f"--disassemble-symbols={line.split()[-1]}",
+                                  str(co)], check=True, capture_output=True, text=True).stdout
+            assert len(re.findall(r"\bglobal_load_", dis)) == Q + 1
+            seen += 1
+    assert seen == 2
