@@ -368,11 +368,10 @@ def test_wall_temperatures_are_not_loaded_lane_by_lane(rlbm_lib, tmp_path):
     for co in built_objects(tmp_path):
         syms = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "-sW", str(co)], check=True, capture_output=True,
                               text=True).stdout
-        for line in syms.splitlines():
-            if " FUNC " not in line or not pattern.fullmatch(line.split()[-1]):
-                continue
-            dis = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", f"--disassemble-symbols={line.split()[-1]}",
-                                  str(co)], check=True, capture_output=True, text=True).stdout
+        names = {line.split()[-1] for line in syms.splitlines() if " FUNC " in line}   # (listed in two symbol tables)
+        for name in filter(pattern.fullmatch, names):
+            dis = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", f"--disassemble-symbols={name}", str(co)],
+                                 check=True, capture_output=True, text=True).stdout
             assert len(re.findall(r"\bglobal_load_", dis)) == Q + 1
             seen += 1
     assert seen == 2
