@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(BX * BY) k_step_batch(const Tables *__restrict
     // (left to itself the scheduler waits for every load in turn in this loop: 80 us a step instead of 50 for 26
     // lattices of sides 64..169)
     pull_ahead<ST, S, A>(tb, fi, sites, o, f);
-    const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
+    const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, -1) : -1.0);
     if (!mac.ok) *(volatile int *)err = 1;
     const uint32_t so = (uint32_t)site * (uint32_t)sizeof(S);
     put_pops<NT>(fo, sites, so, f);
@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(256) k_step_batch_lds(const Tables *__restrict
   A f[ST::Q];
   stage_pull<ST, S, A, false>(tb, fin + elem_off[d.x], sites, x0, y0, buf, f);
   if (x >= nx || y >= ny) return;
-  const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
+  const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, -1) : -1.0);
   if (!mac.ok) *err = 1;
   S *fo = fout + elem_off[d.x];
   const uint32_t so = (uint32_t)(y * nx + x) * (uint32_t)sizeof(S);

@@ -139,17 +139,18 @@ __device__ __forceinline__ void pull_prod(CTables *tb, const S *__restrict__ fin
 
 // Wall temperature of a site: negative off the walls; on the first or last
 // plane of a wall axis the prescribed temperature of that plane, or 0 for the
-// site's own temperature.
+// site's own temperature.  z < 0: a 2D lattice.
 __device__ __forceinline__ double site_wall(CTables *tb, int x, int y, int z) {
   double T = -1.0;
   auto axis = [&](int a, int v, int n) {
     // both planes' temperatures through scalar registers: a load of the lane's own would make every wave wait for the
     // populations that it has in flight (massive order 2, double, walls at 512 x 512: 23.1 us a step instead of 21.6)
+    if (!tb->wall[a]) return;
     double lo = tb->wallT[a][0], hi = tb->wallT[a][1];
     asm("" : "+s"(lo), "+s"(hi));
-    if (tb->wall[a]) T = v == 0 ? lo : (v == n - 1 ? hi : T);
+    T = v == 0 ? lo : (v == n - 1 ? hi : T);
   };
-  axis(2, z, tb->nz);   // the first axis last: it decides on the edges
+  if (z >= 0) axis(2, z, tb->nz);   // the first axis last: it decides on the edges
   axis(1, y, tb->ny);
   axis(0, x, tb->nx);
   return T;

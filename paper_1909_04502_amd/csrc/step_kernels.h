@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 
   A f[ST::Q];
   gather<ST, S, A>(tb, fin, sites, x, y, f);
   const double tau = tau_field != nullptr ? (double)tau1 : tb->tau;
-  const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
+  const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, -1) : -1.0);
   if (!mac.ok) flag_error(err);
   put_pops<NT>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (last.any) write_fields<ST::D>(last, site, sites, mac);
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tab
   if (x >= tb->nx || y >= tb->ny) return;
   const int64_t site = (int64_t)y * tb->nx + x;
   const double tau = site_tau<S>(tb, tau_field, site);
-  const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, 0) : -1.0);
+  const Macro<ST::D> mac = collide_site<ST, N, A, DEV, true, EXT>(tb, f, tau, EXT ? site_wall(tb, x, y, -1) : -1.0);
   if (!mac.ok) flag_error(err);
   put_pops<NT>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (last.any) write_fields<ST::D>(last, site, sites, mac);
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(256) k_init(const Tables *__restrict__ tabs, c
 #pragma unroll
   for (int i = 0; i < Q; ++i) f[i] = DEV ? (A)(fd[i] - tb->fref[i]) : (A)fd[i];
   const double tau = site_tau<S>(tb, tau_field, site);
-  const Macro<D> mac = collide_site<ST, N, A, DEV, true, true>(tb, f, tau, site_wall(tb, x, y, 0));
+  const Macro<D> mac = collide_site<ST, N, A, DEV, true, true>(tb, f, tau, site_wall(tb, x, y, -1));
   if (!mac.ok) flag_error(err);
   put_pops<false>(fout, sites, (uint32_t)site * (uint32_t)sizeof(S), f);
   if (fields0.any) write_fields<D>(fields0, site, sites, mac);
