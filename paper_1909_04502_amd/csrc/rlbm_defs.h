@@ -354,6 +354,13 @@ constexpr int kEosPieces = 5;
 constexpr double kEosTmin = 1.0 / 128.0, kEosTmax = 128.0;
 constexpr int kMaxPacked = 96;   // packed class blocks of Linv (91 entries for d = 3, N = 3)
 
+// The arrays that a kernel reads in runs (up to 64 bytes per scalar load) each start on a cache line.  When the equation
+// of state got shorter they had all moved to the middle of lines: the initial state of the 2D massless rule of order 3
+// took 159 us at 1025 x 1023 in double instead of 138, of the massive one 161 instead of 155; aligned 136 and 138.
+// Steps of 2D lattices change by -3 to +1.5 % (float 720 x 720 31.2 -> 30.5 us, massive order 3 512 x 512 34.5 -> 33.7,
+// float with double arithmetic 640 x 600 25.4 -> 25.6).
+constexpr int kLine = 128;
+
 struct Tables {
   // geometry and physics
   int32_t nx, ny, nz, pad0;
@@ -369,24 +376,24 @@ struct Tables {
   // EOS helper for d = 3: Chebyshev series in log z of h(z) = r(z) (z + 2) / z, r = K1(z)/K2(z),
   // on [cheb_lo, cheb_hi] = [log z_lo, log z_hi], one series per piece of equal width
   double cheb_lo, cheb_hi;
-  double cheb[kEosPieces][kEosTerms];
+  alignas(kLine) double cheb[kEosPieces][kEosTerms];
   int32_t cheb_n, chebT_n;
   // and the inverse of the equation of state: T = (e - m) u(x), x = log(e - m), u a Chebyshev
   // series in x on [chebT_lo, chebT_hi] (e = eps/n; the same temperature range), also by pieces
   // ([0]), next to h at that temperature as a series in the same variable ([1])
   double chebT_lo, chebT_hi;
-  double chebT[kEosPieces][2][kEosTerms];
+  alignas(kLine) double chebT[kEosPieces][2][kEosTerms];
   // per pair of antipodal populations (even member 2pr):
   double c[kMaxPairs][3];       // velocity p^a / p^0
   double mom_e[kMaxPairs][8];   // even moment weights: p0, p0^2, p^a p^b (upper triangle)
   double mom_o[kMaxPairs][6];   // odd moment weights: p^a, p0 p^a
-  double Re[kMaxPairs][kMaxNE]; // projection rows, even basis part
-  double Ro[kMaxPairs][kMaxNO]; // projection rows, odd basis part
-  double Rrest[kMaxNE];         // projection row of a rest population (p = (m, 0)), even part
+  alignas(kLine) double Re[kMaxPairs][kMaxNE]; // projection rows, even basis part
+  alignas(kLine) double Ro[kMaxPairs][kMaxNO]; // projection rows, odd basis part
+  alignas(kLine) double Rrest[kMaxNE];         // projection row of a rest population (p = (m, 0)), even part
   float Rrestf[kMaxNE];
   // on-lattice rules, per group g (p = (p0, v n), v = v0 p0, weight w, D = p0 - m):
   // p0, p0^2, v, p0 v, v^2, w v^l (l = 0..3), w D v^l (l = 0..3)
-  double mgrp[kMaxMassiveGroups][13];
+  alignas(kLine) double mgrp[kMaxMassiveGroups][13];
   float mgrpf[kMaxMassiveGroups][13];
   double wrest, v0;             // rest weight, lattice-speed parameter (1/5 for the printed massless rules)
   float wrestf, v0f;
@@ -400,24 +407,27 @@ struct Tables {
   // per population
   double tapw[kMaxQ][8];        // interpolation weights in the stencil's tap order
   float tapwf[kMaxQ][8];
-  double fref[kMaxQ];           // reference populations f^ref (F32_DEV)
+  alignas(kLine) double fref[kMaxQ];           // reference populations f^ref (F32_DEV)
   float freff[kMaxQ];
   // reference moments (F32_DEV): N^a, T^ab upper triangle, basis moments
-  double Nref[4];
+  alignas(kLine) double Nref[4];
   double Tref[10];
   double Mref[kMaxNM];
   // product rules, per shell j: speed |p|/p^0, moment factors and
   // equilibrium factors W_j (p^0 - m)^a |p|^l (W_j the shell weight; in 2D
   // the direction weight 1/8 is folded in)
-  double sv[kMaxShell];
+  alignas(kLine) double sv[kMaxShell];
   double smom[kMaxShell][5];       // p0, |p|, p0^2, p0 |p|, |p|^2
   double sfeq[kMaxShell][2][4];
-  double Linv[kMaxNM][kMaxNM];     // product rules: inverse Cholesky factor of the Gram matrix of (p^0 - m)^a p^e
-  double LinvP[kMaxPacked];        // its parity-class blocks, packed lower triangles (ClassTable order)
+  // product rules: inverse Cholesky factor of the Gram matrix of (p^0 - m)^a p^e, and its parity-class blocks, packed
+  // lower triangles (ClassTable order)
+  alignas(kLine) double Linv[kMaxNM][kMaxNM];
+  alignas(kLine) double LinvP[kMaxPacked];
   float svf[kMaxShell];
   float smomf[kMaxShell][5];
   float sfeqf[kMaxShell][2][4];
 };
+static_assert(sizeof(Tables) % kLine == 0, "and so do those of the next lattice of a batch");
 
 // Angular structure of the basis for product rules: each basis monomial
 // p0^a p^e is grouped by its angular multi-index e; m0[q] / m1[q] are the
