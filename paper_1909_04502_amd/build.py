@@ -14,7 +14,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["csrc/step_prod2d.hip", "csrc/step_ur2d.hip", "csrc/step_massive2d.hip",
            "csrc/split.hip", "csrc/split_onlat.hip", "csrc/split_ur3d.hip", "csrc/kernels.hip",
-           "csrc/api.hip", "csrc/adjoint.hip", "csrc/batch.hip", "csrc/bandwidth.hip", "csrc/precompute.cpp", "csrc/massive.cpp"]
+           "csrc/api.hip", "csrc/adjoint.hip", "csrc/adjoint_f64.hip", "csrc/batch.hip", "csrc/bandwidth.hip", "csrc/precompute.cpp", "csrc/massive.cpp"]
 LIB = os.path.join(HERE, "librlbm.so")
 
 FLAGS = [

@@ -375,3 +375,11 @@ def test_wall_temperatures_are_not_loaded_lane_by_lane(rlbm_lib, tmp_path):
             assert len(re.findall(r"\bglobal_load_", dis)) == Q + 1
             seen += 1
     assert seen == 2
+
+
+def test_double_reverse_step_fits_its_registers(rlbm_lib, tmp_path):
+    """Two waves per SIMD at order 2 (256 registers); at order 3 one wave, with a quarter of its 512 to spare."""
+    res = {n: r for n, r in kernel_resources(tmp_path).items() if re.search(r"k_adjointINS_7StencilILi1ELi[34]EEELi[23]Ed", n)}
+    assert len(res) == 2
+    for name, (vgprs, scratch) in res.items():
+        assert scratch == 0 and vgprs <= (256 if "ELi2Ed" in name else 384), (name, vgprs)
