@@ -59,8 +59,10 @@ __global__ void __launch_bounds__(BX * BY) k_step_batch(const Tables *__restrict
     }
     A f[ST::Q];
     // (left to itself the scheduler waits for every load in turn in this loop: 80 us a step instead of 50 for 26
-    // lattices of sides 64..169)
-    pull_ahead<ST, S, A>(tb, fi, sites, o, f);
+    // lattices of sides 64..169; not so at order 2 in double, where a shell ahead costs 26 registers and with them one
+    // of four waves per SIMD: 18.5 us instead of 17.9 for 16 lattices of those sides)
+    if constexpr (N == 2 && sizeof(S) == 8 && !EXT) pull_prod<ST, S, false, A>(tb, fi, sites, o, f);
+    else pull_ahead<ST, S, A>(tb, fi, sites, o, f);
     const Macro<ST::D> mac = collide_prod<ST, N, A, DEV, true, EXT>(tb, f, tb->tau, EXT ? site_wall(tb, x, y, -1) : -1.0);
     if (!mac.ok) *(volatile int *)err = 1;
     const uint32_t so = (uint32_t)site * (uint32_t)sizeof(S);

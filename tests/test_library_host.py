@@ -383,3 +383,9 @@ def test_double_reverse_step_fits_its_registers(rlbm_lib, tmp_path):
     assert len(res) == 2
     for name, (vgprs, scratch) in res.items():
         assert scratch == 0 and vgprs <= (256 if "ELi2Ed" in name else 384), (name, vgprs)
+
+
+def test_batch_order_2_in_double_keeps_four_waves(rlbm_lib, tmp_path):
+    res = {n: r for n, r in kernel_resources(tmp_path).items()
+           if re.search(r"k_step_batchINS_7StencilILi1ELi3EEELi2EdLb0ELi\d+ELi\dELb0E", n)}
+    assert len(res) == 6 and all(v <= 128 and scratch == 0 for v, scratch in res.values()), res
