@@ -255,7 +255,9 @@ rlbm_status rlbm_sync(rlbm_lattice *h, hipStream_t stream);
  * RLBM_STATIC_SCRATCH_BYTES on each GPU the library runs on, held until the
  * process ends; every configuration's tables fit it (the size is checked when
  * the library is built).  No hipMalloc, hipFree or other allocating device
- * call is made.
+ * call is made.  (Some step kernels, those of the 3D on-lattice rules among them,
+ * use scratch memory, which the HIP runtime keeps per queue and sets up at the
+ * queue's first such launch.)
  *
  * cfg is validated as by rlbm_create (same errors).  The first call on a GPU,
  * and each call whose configuration differs from the previous call's on that

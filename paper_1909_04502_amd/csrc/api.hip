@@ -215,7 +215,7 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
     if (cfg->bc[a] == RLBM_WALL && m.kind == RLBM_QUAD_UR_ONLATTICE)
       return fail(RLBM_ERR_UNSUPPORTED, "walls are built for the product and massive rules");
     if (cfg->bc[a] == RLBM_WALL && m.kind == RLBM_QUAD_MASSIVE_ONLATTICE && m.d == 3 && cfg->storage == RLBM_F64)
-      return fail(RLBM_ERR_UNSUPPORTED, "walls: the streaming kernel of the 3D massive rule has none");
+      return fail(RLBM_ERR_UNSUPPORTED, "walls are not built for the 3D massive rule in double storage");
     for (int e = 0; e < 2; ++e) {
       if (!(cfg->wall_T[a][e] >= 0.0) || !std::isfinite(cfg->wall_T[a][e]))
         return fail(RLBM_ERR_INVALID_ARG, "wall temperatures must be finite and >= 0");
@@ -229,7 +229,7 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
     return fail(RLBM_ERR_UNSUPPORTED, "the temperature-dependent tau is built for the on-lattice rules");
   if (m.kind == RLBM_QUAD_MASSIVE_ONLATTICE && m.d == 3 && cfg->storage == RLBM_F64 &&
       (cfg->force[0] != 0.0 || cfg->force[1] != 0.0 || cfg->force[2] != 0.0))
-    return fail(RLBM_ERR_UNSUPPORTED, "external force: the streaming kernel of the 3D massive rule has none");
+    return fail(RLBM_ERR_UNSUPPORTED, "an external force is not built for the 3D massive rule in double storage");
   if (cfg->storage != RLBM_F64 && cfg->storage != RLBM_F32_DEV && cfg->storage != RLBM_F32_DEV_F64)
     return fail(RLBM_ERR_INVALID_ARG, "bad storage");
   if (cfg->storage == RLBM_F32_DEV_F64 && m.kind != RLBM_QUAD_PRODUCT)
@@ -252,8 +252,8 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   //  * 2D product rules in double: rows of 64 sites; float storage with double arithmetic: 64 x 4
   //    band tiles of the occupancy-2 build (4 % faster than rows of 64); float storage and
   //    arithmetic: 64 x 4 band tiles of the occupancy-4 build (0.057 against 0.060 ms at 1024^2 for
-  //    the unconstrained one); in every storage the LDS-staged kernel on lattices larger than the
-  //    Infinity Cache (below);
+  //    the unconstrained one); the LDS-staged kernel on lattices larger than the Infinity Cache
+  //    (below);
   //  * 2D on-lattice rules: 64 x 4 tiles of the occupancy-2 build, except the massive rules whose
   //    update fits in 128 registers (order 2, and order 3 in float deviations), which take the
   //    occupancy-4 build: four waves per SIMD instead of three, 7-27 % faster; and small lattices
@@ -279,13 +279,13 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
       if (cfg->bc[a] == RLBM_PERIODIC && std::fabs(h->quad.disp[i * m.d + a]) > (double)cfg->extent[a])
         return fail(RLBM_ERR_INVALID_ARG, "a periodic extent is shorter than the stencil's longest displacement");
   // 2D product rules whose two states outgrow the Infinity Cache take the LDS-staged kernel, at any x extent and
-  // boundary (per step, register kernel -> staged; double 725 x 725 65 -> 58 us, 1026 x 1026 134 -> 120, 2048 x 2048
-  // 494 -> 372, walls and force 515 x 1021 67 -> 59, open x 705 x 777 75 -> 58, order 2 901 x 803 74 -> 58; float
-  // storage 1100 x 1100 85 -> 76, 2048 x 2048 232 -> 210).  Below that, where the halo re-reads hit that cache, the
-  // register kernels stay ahead (double 700 x 700 47.5 against 49.2 us; float storage 1024 x 1024 54 against 57).
-  // Float storage with double arithmetic gains from it with walls or a force (1203 x 1205 111 -> 105) and at order 2
-  // (1303 x 1205 80 -> 76); elsewhere the two are even to within the boxes' spread (1201 x 1101 91.2 and 91.2,
-  // 2048 x 2048 241 and 244, 250 and 254, once 277 and 310), and it stays with the register kernel except where the
+  // boundary (per step, register kernel -> staged; double 725 x 725 69 -> 59 us, 1026 x 1026 134 -> 120, 2048 x 2048
+  // 495 -> 371, walls and force 515 x 1021 70 -> 61, open x 705 x 777 73 -> 58, order 2 901 x 803 73 -> 59; float
+  // storage 1100 x 1100 85 -> 75, 2048 x 2048 230 -> 208).  Below that, where the halo re-reads hit that cache, the
+  // register kernels stay ahead (double 700 x 700 46.6 against 48.4 us; float storage 1024 x 1024 52 against 56).
+  // Float storage with double arithmetic gains from it with walls or a force (1203 x 1205 108 -> 106) and at order 2
+  // (1303 x 1205 80 -> 76); elsewhere the two are even to within the boxes' spread (1201 x 1101 92 and 91, 2048 x 2048
+  // 239 and 241, 250 and 254, once 277 and 310), and it stays with the register kernel except where the
   // staged one has been its default all along: past the non-temporal store threshold, on a periodic x axis of a
   // multiple of 4 sites.
   const int64_t both = 2 * (cfg->storage == RLBM_F64 ? 8 : 4) * (int64_t)h->quad.Q * sites;
@@ -640,10 +640,11 @@ rlbm_status rlbm_batch_create(const rlbm_config *cfgs, int32_t nlat, rlbm_batch 
     b->total_sites += h->sites;
   }
   // default launch: staged 64 x 4 tiles where the two states outgrow the Infinity Cache (96 lattices of sides
-  // 64..512, per step, runs of 256 sites -> staged: double 1440 -> 1184 us, float 799 -> 662, float with double
-  // arithmetic 878 -> 808; 404 MiB in double 119 -> 109, 296 MiB in float 117 -> 101).  Below that, runs of 256
-  // consecutive sites, no lane of which idles past a row's end (56 MiB in double 22 against 24 us), on the
-  // 2048-block grid in double and the 512-block grid in float
+  // 64..512, per step, runs of 256 sites -> staged: double 1175 -> 937 us, float 569 -> 494, float with double
+  // arithmetic 592 -> 565; 373 MiB in double 107 -> 93, 378 MiB in float 113 -> 100; with double arithmetic lattices of
+  // sides 128..300 are even, 378 MiB 114 -> 116, 649 MiB 194 -> 192, and larger ones not, 368 MiB of sides 200..500
+  // 113 -> 105).  Below that, runs of 256 consecutive sites, no lane of which idles past a row's end (137 MiB in double
+  // 28 against 31 us), on the 2048-block grid in double and the 512-block grid in float
   if (2 * b->total_elems * b->elem > kStagedFootprint) b->variant = 0;
   else b->variant = b->storage == RLBM_F64 ? 2 * 4 + rlbm::kBatchLinearTile : rlbm::kBatchLinearTile;
   hipError_t he = hipMalloc(&b->d_tabs, sizeof(rlbm::Tables) * nlat);

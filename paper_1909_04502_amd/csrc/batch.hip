@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(BX * BY) k_step_batch(const Tables *__restrict
 }
 
 // The 64 x 4 tiles of the batch, one per block, their populations pulled through LDS (stage2d.h).  96 lattices of
-// sides 64..512, 5.1 GiB in double: 1180 us a step, 4.7 TB/s of what it has to move, against 1440 for runs of 256
+// sides 64..512, 4.1 GiB in double: 937 us a step, 4.7 TB/s of what it has to move, against 1175 for runs of 256
 // sites pulled to registers, whose L1 is busy all the time with taps of 8 bytes per lane (97 loads per site for 32
 // populations).  Blocks of a finished tile make room for the next tile's loads, so none walks a list.
 template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, typename A = S>

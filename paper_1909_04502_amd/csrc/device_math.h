@@ -13,8 +13,8 @@ namespace rlbm {
 
 // The tables as kernels read them: in the constant address space, where uniform reads are scalar loads whatever
 // else the kernel does to memory (the 3D product rule in double: 97 x 130 x 83 0.54 ms a step instead of 0.60).
-// The 3D on-lattice rules read them as plain memory: with scalar loads moved freely past their stores the massive
-// rule takes 3.42 ms at 192^3 instead of 3.27.
+// The 3D on-lattice rules and the reverse step in double read them as plain memory: with scalar loads moved freely
+// past their stores the massive rule takes 3.42 ms at 192^3 instead of 3.27 (the reverse step: adjoint_f64.hip).
 #ifdef RLBM_TABLES_PLAIN
 typedef const Tables CTables;
 typedef const double CDouble;

@@ -14,10 +14,9 @@ struct FieldPtrs {
   int any;
 };
 
-// Launch variants of the step kernel: block shape bx x by x bz (2D lattices
-// fold bz into by), occupancy target (minimum waves per SIMD the compiler must
-// allow, 0 = its choice) and tile order (0 = as dealt, 1 = a contiguous band of
-// tiles per XCD, 2 = (y, z) patches per XCD in 3D, a band in 2D).  lds: the 2D
+// Launch variants of the 2D step kernels: block shape bx x (by bz), occupancy
+// target (minimum waves per SIMD the compiler must allow, 0 = its choice) and tile
+// order (0 = as dealt, else a contiguous band of tiles per XCD).  lds: the 2D
 // product rules stage their upstream windows in LDS (64 x 4 band tiles).
 // The 3D rules have one kernel and launch shape under every variant.
 struct Variant {

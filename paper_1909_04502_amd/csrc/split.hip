@@ -6,8 +6,8 @@
 // populations), forms that shell's direction sums and, once the macroscopic state is known, relaxes and
 // stores that shell.  One wave takes the sums of all shells to the state (the eigen-solve and the equation of
 // state), all of them share the projection by parity classes; sums, state and coefficients pass through LDS.
-// 125 to 159 registers per lane and up to 38 KB of LDS per block: four (float arithmetic) or three blocks of
-// four waves per CU, each in another phase, so that loads, arithmetic and stores of different blocks overlap.
+// 123 to 127 (float arithmetic) or 150 to 167 registers per lane and up to 38 KB of LDS per block: four or three
+// blocks of four waves per CU, each in another phase, so that loads, arithmetic and stores of different blocks overlap.
 //
 // What bounds it: the lines a CU's L1 fetches for the taps (198 of 128 bytes per wave in float storage, 52 of
 // them its own; L1-to-L2 reads of 650-770 cycles, 60 in flight per CU) and, in double, the waves' wait for the
@@ -15,12 +15,12 @@
 // storage and 3.05 of 3.60 ms in double; a copy of the same planes takes 1.17 and 2.35 ms.
 // Per step, against the register kernel that this one replaced (64 x 4 sites per block, one site per thread,
 // the equation of state in the same form):
-//   double 97 x 130 x 83     0.54 ms (3.2 TB/s of population traffic)   0.91
-//   double 192^3             3.6 ms (3.3 TB/s)                          4.1
-//   double 128^3, order 2    0.77 ms                                    2.8
+//   double 97 x 130 x 83     0.53 ms (3.3 TB/s of population traffic)   0.91
+//   double 192^3             3.2 to 3.6 ms (3.7 to 3.3 TB/s)            4.1
+//   double 128^3, order 2    0.71 ms                                    2.8
 //   float 256^3              4.1 ms (3.4 TB/s)                          4.2
-//   float, double arithmetic 256^3   4.5 ms                             6.1
-//   float 31 x 40 x 24       0.015 ms                                   0.021
+//   float, double arithmetic 256^3   4.6 ms                             6.1
+//   float 31 x 40 x 24       0.013 ms                                   0.021
 //
 // Sites are dealt to blocks in runs of 64 consecutive sites of a slab of kSlab rows (all rows of the
 // slab joined end to end, so that rows of any length fill their waves), slab by slab and plane by plane

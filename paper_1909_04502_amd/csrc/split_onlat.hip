@@ -3,15 +3,17 @@
 //
 // Wave w of a block takes some of the stencil's groups for 64 sites: it loads their populations (one load each:
 // integer shifts), adds up their part of the moments, and relaxes and stores them once the state is known.  So
-// every population is read once and stays in registers (38 values per lane).  One thread per site could not hold
-// all 143: the double form read 95 of them twice and waited for each group's second load, the float form spilled.
-// Bound by memory: 4.8-5.0 TB/s of population traffic at 192^3, where a plain copy of as many bytes reaches 5.7.
+// every population is read once (38 values per lane; the step kernels hold them in registers but for 10 values in
+// scratch, 13 with walls and force).  One thread per site could not hold all 143: the double form read 95 of them
+// twice and waited for each group's second load, the float form had 188 bytes of scratch per lane, now 44 or 56.
+// Bound by memory: 4.8-4.9 TB/s of population traffic at 192^3, where a plain copy of as many bytes reaches 5.7.
 // Per step, against one thread per site:
-//   192^3 double             3.25 ms    4.02
+//   192^3 double             3.28 ms    4.02
 //   130 x 97 x 83 double     0.56 ms    0.84
 //   192^3 float              1.68 ms    1.90
-//   40 x 33 x 30 double      0.030 ms   0.034
-// (occupancy targets: double 3 waves per SIMD, 2 gives 3.38 ms and 4 spills, 6.9; float 4, as fast as 3)
+//   40 x 33 x 30 double      0.028 ms   0.034
+// (occupancy targets: double 3 waves per SIMD, 2 gives 3.38 ms and 4 spills, 6.9; float 4: 3 spill nothing and are as
+// fast on large lattices, but 40 x 33 x 30 takes 21.9 us instead of 17.4)
 #define RLBM_TABLES_PLAIN   // device_math.h
 #include <hip/hip_runtime.h>
 

@@ -5,9 +5,9 @@
 // only what its direction reads: the tile's 4 rows, a fifth row on the upstream side where n_y != 0, and
 // one column element per row on the upstream side where n_x != 0.  Rows are loaded 4 bytes per lane, so
 // that any row start and any x extent will do, and lanes address their columns one by one, so that
-// periodic and open axes wrap and clamp as in the register kernels (or, WIDE, 16 bytes per lane: stage_wide).  Two buffers alternate: the loads of
-// shell j + 1 are in flight while the taps of shell j are read from LDS and summed; the block's four
-// waves share each window.  The taps, weights and summation order are those of pull_prod, so the
+// periodic and open axes wrap and clamp as in the register kernels (or, WIDE, 16 bytes per lane:
+// stage_wide).  Two buffers alternate: the loads of shell j + 1 are in flight while the taps of shell j
+// are read from LDS and summed; the block's four waves share each window.  The taps, weights and summation order are those of pull_prod, so the
 // populations are the same values to the last bit.
 //
 // What bounds the pull is the number of cache lines that a CU has in flight on their way to its L1 (some
@@ -349,9 +349,10 @@ __device__ __forceinline__ void stage_pull(CTables *tb, const S *__restrict__ fi
 
 // Rows may be loaded 16 bytes per lane: every row of every plane starts on 16 bytes and every chunk of 16 lies inside
 // the lattice or past its edge as a whole (an open x axis repeats its last site, so no chunk may lie past it).
-// Taken in double storage without walls and force, where a wave then issues 7 loads a shell instead of 20 (even in
-// time: 371.5 against 372.3 us at 2048 x 2048, 103.3 against 102.9 at 1024 x 1024); in float storage and with walls
-// the 4-byte loads are ahead (float 2048 x 2048 210 against 211.6 us, walls at 1024 x 1024 106.7 against 107.5).
+// Taken in double storage without walls and force, where a wave then issues 7 loads a shell instead of 20.  That is
+// all it gives: in time the two forms are even (2048 x 2048 371.4 and 371.5 us, 1024 x 1024 102.6 and 103.3,
+// 3000 x 1500 466 and 465); in float storage and with walls the 4-byte loads are ahead (float 2048 x 2048 210 against
+// 211.6 us, walls at 1024 x 1024 106.7 against 107.5).
 inline bool stage_wide(const void *fin, int nx, int elem, bool openx) {
   return (uintptr_t)fin % 16 == 0 && nx * elem % 16 == 0 && (!openx || nx % 64 == 0);
 }

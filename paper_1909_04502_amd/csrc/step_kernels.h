@@ -150,9 +150,10 @@ __device__ __forceinline__ bool site_coords(CTables *tb, const Tiling &tl, int &
 // at 512 x 512), by the taps' latency before them and by the launch, not by memory.  A fifth of those instructions
 // used to move scalars that did not fit the scalar registers (all planes' addresses and all tables at once) and to
 // form quotients for the tile's place: see one_after_another, from_here_on and tile_origin.  Per step, before ->
-// after: float 512 x 512 19.2 -> 17.1 us, 1024 x 1024 59 -> 53; float with double arithmetic 512 x 512 24.3 -> 19.8;
-// double 64 x 64 7.5 -> 5.7, 300 x 301 13.9 -> 12.4, walls and force 515 x 1021 67 -> 59; massive order 3 512 x 512
-// 39 -> 35 (a copy of its bytes takes 36); massless order 3 512 x 512 38 -> 34.
+// after: float 512 x 512 19.2 -> 16.4 us, 1024 x 1024 59 -> 52; float with double arithmetic 512 x 512 24.3 -> 19.8;
+// double 64 x 64 7.5 -> 5.7, 300 x 301 13.9 -> 12.4; massive order 3 512 x 512 39 -> 34 (a copy of its bytes takes 36);
+// massless order 3 512 x 512 38 -> 32.  Past the Infinity Cache the double build, which holds 209 registers instead of
+// 153, is 2-3 % slower than it was (1026 x 1026 130 -> 134): the staged kernel is the default there.
 template <class ST, int N, typename S, bool DEV, int OCC, bool EXT, bool NT, typename A = S>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 1, 8))) k_step(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                               S *__restrict__ fout, const void *__restrict__ tau_field,
@@ -177,10 +178,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 
 // One 64 x 4 tile per block in the band order, its populations pulled through LDS (stage2d.h).  Bound by
 // HBM where the two states do not fit the Infinity Cache: the register kernels fetch every row of a
 // window once per wave that reads it, which there costs memory traffic and lines in flight.  Per step,
-// order 3: 103 us at 1024 x 1024 in double (5.2 TB/s of what a step has to move, a copy's rate; register
-// kernel 121, windows of 5 full rows in 16-byte chunks 107), 60 with walls and a force at 700 x 801
-// (register 76), 119 at 1023 x 1025 (130), 373 at 2048 x 2048 (windows of full rows 394); order 2 at
-// 1025 x 1023 86 (107).
+// order 3: 103 us at 1024 x 1024 in double (5.2 TB/s of what a step has to move, the rate of an ordinary
+// copy; a non-temporal one reaches 5.9 in the same layout and 6.9 flat; register kernel 123, windows of 5
+// full rows in 16-byte chunks 107), 60 with walls and a force at 700 x 801 (register 76), 119 at
+// 1023 x 1025 (132), 371 at 2048 x 2048 (up to 410 on other boxes; register 495, windows of full rows
+// 394); order 2 at 1025 x 1023 87 (103).
 template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, bool WIDE, typename A = S>
 __global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                                   S *__restrict__ fout, const void *__restrict__ tau_field,

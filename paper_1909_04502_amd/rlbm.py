@@ -409,7 +409,7 @@ class Lattice:
 
 
 class Batch:
-    """Many 2D product-rule lattices advanced by one persistent launch per step (rlbm_batch_*).
+    """Many 2D product-rule lattices advanced by one launch per step (rlbm_batch_*).
 
     ``specs`` is a list of dicts with keys extent, zeta, tau (and optional bc).
     The state is one flat tensor of ``total_elems`` elements; ``view(f, l)``
