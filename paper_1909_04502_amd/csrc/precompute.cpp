@@ -444,8 +444,9 @@ static ld cheb_eval_pieces(const Series &coef, int n, ld u) {
 
 // e - m = m (r(m/T) - 1) + 3 T for d = 3 (e = eps/n = T (G_3 - 1), G_3 = z r + 4), with r from
 // the long double Bessel functions; its derivative in T is 3 - z^2 r'(z), r' = r^2 + 3 r/z - 1
-static ld kinetic_exact(ld m, ld T, ld &dk) {
-  const ld z = m / T, r = bessel_k(1.0L, z) / bessel_k(2.0L, z);
+static ld kinetic_exact(ld m, ld T, ld &dk, ld &r) {
+  const ld z = m / T;
+  r = bessel_k(1.0L, z) / bessel_k(2.0L, z);
   dk = 3.0L - z * z * (r * r + 3.0L * r / z - 1.0L);
   return m * (r - 1.0L) + 3.0L * T;
 }
@@ -459,8 +460,8 @@ static ld r_fitted(const Tables &t, const Series &h, ld z) {
 // the temperature of kinetic energy d per particle.  kinetic(T) increases in T from 1.5 T (cold)
 // to 3 T (hot), so the root lies in [d/3, d/1.5]: bisection on the kinetic energy of the fitted r
 // (cheap, and good to about 1e-12 where the cold cancellation magnifies the fit's rounding), then
-// safeguarded Newton steps on the exact kinetic energy
-static ld temperature_exact(const Tables &t, const Series &h, ld m, ld d) {
+// safeguarded Newton steps on the exact kinetic energy.  r: K1/K2 at m/T
+static ld temperature_exact(const Tables &t, const Series &h, ld m, ld d, ld &r) {
   ld lo = d / 3.05L, hi = d / 1.45L;
   {
     ld a = fmaxl(lo, (ld)kEosTmin), b = fminl(hi, (ld)kEosTmax);
@@ -472,10 +473,11 @@ static ld temperature_exact(const Tables &t, const Series &h, ld m, ld d) {
     lo = fmaxl(lo, 0.5L * (a + b) * (1.0L - 1e-6L));
     hi = fminl(hi, 0.5L * (a + b) * (1.0L + 1e-6L));
   }
-  ld T = 0.5L * (lo + hi);
+  ld T = 0.5L * (lo + hi), at = 0.0L;   // r is that of `at`
   for (int it = 0; it < 100; ++it) {
     ld dk;
-    const ld f = kinetic_exact(m, T, dk) - d;
+    at = T;
+    const ld f = kinetic_exact(m, T, dk, r) - d;
     if (f < 0.0L) lo = T;
     else hi = T;
     ld Tn = T - f / dk;
@@ -484,6 +486,7 @@ static ld temperature_exact(const Tables &t, const Series &h, ld m, ld d) {
     T = Tn;
     if (done) break;
   }
+  if (at != T) r = bessel_k(1.0L, m / T) / bessel_k(2.0L, m / T);
   return T;
 }
 
@@ -523,13 +526,13 @@ int build_eos_fit(double m, Tables &t, std::string &err) {
   // inverse: T = (e - m) u(x), x = log(e - m), over the same temperature range, fitted to the
   // exact equation of state (the kinetic energy m (r - 1) + 3 T cancels to 1.5 T from terms of
   // size m when cold, so it is taken from the long double Bessel functions, not the fitted r)
-  ld dk;
-  const ld xlo = logl(kinetic_exact(m, tmin, dk)), xhi = logl(kinetic_exact(m, tmax, dk));
+  ld dk, r;
+  const ld xlo = logl(kinetic_exact(m, tmin, dk, r)), xhi = logl(kinetic_exact(m, tmax, dk, r));
   // T/(e - m) and h(m/T) at the variable u of the whole range
   auto state = [&](ld u, ld &tq, ld &h) {
-    const ld d = expl(0.5L * (xhi + xlo) + 0.5L * (xhi - xlo) * u), T = temperature_exact(t, hs, m, d), z = m / T;
+    const ld d = expl(0.5L * (xhi + xlo) + 0.5L * (xhi - xlo) * u), T = temperature_exact(t, hs, m, d, r), z = m / T;
     tq = T / d;
-    h = bessel_k(1.0L, z) / bessel_k(2.0L, z) * (z + 2.0L) / z;
+    h = r * (z + 2.0L) / z;
   };
   for (int p = 0; p < kEosPieces; ++p) {
     ld tq[kFitNodes], h[kFitNodes];
