@@ -284,8 +284,8 @@ static rlbm_status prepare_lattice(const rlbm_config *cfg, rlbm_lattice *h, rlbm
   // storage 1100 x 1100 85 -> 75, 2048 x 2048 230 -> 208).  Below that, where the halo re-reads hit that cache, the
   // register kernels stay ahead (double 700 x 700 46.6 against 48.4 us; float storage 1024 x 1024 52 against 56).
   // Float storage with double arithmetic gains from it with walls or a force (1203 x 1205 108 -> 106) and at order 2
-  // (1303 x 1205 80 -> 76); elsewhere the two are even to within the boxes' spread (1201 x 1101 92 and 91, 2048 x 2048
-  // 239 and 241, 250 and 254, once 277 and 310), and it stays with the register kernel except where the
+  // (1303 x 1205 80 -> 76); elsewhere the two are even or the register kernel is ahead, by box (1201 x 1101 92 and 91,
+  // 2048 x 2048 239 and 241, 250 and 254, 263 and 279, 277 and 310), and it stays with that one except where the
   // staged one has been its default all along: past the non-temporal store threshold, on a periodic x axis of a
   // multiple of 4 sites.
   const int64_t both = 2 * (cfg->storage == RLBM_F64 ? 8 : 4) * (int64_t)h->quad.Q * sites;

@@ -9,9 +9,9 @@
 // 123 to 127 (float arithmetic) or 150 to 167 registers per lane and up to 38 KB of LDS per block: four or three
 // blocks of four waves per CU, each in another phase, so that loads, arithmetic and stores of different blocks overlap.
 //
-// What bounds it: the lines a CU's L1 fetches for the taps (198 of 128 bytes per wave in float storage, 52 of
-// them its own; L1-to-L2 reads of 650-770 cycles, 60 in flight per CU) and, in double, the waves' wait for the
-// one that solves for the state.  Pull and store alone take 1.41 of the step's 1.49 ms at 192^3 in float
+// What bounds it: the lines a CU's L1 fetches for the taps (195 of 128 bytes per wave in float storage, 52 of
+// them its own; L1-to-L2 reads of 690 cycles, 58 to 64 in flight per CU by its counters) and, in
+// double, the waves' wait for the one that solves for the state.  Pull and store alone take 1.41 of the step's 1.49 ms at 192^3 in float
 // storage and 3.05 of 3.60 ms in double; a copy of the same planes takes 1.17 and 2.35 ms.
 // Per step, against the register kernel that this one replaced (64 x 4 sites per block, one site per thread,
 // the equation of state in the same form):
