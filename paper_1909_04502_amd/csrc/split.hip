@@ -10,9 +10,9 @@
 // blocks of four waves per CU, each in another phase, so that loads, arithmetic and stores of different blocks overlap.
 //
 // What bounds it: the lines a CU's L1 fetches for the taps (195 of 128 bytes per wave in float storage, 52 of
-// them its own; L1-to-L2 reads of 690 cycles, 58 to 64 in flight per CU by its counters) and, in
-// double, the waves' wait for the one that solves for the state.  Pull and store alone take 1.41 of the step's 1.49 ms at 192^3 in float
-// storage and 3.05 of 3.60 ms in double; a copy of the same planes takes 1.17 and 2.35 ms.
+// them its own; L1-to-L2 reads of 690 cycles, 58 to 64 in flight per CU by its counters) and, in double, the
+// waves' wait for the one that solves for the state.  Pull and store alone take 1.41 of the step's 1.49 ms at
+// 192^3 in float storage and 3.05 of 3.60 ms in double; a copy of the same planes takes 1.17 and 2.35 ms.
 // Per step, against the register kernel that this one replaced (64 x 4 sites per block, one site per thread,
 // the equation of state in the same form):
 //   double 97 x 130 x 83     0.53 ms (3.3 TB/s of population traffic)   0.91

@@ -181,8 +181,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC > 
 // order 3: 103 us at 1024 x 1024 in double (5.2 TB/s of what a step has to move, the rate of an ordinary
 // copy; a non-temporal one reaches 5.9 in the same layout and 6.9 flat; register kernel 123, windows of 5
 // full rows in 16-byte chunks 107), 60 with walls and a force at 700 x 801 (register 76), 119 at
-// 1023 x 1025 (132), 371 at 2048 x 2048 (up to 410 on other boxes; register 495, windows of full rows
-// 394); order 2 at 1025 x 1023 87 (103).
+// 1023 x 1025 (132), 371 at 2048 x 2048 in long runs (395 to 413 over the first 22 launches; register 495
+// and 507, windows of full rows 394); order 2 at 1025 x 1023 87 (103).
 template <class ST, int N, typename S, bool DEV, bool EXT, bool NT, bool WIDE, typename A = S>
 __global__ void __launch_bounds__(256) k_step_lds(const Tables *__restrict__ tabs, const S *__restrict__ fin,
                                                   S *__restrict__ fout, const void *__restrict__ tau_field,
